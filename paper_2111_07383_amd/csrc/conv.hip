@@ -24,6 +24,7 @@
 #include "conv.hpp"
 #include "norm.hpp"
 #include "gather_mfma.hpp"
+#include "gather_split.hpp"
 #include "kgrad_mfma.hpp"
 
 namespace ssconv {
@@ -339,6 +340,14 @@ static bool use_bf16_kernel(ssconv_dtype dt, int64_t n_src, int ca, int cb, int 
   return dt == SSCONV_BF16 && debug_gather_variant() != 5 && gather_bf16_supported(n_src, ca, cb, K);
 }
 
+// fp32 on the bf16 matrix cores; the overrides that pick an fp32 MFMA variant keep that kernel, and a
+// fixed scratch region too small for the split operands does.
+static bool use_split(const CallScratch* sc, int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+  const int64_t v = debug_gather_variant();
+  if (v == 1 || v == 2 || v == 3 || v == 8 || !gather_split_supported(n_src, ca, cb, K)) return false;
+  return !(sc && sc->fixed()) || gather_split_bytes(n_src, ca, cb, n_pos, K) <= sc->left();
+}
+
 // Records the timing-hook events (ssconv_debug_set option 4) around one kernel launch.
 struct KernelTimer {
   hipEvent_t start = nullptr, stop = nullptr;
@@ -368,6 +377,11 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
     }
     scratch_give(sc, ws, st);
     return rc;
+  }
+  if (dt == SSCONV_F32 && use_split(sc, rb->n_in, cin, cout, rb->n_out, rb->K)) {
+    KernelTimer timer(st);
+    return gather_split((const float*)feats, rb->n_in, cin, {(const float*)W, 0, 0}, cout, rb->nbr, rb->n_out, rb->K,
+                        (float*)out, st, sc);
   }
   if (dt == SSCONV_F32) {
     KernelTimer timer(st);
@@ -503,6 +517,11 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
     nbrT = inv;
   }
   const int64_t nw = (int64_t)K * cin * cout;
+  if (dt == SSCONV_F32 && use_split(nullptr, rb->n_out, cout, cin, rb->n_in, K)) {
+    KernelTimer timer(st);
+    return gather_split((const float*)grad_out, rb->n_out, cout, {(const float*)W, 1, mirror ? 1 : 0}, cin, nbrT,
+                        rb->n_in, K, (float*)grad_feats, st, nullptr);
+  }
   if (dt == SSCONV_F32) {
     transpose_kernel<float><<<cdiv(nw, 256), 256, 0, st>>>((const float*)W, K, cout, cin, mirror, (float*)Wt);
     SSC_HIP(hipGetLastError());

@@ -1,0 +1,626 @@
+// fp32 output-stationary gather -> MFMA GEMM on the bf16 matrix cores (Sec. 3.2.3, Alg. 1):
+//
+//   out[x] = sum_s kappa(s) in[nbr[s][x]]
+//
+// Every fp32 value is the sum of three bf16 values (a0 = bf16(a), a1 = bf16(a - a0), a2 = the rest:
+// 24 bits, exact), so a product of two is six bf16 products -- a2 b0, a1 b1, a0 b2, a1 b0, a0 b1 and
+// a0 b0, summed in fp32 -- and three dropped ones below 2^-26 of it.  Six bf16 products cost 0.375 of
+// one fp32 MFMA product's matrix-core time.  The five small terms of a chunk are summed by
+// themselves and join the large sum once, so that the latter is rounded twice a chunk instead of six
+// times: errors against fp64 came out 0.3 - 0.8 of those of v_mfma_f32_16x16x4f32 on every layer tried.
+// What three parts cannot carry (infinities, NaN, values past bf16's largest, results under 2^-100)
+// is recomputed by plain fp32 multiply-adds.
+//
+// Bound: the matrix cores (55 - 60% busy) and the texture path that feeds the LDS (63 KB of DMA per
+// 256 x 112 x 32 chunk).  Two workgroup-wide stages of 69 KB fill the LDS; tall tiles because LDS
+// reads per product fall with the tile (256 rows: 93 bytes a clock of 128).  Measured on a 36 555-site
+// 5x5x5 layer, 104 -> 104: 1100 us (fp32 MFMA, 286 tiles on 256 compute units) -> 490 us.  On the way:
+// chunks that straddle two 64-byte parts 544 us against 496 aligned; DMAs issued in one burst 568
+// against 534 spread out; kappa and rows always from L2 (a probe) 510 against 544, so memory is not it.
+#include <algorithm>
+
+#include "conv.hpp"
+#include "gather_split.hpp"
+#include "lds_dma.hpp"
+
+namespace ssconv {
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kNT = 512;                     // 8 wavefronts, two per SIMD
+constexpr int kMaxK = 128;
+constexpr int kLdsLimit = 160 * 1024;
+constexpr int kMaxWG = 256;                  // one workgroup per compute unit
+constexpr uint32_t kAbsent = 0x80000000u;    // row offset past any operand: the DMA writes zeros
+constexpr int kBufferWord3 = 0x00020000;     // buffer descriptor word 3 for gfx9-family raw loads
+
+// Split rows: [row][ceil(ca / 32)][3 parts][32 channels] bf16, zero past ca; 192 bytes per 32 channels.
+__host__ __device__ __forceinline__ int chunks32(int ca) { return (ca + 31) / 32; }
+__host__ __device__ __forceinline__ int pad8(int c) { return (c + 7) & ~7; }
+// channels of a kappa row: whole 8-channel groups, and whole chunks where the last one is padded (a rest of 24)
+__host__ __device__ __forceinline__ int pad_k(int c) { return pad8(c) % 32 == 24 ? pad8(c) + 8 : pad8(c); }
+__host__ __device__ __forceinline__ int pad16(int c) { return (c + 15) & ~15; }
+
+__device__ __forceinline__ void split3(float x, uint16_t* p) {
+  p[0] = f32_to_bf16_rne(x);
+  const float r1 = x - bf16_to_f32(p[0]);
+  p[1] = f32_to_bf16_rne(r1);
+  p[2] = f32_to_bf16_rne(r1 - bf16_to_f32(p[1]));
+}
+
+__device__ __forceinline__ void store_parts(const uint16_t (*e)[3], uint16_t* dst, int64_t step) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    uint16_t t[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = e[j][p];
+    uint4 v;
+    __builtin_memcpy(&v, t, 16);
+    *reinterpret_cast<uint4*>(dst + p * step) = v;
+  }
+}
+
+// Both operands in one launch: blocks below row_blocks split the gathered rows (a thread takes 8
+// channels of one row), the others kappa into B3[s][pad_k(ca) / 8][3 parts][cb16][8] (zeros
+// past the end), a thread one 8-channel run of one column.
+__global__ __launch_bounds__(256) void split_operands(const float* __restrict__ src, int64_t n_src, int ca,
+                                                      unsigned row_blocks, SplitKernel B, int K, int cb,
+                                                      uint16_t* __restrict__ A3, uint16_t* __restrict__ B3) {
+  uint16_t e[8][3];
+  if (blockIdx.x < row_blocks) {
+    const int cc = chunks32(ca), per = 4 * cc;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n_src * per) return;
+    const int64_t r = i / per;
+    const int q = (int)(i - r * per), c0 = 8 * q;
+    const float* s = src + r * ca + c0;
+    float v[8];
+    if ((ca & 3) == 0 && c0 + 8 <= ca) {
+      const float4 a = *reinterpret_cast<const float4*>(s), b = *reinterpret_cast<const float4*>(s + 4);
+      v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = c0 + j < ca ? s[j] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) split3(v[j], e[j]);
+    store_parts(e, A3 + (r * cc + (q >> 2)) * 96 + 8 * (q & 3), 32);
+    return;
+  }
+  const int cg = pad_k(ca) / 8, cbp = pad16(cb);
+  const int64_t i = (int64_t)(blockIdx.x - row_blocks) * 256 + threadIdx.x;
+  if (i >= (int64_t)K * cg * cbp) return;
+  const int n = (int)(i % cbp);
+  const int64_t sc = i / cbp;
+  const int k0 = (int)(sc % cg) * 8;
+  const int64_t s = sc / cg, sw = B.mirror ? K - 1 - s : s;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float x = 0.f;
+    if (n < cb && k0 + j < ca) x = B.transposed ? B.W[(sw * ca + k0 + j) * cb + n] : B.W[(sw * cb + n) * ca + k0 + j];
+    split3(x, e[j]);
+  }
+  store_parts(e, B3 + (sc * 3 * cbp + n) * 8, (int64_t)cbp * 8);
+}
+
+// Workgroup i -> slot such that each XCD (i % 8) runs a contiguous range of slots.
+__device__ __forceinline__ int xcd_slot(int i, int n) {
+  const int x = i & 7, j = i >> 3, q = n >> 3, r = n & 7;
+  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
+}
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void dma16_buf(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t lds) {
+  const uint32_t l = __builtin_amdgcn_readfirstlane(lds);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(l), "v"(off), "s"(rsrc)
+               : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+// One output by plain fp32 multiply-adds: what a value that the split cannot carry (infinite, NaN,
+// above bf16's largest, or so small that its third part would be lost) makes of an output is
+// computed again this way.
+__device__ __forceinline__ float plain_dot(const float* __restrict__ src, int ca, const SplitKernel& B, int cb,
+                                           const int32_t* __restrict__ nbr, int64_t n_pos, int K, int64_t p, int n) {
+  float acc = 0.f;
+  for (int s = 0; s < K; ++s) {
+    const int r = nbr[(int64_t)s * n_pos + p];
+    if (r < 0) continue;
+    const int64_t sw = B.mirror ? K - 1 - s : s;
+    for (int k = 0; k < ca; ++k)
+      acc = fmaf(src[(int64_t)r * ca + k], B.transposed ? B.W[(sw * ca + k) * cb + n] : B.W[(sw * cb + n) * ca + k], acc);
+  }
+  return acc;
+}
+__device__ __forceinline__ bool doubtful(float v) {
+  const float a = fabsf(v);
+  return !(a <= 3.0e38f) || (a > 0.f && a < 7.9e-31f);  // 2^-100
+}
+
+// Tile of BM = 64 MR output rows x 16 NB columns.  Row group wm = w % 4 (MR 16-row blocks), column
+// group wn = w / 4 (ceil or floor of NB / 2 blocks); the two wavefronts of a SIMD have one of each.
+template <int NB, int MR>
+struct GS {
+  static constexpr int BM = 64 * MR, BN = 16 * NB;
+  static constexpr int WN0 = (NB + 1) / 2, WN1 = NB - WN0;
+  static constexpr int ABYTES = 4 * MR * 3 * 1024;           // gathered rows of one 32-channel chunk
+  static constexpr int STAGE = ABYTES + NB * 3 * 1024;       // + kappa
+  static constexpr int S = MR == 4 ? 2 : 3;                  // LDS stages
+  static constexpr int LA = (12 * MR + 7) / 8, LB = (3 * NB + 7) / 8, L = LA + LB;  // DMAs per wavefront per chunk
+  static constexpr int NRB = MR == 4 ? 2 : 1;                // row blocks a wavefront fetches
+  static constexpr int MISC = 1024 + kMaxK * 5 + 16;         // junk block, offset flags, offset list, count
+  static constexpr int PANEL = (kLdsLimit - S * STAGE - MISC) / (BM * 4);  // offsets whose row table fits
+  static constexpr size_t smem(int K) {
+    return (size_t)S * STAGE + MISC + (size_t)(K < PANEL ? K : PANEL) * BM * 4;
+  }
+};
+
+struct SplitPlan {
+  int G;           // workgroups
+  int mt, nt;      // row and column tiles
+  int64_t units;   // mt * nt * K: (tile, offset)
+};
+
+// Workgroup i takes the units [i * units / G, (i + 1) * units / G) of the (tile, offset) sequence, so
+// that every workgroup has the same number of offsets whatever the tile count.  A tile's first
+// piece (mostly the whole tile) is written to out; a workgroup that starts inside a tile leaves that piece
+// in part, slot i, and split_fixup adds the pieces in order.
+template <int NB, int MR>
+__global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __restrict__ A3, int64_t a_bytes, int ca,
+                                                           const uint16_t* __restrict__ B3, int cb,
+                                                           const int32_t* __restrict__ nbr, int64_t n_pos, int K,
+                                                           SplitPlan plan, float* __restrict__ part,
+                                                           const float* __restrict__ src, SplitKernel B,
+                                                           float* __restrict__ out) {
+  using G = GS<NB, MR>;
+  constexpr int BM = G::BM, S = G::S, NRB = G::NRB;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  char* stages = smem;
+  char* junk = smem + S * G::STAGE;
+  uint32_t* bmask = reinterpret_cast<uint32_t*>(junk + 1024);   // [kMaxK]
+  uint8_t* act = reinterpret_cast<uint8_t*>(bmask + kMaxK);     // [kMaxK]
+  int* n_act_p = reinterpret_cast<int*>(act + kMaxK);           // [4]
+  uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);    // [PANEL][BM] byte offsets of gathered rows
+
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = w & 3, wn = w >> 2;
+  const int wg = xcd_slot(blockIdx.x, plan.G);
+  const int64_t u_beg = wg * plan.units / plan.G, u_end = (wg + 1) * plan.units / plan.G;
+  const int cc = chunks32(ca), cap = pad_k(ca), cg = cap / 8, cbp = pad16(cb);
+  const uint32_t row_bytes = (uint32_t)cc * 192u;
+  const uint32_t stage0 = lds_addr(stages), junk_a = lds_addr(junk);
+  const __amdgpu_buffer_rsrc_t a_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A3), (short)0, (int)a_bytes, kBufferWord3);
+  const uint32_t bstep = 4u * 48u * (uint32_t)cbp;   // kappa: +4 channel groups per chunk
+  // A row's channels are read in whole 32-channel chunks (their 64-byte parts are aligned; straddling
+  // ones cost the texture path a second access per row) and a rest of 8 or 16, of which 4 or 2
+  // offsets share a chunk; 24 channels are padded to a chunk.
+  const int rest = cap % 32, full = cap / 32, quad = rest ? 32 / rest : 1;
+  const int g_slot = rest ? 8 * g / rest : 0, g_ch = rest ? 32 * full + 8 * g % rest : 0;
+
+  uint32_t boff[G::LB];  // kappa block e = w + 8 j: part e % 3 of column block e / 3
+#pragma unroll
+  for (int j = 0; j < G::LB; ++j) boff[j] = (uint32_t)((w + 8 * j) % 3 * cbp + (w + 8 * j) / 3 * 16) * 16u;
+
+  for (int64_t u = u_beg; u < u_end;) {
+    const int64_t t = u / K;
+    const int sa = (int)(u - t * K), sb = (int)(u_end - t * K < K ? u_end - t * K : K);
+    const int64_t p0 = (t / plan.nt) * BM;
+    const int n0 = (int)(t % plan.nt) * G::BN;
+
+    f4 acc[MR][G::WN0];
+#pragma unroll
+    for (int mb = 0; mb < MR; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < G::WN0; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
+
+    // panels of near-equal numbers of offsets whose row table fits the LDS
+    const int npan = (sb - sa + G::PANEL - 1) / G::PANEL;
+    for (int pn = 0; pn < npan; ++pn) {
+      const int s0 = sa + (sb - sa) * pn / npan, s1 = sa + (sb - sa) * (pn + 1) / npan, ns = s1 - s0;
+      // 1. rows of the tile at every offset of the panel (byte offsets, kAbsent: no neighbour) and the
+      //    offsets that occur at all, in order
+      __syncthreads();  // the previous panel (or tile) is done with the table and the stages
+      for (int s = tid; s < ns; s += kNT) bmask[s] = 0u;
+      __syncthreads();
+      {
+        constexpr int STEP = kNT / BM;  // offsets read side by side
+        int et = tid;
+        asm volatile("" : "+v"(et));
+        const int r = et % BM;
+        const int64_t p = p0 + r;
+        const bool in = p < n_pos;
+        for (int j0 = et / BM; j0 < ns; j0 += 8 * STEP) {
+          int v[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            v[j] = in && j0 + STEP * j < ns ? nbr[(int64_t)(s0 + j0 + STEP * j) * n_pos + p] : -1;
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (j0 + STEP * j < ns) {
+              rows[(j0 + STEP * j) * BM + r] = v[j] >= 0 ? (uint32_t)v[j] * row_bytes : kAbsent;
+              if (v[j] >= 0) bmask[j0 + STEP * j] = 1u;
+            }
+        }
+      }
+      __syncthreads();
+      if (w == 0) {
+        int base = 0;
+        for (int j0 = 0; j0 < ns; j0 += 64) {
+          const int j = j0 + lane;
+          const bool a = j < ns && bmask[j] != 0;
+          const uint64_t b = __ballot(a);
+          if (a) act[base + __popcll(b & ((1ull << lane) - 1ull))] = (uint8_t)j;
+          base += __popcll(b);
+        }
+        if (lane == 0) n_act_p[0] = base;
+      }
+      __syncthreads();
+      const int n_act = __builtin_amdgcn_readfirstlane(n_act_p[0]);
+      const int nchunk = n_act * full + (rest ? (n_act + quad - 1) / quad : 0);
+
+      // 2. the chunk being fetched: full ones of slot r_slot at channel 32 r_f + 8 g, then the rests of
+      //    the `quad` slots from r_base on, lane group g taking its share
+      int r_base = 0, r_slot = 0, r_f = 0;
+      uint32_t arow[NRB], bbase, achan;
+      auto refresh = [&](int slot, int ch) {
+        const bool live = slot < n_act;
+        const int j = live ? act[slot] : 0;
+        achan = (uint32_t)(ch >> 5) * 192u + (ch & 31) * 2u;
+#pragma unroll
+        for (int q = 0; q < NRB; ++q)
+          arow[q] = live ? rows[j * BM + 16 * ((w + 8 * q) % (4 * MR)) + r16] : kAbsent;
+        bbase = live ? ((uint32_t)((s0 + j) * cg + (ch >> 3)) * 3u * (uint32_t)cbp + (uint32_t)(n0 + r16)) * 16u : 0u;
+      };
+      auto seek = [&]() {  // to the chunk at (r_base, r_slot, r_f = 0)
+        const int end = r_base + quad < n_act ? r_base + quad : n_act;
+        if (full == 0) r_slot = end;
+        if (r_slot < end)
+          refresh(r_slot, 8 * g);
+        else if (rest)
+          refresh(r_base + g_slot, g_ch);
+      };
+      // DMA q of this wavefront for the chunk going into stage k: q < LA a row block's part, else a
+      // part of a kappa block
+      auto dma = [&](int q, uint32_t sbase) {
+        if (q < G::LA) {
+          // row block w + 8 (q % 2) part q / 2 of 16 blocks; block w part q of 8; block w % 4 part w / 4 + 2 q of 4
+          const uint32_t row = arow[MR == 4 ? q & 1 : 0] + achan;
+          if constexpr (MR == 4)
+            dma16_buf(a_rsrc, row + (q >> 1) * 64u, sbase + w * 3072 + (q & 1) * 24576 + (q >> 1) * 1024);
+          else if constexpr (MR == 2)
+            dma16_buf(a_rsrc, row + q * 64u, sbase + w * 3072 + q * 1024);
+          else if (q == 0 || w < 4)
+            dma16_buf(a_rsrc, row + (wn + 2 * q) * 64u, sbase + wm * 3072 + (wn + 2 * q) * 1024);
+          else
+            dma16_buf(a_rsrc, kAbsent, junk_a);
+        } else {
+          const int j = q - G::LA;
+          if (8 * j + 8 <= 3 * NB || w < 3 * NB - 8 * j)
+            dma16_off(B3, bbase + boff[j], sbase + G::ABYTES + (w + 8 * j) * 1024);
+          else if (S > 2)
+            dma16_buf(a_rsrc, kAbsent, junk_a);
+        }
+      };
+      auto advance = [&]() {
+        const int end = r_base + quad < n_act ? r_base + quad : n_act;
+        if (r_slot < end) {
+          if (++r_f < full) {
+            achan += 192u;
+            bbase += bstep;
+            return;
+          }
+          r_f = 0;
+          ++r_slot;
+          if (r_slot == end && !rest) r_base = end;
+        } else {  // after the rests
+          r_base = r_slot = end;
+          r_f = 0;
+        }
+        seek();
+      };
+      seek();
+      wait_vm<0>();  // the waits below count this panel's DMAs alone
+      for (int c = 0; c < S - 1 && c < nchunk; ++c) {
+#pragma unroll
+        for (int q = 0; q < G::L; ++q) dma(q, stage0 + c * G::STAGE);
+        advance();
+      }
+
+      // 3. iteration c: this wavefront's DMAs of chunk c have landed, one barrier publishes them (and
+      //    retires the reads of the stage refilled next); the fragments are read one step ahead of the
+      //    MFMAs that use them, the DMAs of chunk c + S - 1 go out between the first steps
+#define SSG_RDA(d_, mb_)                                                                            \
+  _Pragma("unroll") for (int p = 0; p < 3; ++p)                                                     \
+    d_[p] = *reinterpret_cast<const uint4*>(sb_ + ((wm * MR + (mb_)) * 3 + p) * 1024 + 16 * lane)
+#define SSG_RDB(nb_)                                                                                \
+  _Pragma("unroll") for (int p = 0; p < 3; ++p)                                                     \
+    fb[nb_][p] = *reinterpret_cast<const uint4*>(sb_ + G::ABYTES + ((NOFF + (nb_)) * 3 + p) * 1024 + 16 * lane)
+#define SSG_LOOP(WNX_, NOFF_)                                                                       \
+  {                                                                                                 \
+    constexpr int WNX = WNX_;                                                                       \
+    const int NOFF = NOFF_;                                                                         \
+    constexpr int NP = WNX < 2 ? 1 : WNX / 2;   /* steps per row block: two columns, the last three if odd */ \
+    constexpr int NS = 2 * MR * NP;             /* places for DMAs: two per step */                 \
+    int k_ = 0, ki_ = S - 1;                                                                        \
+    for (int c = 0; c < nchunk; ++c) {                                                              \
+      if (c + S - 2 < nchunk)                                                                       \
+        wait_vm<(S - 2) * G::L>();                                                                  \
+      else                                                                                          \
+        wait_vm<0>();                                                                               \
+      __syncthreads();                                                                              \
+      const bool iss_ = c + S - 1 < nchunk;                                                         \
+      const char* sb_ = stages + k_ * G::STAGE;                                                     \
+      const uint32_t si_ = stage0 + ki_ * G::STAGE;                                                 \
+      uint4 fa[2][3], fb[WNX][3];                                                                   \
+      constexpr int W0 = NP == 1 ? WNX : 2;                                                         \
+      f4 low_[2][WNX - 2 * NP + 2];                                                                 \
+      /* in the order the products need them: the first may start after two reads */                \
+      _Pragma("unroll") for (int p = 0; p < 3; ++p) {                                               \
+        fa[0][2 - p] = *reinterpret_cast<const uint4*>(sb_ + (wm * MR * 3 + 2 - p) * 1024 + 16 * lane); \
+        _Pragma("unroll") for (int h = 0; h < W0; ++h)                                              \
+          fb[h][p] = *reinterpret_cast<const uint4*>(sb_ + G::ABYTES + ((NOFF + h) * 3 + p) * 1024 + 16 * lane); \
+      }                                                                                             \
+      __builtin_amdgcn_sched_barrier(0);                                                            \
+      _Pragma("unroll") for (int mb = 0; mb < MR; ++mb) {                                           \
+        _Pragma("unroll") for (int np = 0; np < NP; ++np) {                                         \
+          const int n1 = np == NP - 1 ? WNX : 2 * np + 2;                                           \
+          if (mb == 0 && np + 1 < NP) {                                                             \
+            _Pragma("unroll") for (int nb = n1; nb < (np + 2 == NP ? WNX : n1 + 2); ++nb) { SSG_RDB(nb % WNX); } \
+          }                                                                                         \
+          if (np == NP - 1 && mb + 1 < MR) { SSG_RDA(fa[(mb + 1) & 1], mb + 1); }                   \
+          _Pragma("unroll") for (int th = 0; th < 2; ++th) {                                        \
+            const int place = (mb * NP + np) * 2 + th;                                              \
+            _Pragma("unroll") for (int q = place * G::L / NS; q < (place + 1) * G::L / NS; ++q)     \
+              if (iss_) dma(q, si_);                                                                \
+            /* the step before: its small terms, long done, join the sum */                         \
+            if (th == 1 && mb * NP + np > 0) {                                                      \
+              const int pmb = np > 0 ? mb : mb - 1, pnp = np > 0 ? np - 1 : NP - 1;                 \
+              _Pragma("unroll") for (int nb = 2 * pnp; nb < (pnp == NP - 1 ? WNX : 2 * pnp + 2); ++nb) \
+                acc[pmb][nb] += low_[(pmb * NP + pnp) & 1][nb - 2 * pnp];                           \
+            }                                                                                       \
+            __builtin_amdgcn_sched_barrier(0);                                                      \
+            _Pragma("unroll") for (int term = 3 * th; term < 3 * th + 3; ++term) {                  \
+              constexpr int qa_[6] = {2, 1, 0, 1, 0, 0}, qb_[6] = {0, 1, 2, 0, 1, 0};               \
+              _Pragma("unroll") for (int nb = 2 * np; nb < n1; ++nb) {                              \
+                f4& lo = low_[(mb * NP + np) & 1][nb - 2 * np];                                     \
+                if (term == 0) lo = f4{0.f, 0.f, 0.f, 0.f};                                         \
+                f4& to = term == 5 ? acc[mb][nb] : lo;                                              \
+                to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                                       \
+                    __builtin_bit_cast(bf16x8, fa[mb & 1][qa_[term]]),                              \
+                    __builtin_bit_cast(bf16x8, fb[nb][qb_[term]]), to, 0, 0, 0);                    \
+              }                                                                                     \
+            }                                                                                       \
+            __builtin_amdgcn_sched_barrier(0);                                                      \
+          }                                                                                         \
+        }                                                                                           \
+      }                                                                                             \
+      if (iss_) advance();                                                                          \
+      _Pragma("unroll") for (int nb = 2 * NP - 2; nb < WNX; ++nb)                                   \
+        acc[MR - 1][nb] += low_[(MR * NP - 1) & 1][nb - 2 * NP + 2];                                \
+      k_ = k_ + 1 == S ? 0 : k_ + 1;                                                                \
+      ki_ = ki_ + 1 == S ? 0 : ki_ + 1;                                                             \
+    }                                                                                               \
+  }
+      if constexpr (G::WN0 == G::WN1) {
+        SSG_LOOP(G::WN0, wn * G::WN0)
+      } else {
+        if (wn == 0) SSG_LOOP(G::WN0, 0) else SSG_LOOP(G::WN1, G::WN0)
+      }
+#undef SSG_LOOP
+#undef SSG_RDA
+#undef SSG_RDB
+    }
+
+    // 4. the tile, or this workgroup's share of it
+    const bool whole = sa == 0 && sb == K;
+    // (the lane index again, opaque: its address arithmetic would otherwise be hoisted out of the tile
+    // loop and hold some 60 registers through the chunk loop)
+    int el = lane;
+    asm volatile("" : "+v"(el));
+    const int g = el >> 4, r16 = el & 15;
+    const int nbc = wn == 0 ? G::WN0 : G::WN1;
+    const int c0 = 16 * G::WN0 * wn;
+    if (sa == 0) {  // whole, or its first piece: straight to out
+      bool odd = false;
+#pragma unroll
+      for (int mb = 0; mb < MR; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t p = p0 + 16 * (wm * MR + mb) + 4 * g + i;
+          if (p >= n_pos) continue;
+#pragma unroll
+          for (int nb = 0; nb < G::WN0; ++nb) {
+            const int col = n0 + c0 + 16 * nb + r16;
+            if (nb < nbc && col < cb) {
+              out[p * cb + col] = acc[mb][nb][i];
+              odd |= doubtful(acc[mb][nb][i]);
+            }
+          }
+        }
+      if (odd && whole) {
+        for (int e = 0; e < MR * 4 * nbc; ++e) {
+          const int64_t p = p0 + 16 * (wm * MR + e / (4 * nbc)) + 4 * g + e / nbc % 4;
+          const int col = n0 + c0 + 16 * (e % nbc) + r16;
+          if (p < n_pos && col < cb && doubtful(out[p * cb + col]))
+            out[p * cb + col] = plain_dot(src, ca, B, cb, nbr, n_pos, K, p, col);
+        }
+      }
+    } else {
+      float* dst = part + (int64_t)wg * BM * G::BN;
+#pragma unroll
+      for (int mb = 0; mb < MR; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = 16 * (wm * MR + mb) + 4 * g + i;
+#pragma unroll
+          for (int nb = 0; nb < G::WN0; ++nb)
+            if (nb < nbc) dst[row * G::BN + c0 + 16 * nb + r16] = acc[mb][nb][i];
+        }
+    }
+    u = t * K + sb;
+  }
+}
+
+// Adds the pieces of the tiles that more than one workgroup held, in workgroup order.  A block takes
+// 1024 consecutive values of one tile.
+__global__ __launch_bounds__(256) void split_fixup(const float* __restrict__ part, SplitPlan plan, int K, int BM,
+                                                   int BN, int cb, const int32_t* __restrict__ nbr, int64_t n_pos,
+                                                   const float* __restrict__ src, int ca, SplitKernel B,
+                                                   float* __restrict__ out) {
+  const int64_t t = blockIdx.x, ua = t * K, ub = ua + K - 1;
+  auto owner = [&](int64_t u) {
+    int64_t i = u * plan.G / plan.units;
+    while ((i + 1) * plan.units / plan.G <= u) ++i;
+    while (i * plan.units / plan.G > u) --i;
+    return i;
+  };
+  const int64_t i0 = owner(ua), i1 = owner(ub);
+  if (i0 == i1) return;
+  const int e = (blockIdx.y * 256 + threadIdx.x) * 4, r = e / BN, c = e - r * BN;
+  const int64_t p = (t / plan.nt) * BM + r;
+  const int col = (int)(t % plan.nt) * BN + c;
+  if (r >= BM || p >= n_pos || col >= cb) return;
+  float* o = out + p * cb + col;
+  float v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = col + k < cb ? o[k] : 0.f;
+  for (int64_t i = i0 + 1; i <= i1; ++i) {
+    const float4 x = *reinterpret_cast<const float4*>(part + i * BM * BN + e);
+    v[0] += x.x, v[1] += x.y, v[2] += x.z, v[3] += x.w;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (col + k < cb && doubtful(v[k])) v[k] = plain_dot(src, ca, B, cb, nbr, n_pos, K, p, col + k);
+  if ((cb & 3) == 0) {
+    *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (col + k < cb) o[k] = v[k];
+  }
+}
+
+struct SplitShape {
+  int nb, mr;
+  SplitPlan plan;
+};
+
+size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+size_t a3_bytes(int64_t n_src, int ca) { return align256((size_t)n_src * chunks32(ca) * 192); }
+// (the column blocks of the last tile past cb16 read on past the end: up to 2 KB)
+size_t b3_bytes(int ca, int cb, int K) { return align256((size_t)K * pad_k(ca) * pad16(cb) * 6 + 2048); }
+bool whole_tiles(const SplitPlan& p, int K) { return p.units % ((int64_t)p.G * K) == 0; }
+size_t part_bytes(const SplitShape& s, int K) {
+  return whole_tiles(s.plan, K) ? 0 : (size_t)s.plan.G * 64 * s.mr * 16 * s.nb * 4;
+}
+size_t shape_bytes(const SplitShape& s, int64_t n_src, int ca, int cb, int K) {
+  return a3_bytes(n_src, ca) + b3_bytes(ca, cb, K) + part_bytes(s, K);
+}
+
+// Tile height and share of the workgroups.  A 32-channel chunk of an MR x NB tile takes about
+// 0.3 + 0.0625 MR NB us (measured: 2.07 us at 4 x 7; the constant part is the barrier and the first
+// fragment reads, which is why tall tiles win where there are rows enough).  Either every workgroup
+// holds whole tiles, in rounds of one per compute unit, or the (tile, offset) sequence is cut evenly
+// over the compute units, which costs the pieces' traffic and one more launch (8 us and up).  Shapes
+// whose scratch fits the fixed region of the allocation-free forward come first, so that it gives
+// the same bits.
+SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+  const int blocks = (cb + 15) / 16, tiles = (blocks + 7) / 8, per = (blocks + tiles - 1) / tiles;
+  SplitShape best, s;
+  s.nb = per <= 2 ? 2 : per <= 4 ? 4 : per;
+  s.plan.nt = (int)cdiv(cb, 16 * s.nb);
+  const double chunks = pad_k(ca) / 32.0 * K;
+  double best_cost = 0.0;
+  bool best_fits = false;
+  for (int i = 0; i < 6; ++i) {
+    s.mr = 4 >> (i >> 1);
+    s.plan.mt = (int)cdiv(n_pos, 64 * s.mr);
+    const int64_t nt = (int64_t)s.plan.mt * s.plan.nt;
+    s.plan.units = nt * K;
+    const bool cut = i & 1;
+    double cost = chunks * (0.3 + 0.0625 * s.mr * s.nb);
+    if (cut) {
+      s.plan.G = (int)std::min<int64_t>(kMaxWG, s.plan.units);
+      cost = cost * nt / s.plan.G + 8.0 + (double)part_bytes(s, K) / 4e6;
+    } else {
+      s.plan.G = (int)std::min<int64_t>(nt, INT32_MAX);
+      cost *= cdiv(nt, kMaxWG);
+    }
+    const bool fits = shape_bytes(s, n_src, ca, cb, K) <= SSCONV_NOALLOC_SCRATCH_BYTES;
+    if (i == 0 || (fits && !best_fits) || (fits == best_fits && cost < best_cost))
+      best = s, best_cost = cost, best_fits = fits;
+  }
+  return best;
+}
+
+template <int NB, int MR>
+int launch(const SplitShape& s, const uint16_t* A3, int64_t a_bytes, int ca, const uint16_t* B3, int cb,
+           const int32_t* nbr, int64_t n_pos, int K, float* part, const float* src, const SplitKernel& B, float* out,
+           hipStream_t st) {
+  auto kern = gather_split_kernel<NB, MR>;
+  const size_t smem = GS<NB, MR>::smem(K);
+  SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  kern<<<s.plan.G, kNT, smem, st>>>(A3, a_bytes, ca, B3, cb, nbr, n_pos, K, s.plan, part, src, B, out);
+  SSC_HIP(hipGetLastError());
+  return SSCONV_OK;
+}
+
+}  // namespace
+
+bool gather_split_supported(int64_t n_src, int ca, int cb, int K) {
+  return ca >= 1 && cb >= 1 && K >= 1 && K <= kMaxK && n_src >= 1 && a3_bytes(n_src, ca) < ((size_t)1 << 31) &&
+         b3_bytes(ca, cb, K) < ((size_t)1 << 31);
+}
+
+size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+  return shape_bytes(split_shape(n_src, ca, cb, n_pos, K), n_src, ca, cb, K);
+}
+
+int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, int cb, const int32_t* nbr,
+                 int64_t n_pos, int K, float* out, hipStream_t st, CallScratch* sc) {
+  if (n_pos == 0) return SSCONV_OK;
+  const SplitShape s = split_shape(n_src, ca, cb, n_pos, K);
+  char* ws = nullptr;
+  SSC_TRY(scratch_take(sc, (void**)&ws, shape_bytes(s, n_src, ca, cb, K), st));
+  uint16_t* A3 = (uint16_t*)ws;
+  uint16_t* B3 = (uint16_t*)(ws + a3_bytes(n_src, ca));
+  float* part = (float*)(ws + a3_bytes(n_src, ca) + b3_bytes(ca, cb, K));
+  const unsigned row_blocks = cdiv(n_src * 4 * chunks32(ca), 256);
+  const unsigned b_blocks = cdiv((int64_t)K * (pad_k(ca) / 8) * pad16(cb), 256);
+  split_operands<<<row_blocks + b_blocks, 256, 0, st>>>(src, n_src, ca, row_blocks, B, K, cb, A3, B3);
+  int rc = hipGetLastError() == hipSuccess ? SSCONV_OK : fail(SSCONV_E_HIP, "operand split launch failed");
+  const int64_t ab = (int64_t)n_src * chunks32(ca) * 192;
+#define SSG_GO(NB_, MR_) rc = launch<NB_, MR_>(s, A3, ab, ca, B3, cb, nbr, n_pos, K, part, src, B, out, st)
+#define SSG_NB(NB_)                                                   \
+  case NB_:                                                           \
+    if (s.mr == 4) SSG_GO(NB_, 4);                                    \
+    else if (s.mr == 2) SSG_GO(NB_, 2);                               \
+    else SSG_GO(NB_, 1);                                              \
+    break;
+  if (rc == SSCONV_OK) {
+    switch (s.nb) {
+      SSG_NB(2) SSG_NB(4) SSG_NB(5) SSG_NB(6) SSG_NB(7)
+      default:
+        if (s.mr == 4) SSG_GO(8, 4);
+        else if (s.mr == 2) SSG_GO(8, 2);
+        else SSG_GO(8, 1);
+    }
+  }
+#undef SSG_NB
+#undef SSG_GO
+  if (rc == SSCONV_OK && !whole_tiles(s.plan, K)) {
+    const int BM = 64 * s.mr, BN = 16 * s.nb;
+    dim3 grid((unsigned)(s.plan.mt * s.plan.nt), cdiv(BM * BN, 1024));
+    split_fixup<<<grid, 256, 0, st>>>(part, s.plan, K, BM, BN, cb, nbr, n_pos, src, ca, B, out);
+    if (hipGetLastError() != hipSuccess) rc = fail(SSCONV_E_HIP, "split fix-up launch failed");
+  }
+  scratch_give(sc, ws, st);
+  return rc;
+}
+
+}  // namespace ssconv

@@ -1,0 +1,23 @@
+// fp32 output-stationary gather GEMM on the bf16 matrix cores (three bf16 parts per value).
+#pragma once
+
+#include "common.hpp"
+
+namespace ssconv {
+
+// kappa as the kernels see it: B[s][n][k] = W[s][n][k], or W[s'][k][n] when transposed, s' = s or
+// K-1-s (mirror); W fp32.
+struct SplitKernel {
+  const float* W;
+  int transposed, mirror;
+};
+
+// True when the shape is handled (32-bit byte offsets into the split operands).
+bool gather_split_supported(int64_t n_src, int ca, int cb, int K);
+// Scratch of a call (the split operands and the partial tiles).
+size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K);
+// out[p][:] = sum_s B[s] (cb x ca) . src[nbr[s][p]] for p < n_pos; src [n_src, ca], out [n_pos, cb].
+int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, int cb, const int32_t* nbr,
+                 int64_t n_pos, int K, float* out, hipStream_t st, CallScratch* sc);
+
+}  // namespace ssconv
