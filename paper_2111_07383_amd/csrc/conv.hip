@@ -336,8 +336,13 @@ int dispatch_dw(const void* G, int cout, const void* F, int cin, const int32_t* 
 
 }  // namespace
 
-static bool use_bf16_kernel(ssconv_dtype dt, int64_t n_src, int ca, int cb, int K) {
-  return dt == SSCONV_BF16 && debug_gather_variant() != 5 && gather_bf16_supported(n_src, ca, cb, K);
+// The bf16 pipeline kernel.  With a fixed scratch region a call whose operands do not fit takes the
+// kernels that need none, except where packed kappa alone was always the limit (channels in multiples of
+// 8, at most 27 offsets): there the region's error stands.
+static bool use_bf16_kernel(const CallScratch* sc, ssconv_dtype dt, int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+  if (dt != SSCONV_BF16 || debug_gather_variant() == 5 || !gather_bf16_supported(n_src, ca, cb, K)) return false;
+  if (!(sc && sc->fixed()) || gather_bf16_bytes(n_src, ca, cb, n_pos, K) <= sc->left()) return true;
+  return ca % 8 == 0 && K <= 27 && (size_t)K * ca * cb * 2 > sc->left();
 }
 
 // fp32 on the bf16 matrix cores; the overrides that pick an fp32 MFMA variant keep that kernel, and a
@@ -387,17 +392,9 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
     KernelTimer timer(st);
     return dispatch_gg<float>(feats, rb->n_in, cin, W, cout, rb->nbr, rb->n_out, rb->K, out, st, sc, sink);
   }
-  if (use_bf16_kernel(dt, rb->n_in, cin, cout, rb->K)) {
-    // kappa packed for the bf16 kernel in a stream-ordered scratch buffer
-    void* Bp = nullptr;
-    SSC_TRY(scratch_take(sc, &Bp, (size_t)rb->K * cin * cout * 2, st));
-    int rc = pack_b_bf16(W, rb->K, cin, cout, false, false, Bp, st);
-    if (rc == SSCONV_OK) {
-      KernelTimer timer(st);
-      rc = gather_bf16(feats, rb->n_in, cin, Bp, cout, rb->nbr, nullptr, rb->n_out, rb->K, out, st, sink);
-    }
-    scratch_give(sc, Bp, st);
-    return rc;
+  if (use_bf16_kernel(sc, dt, rb->n_in, cin, cout, rb->n_out, rb->K)) {
+    KernelTimer timer(st);
+    return gather_bf16(feats, rb->n_in, cin, W, false, false, cout, rb->nbr, rb->n_out, rb->K, out, st, sc);
   }
   KernelTimer timer(st);
   return dispatch_gg<uint16_t>(feats, rb->n_in, cin, W, cout, rb->nbr, rb->n_out, rb->K, out, st, sc, sink);
@@ -528,11 +525,9 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
     KernelTimer timer(st);
     return dispatch_gg<float>(grad_out, rb->n_out, cout, Wt, cin, nbrT, rb->n_in, K, grad_feats, st);
   }
-  if (use_bf16_kernel(dt, rb->n_out, cout, cin, K)) {
-    // kappa^T packed for the bf16 kernel: Bp[s][o/8][i][o%8] = W[s'][o][i], s' = s or K-1-s
-    SSC_TRY(pack_b_bf16(W, K, cout, cin, true, mirror, Wt, st));
+  if (use_bf16_kernel(nullptr, dt, rb->n_out, cout, cin, rb->n_in, K)) {
     KernelTimer timer(st);
-    return gather_bf16(grad_out, rb->n_out, cout, Wt, cin, nbrT, nullptr, rb->n_in, K, grad_feats, st);
+    return gather_bf16(grad_out, rb->n_out, cout, W, true, mirror, cin, nbrT, rb->n_in, K, grad_feats, st, nullptr);
   }
   transpose_kernel<uint16_t><<<cdiv(nw, 256), 256, 0, st>>>((const uint16_t*)W, K, cout, cin, mirror, (uint16_t*)Wt);
   SSC_HIP(hipGetLastError());

@@ -1,33 +1,34 @@
 // bf16 output-stationary gather -> MFMA GEMM (Sec. 3.2.3, Alg. 1 feature update):
 //
-//   out[x] = sum_s kappa(s) in[nbr[s][x]]   for the 256 output rows x of a tile
+//   out[x] = sum_s kappa(s) in[nbr[s][x]]   for the 64 MR output rows x of a tile
 //
-// The reduction dimension is the concatenation, over the offsets present in the tile, of each
-// offset's input channels, cut into 32-wide chunks (one v_mfma_f32_16x16x32_bf16 step each);
-// a chunk may straddle two offsets, so no channel padding is paid per offset.
+// The reduction runs over the offsets present in the tile and their input channels, in chunks of 32
+// (one v_mfma_f32_16x16x32_bf16 step each): an offset's whole chunks first, then the rests of 8 or 16
+// channels of four or two offsets in one chunk (a rest of 24 is padded).
 //
 // Layout and data movement (gfx950), chosen from measurement:
-//   * eight wavefronts, two per SIMD: row group wm = w % 4 (64 rows) x column group wn = w / 4
+//   * eight wavefronts, two per SIMD: row group wm = w % 4 (MR 16-row blocks) x column group wn = w / 4
 //     (ceil(NB/2) or floor(NB/2) 16-column blocks); the two wavefronts of a SIMD cover
 //     complementary column groups, so with an odd block count the SIMD still does exactly the
 //     tile's MFMA work, and one wavefront issues MFMAs while the other is stalled on issue;
 //   * both operands reach LDS by DMA (16 bytes per lane, written at M0 + 16 * lane): gathered
 //     rows with buffer DMA on 32-bit row offsets (an absent neighbour gets an offset past the
 //     end of the buffer, which the hardware fills with zeros), kappa from a packed copy
-//     Bp[K][ca/8][cb][8] so that a 16-column block of one chunk is four contiguous 256-byte
+//     Bp[K][k / 8][cb16][8] so that a 16-column block of one chunk is four contiguous 256-byte
 //     runs; no operand is loaded into registers asynchronously;
 //   * four LDS stages: iteration c waits for its own DMAs of chunk c+1, publishes them with one
 //     barrier, then runs the MFMAs of chunk c with the LDS fragment reads of chunk c+1 and the
-//     four DMAs of chunk c+3 spread between the column blocks (issuing them in a burst stalls
+//     DMAs of chunk c+3 spread between the column blocks (issuing them in a burst stalls
 //     the wavefront for the texture path's whole backlog);
-//   * the row offsets of the tile are compacted per active offset once, and each lane reads the
-//     next offset's rows ahead, so crossing into the next offset costs no LDS round trip;
+//   * rows whose channels are not a multiple of 8 are copied once, padded with zeros to a multiple
+//     of 32 (64-byte pieces), so that every channel count takes this path;
+//   * offsets are taken in panels whose row table fits the LDS, so that every kernel size does;
 //   * tiles are mapped XCD-contiguously (workgroups are dispatched round-robin over the 8 XCDs;
-//     workgroup i runs tile (i % 8) * ceil(T / 8) + i / 8), so each XCD's L2 sees neighbouring
-//     tiles, which share gathered rows;
-//   * the epilogue stages each wavefront's rows in LDS and writes 16-byte pieces of rows.
+//     neighbouring tiles gather the same input rows and share that XCD's L2).
+#include <algorithm>
+
 #include "gather_mfma.hpp"
-#include "lds_dma.hpp"
+#include "gather_tile.hpp"
 #include "norm.hpp"
 
 namespace ssconv {
@@ -36,236 +37,136 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kNT = 512;        // 8 wavefronts, two per SIMD
-constexpr int kBM = 256;        // output rows per tile
-constexpr int kBK = 32;         // reduction channels per chunk
-constexpr int kD = 4;           // pipeline depth: LDS stages (gathered rows + kappa of one chunk)
-constexpr int kMaxK = 128;
-constexpr int kLdsLimit = 160 * 1024;
+constexpr int kD = 4;  // pipeline depth: LDS stages (gathered rows + kappa of one chunk)
 
-constexpr uint32_t kAbsent = 0x80000000u;         // row offset past any src: the DMA writes zeros
-constexpr int kBufferWord3 = 0x00020000;          // buffer descriptor word 3 for gfx9-family raw loads
-
-template <int NB>
+template <int NB, int MR>
 struct GB {
-  static constexpr int WN0 = (NB + 1) / 2;          // column blocks of column group 0
-  static constexpr int WN1 = NB - WN0;              // ... and of column group 1
-  static constexpr int ABYTES = (kBM / 16) * 1024;  // gathered rows of one chunk (16-row blocks)
-  static constexpr int STAGE = ABYTES + NB * 1024;  // + kappa blocks
-  static constexpr int L = 4;                       // DMAs per wavefront per chunk: 2 row blocks, 2 kappa slots
-  static constexpr int PITCH = WN0 * 32 + 16;       // bytes per staged output row in the epilogue
+  static constexpr int BM = 64 * MR, BN = 16 * NB;
+  static constexpr int WN0 = (NB + 1) / 2, WN1 = NB - WN0;  // column blocks of the two column groups
+  static constexpr int ABYTES = 4 * MR * 1024;              // gathered rows of one chunk (16-row blocks)
+  static constexpr int STAGE = ABYTES + NB * 1024;          // + kappa blocks
+  static constexpr int LA = (4 * MR + 7) / 8, LB = (NB + 7) / 8, L = LA + LB;  // DMAs per wavefront per chunk
+  static constexpr int NRB = MR == 4 ? 2 : 1;               // row blocks a wavefront fetches
+  static constexpr int PITCH = WN0 * 32 + 16;               // bytes per staged output row in the epilogue
+  static constexpr int FIT = (kTileLds - kD * STAGE - kTileMisc) / (BM * 4);
+  static constexpr int PANEL = FIT < kTileMaxK ? FIT : kTileMaxK;  // offsets whose row table fits
+  static constexpr size_t smem(int K) {
+    return (size_t)kD * STAGE + kTileMisc + (size_t)(K < PANEL ? K : PANEL) * BM * 4;
+  }
 };
 
-template <int NB>
-size_t bf16_smem(int K) {
-  return (size_t)kD * GB<NB>::STAGE + 1024 + kMaxK * 5 + 16 + (size_t)K * kBM * 4;
-}
-
-// Workgroup i -> tile index such that each XCD (i % 8) runs a contiguous range of tiles.
-__device__ __forceinline__ int64_t xcd_tile(int64_t i, int64_t total) {
-  const int64_t x = i & 7, j = i >> 3, q = total >> 3, r = total & 7;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-}
-
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-// 16 bytes per lane at byte offset off of the buffer described by rsrc into LDS at byte
-// lds + 16 * lane (buffer_load_dwordx4 with the LDS bit; an offset past the end of the buffer
-// writes zeros).  One wait state separates the M0 write from the DMA.
-__device__ __forceinline__ void dma16_buf(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t lds) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(lds);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(l), "v"(off), "s"(rsrc)
-               : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-template <int NB, bool kStats>
-__global__ __launch_bounds__(kNT) void gather_bf16_kernel(const uint16_t* __restrict__ src, int64_t src_bytes, int ca,
-                                                          const uint16_t* __restrict__ Bp, int cb,
-                                                          const int32_t* __restrict__ nbr,
-                                                          const int32_t* __restrict__ order, int64_t n_pos, int K,
-                                                          uint16_t* __restrict__ out, double* __restrict__ stats) {
-  using G = GB<NB>;
-  constexpr int WN0 = G::WN0, WN1 = G::WN1, L = G::L;
+// Pieces of tiles that more than one workgroup holds go to part (fp32, slot 2 i: the first tile of
+// workgroup i, 2 i + 1: its last) and are added in order by bf16_fixup; whole tiles go to out.
+template <int NB, int MR>
+__global__ __launch_bounds__(kTileThreads) void gather_bf16_kernel(const uint16_t* __restrict__ src, int64_t src_bytes,
+                                                                   int row_bytes, int ca,
+                                                                   const uint16_t* __restrict__ Bp, int cb,
+                                                                   const int32_t* __restrict__ nbr, int64_t n_pos, int K,
+                                                                   TilePlan plan, float* __restrict__ part,
+                                                                   uint16_t* __restrict__ out) {
+  using G = GB<NB, MR>;
+  constexpr int BM = G::BM, WN0 = G::WN0, WN1 = G::WN1, L = G::L, LA = G::LA, NRB = G::NRB;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char* stages = smem;                                         // kD * STAGE bytes
-  char* junk = smem + kD * G::STAGE;                           // 1 KB sink
-  uint32_t* bmask = reinterpret_cast<uint32_t*>(junk + 1024);  // [kMaxK]
-  uint8_t* act = reinterpret_cast<uint8_t*>(bmask + kMaxK);    // [kMaxK]
-  int* n_act_p = reinterpret_cast<int*>(act + kMaxK);          // [4]
-  uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);   // [K][kBM] byte offsets of gathered rows
+  char* stages = smem;                                           // kD * STAGE bytes
+  char* junk = smem + kD * G::STAGE;                             // 1 KB sink
+  uint32_t* bmask = reinterpret_cast<uint32_t*>(junk + 1024);    // [kTileMaxK]
+  uint8_t* act = reinterpret_cast<uint8_t*>(bmask + kTileMaxK);  // [kTileMaxK]
+  int* n_act_p = reinterpret_cast<int*>(act + kTileMaxK);        // [4]
+  uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);     // [PANEL][BM] byte offsets of gathered rows
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, scalar
   const int wm = w & 3, wn = w >> 2;  // row group and column group; SIMD w % 4 hosts (wm, 0), (wm, 1)
-  const int64_t lin = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  const int64_t t = xcd_tile(lin, (int64_t)gridDim.x * gridDim.y);
-  const int64_t p0 = (t / gridDim.y) * kBM;
-  const int n0 = (int)(t % gridDim.y) * NB * 16;
-  const uint32_t row_bytes = (uint32_t)ca * 2u;
-
-  // 1. neighbour rows of the tile (all offsets) as byte offsets into src (kAbsent: no neighbour)
-  //    and whether each offset occurs in the tile; thread tid owns tile row tid % 256 for the
-  //    offsets of parity tid / 256, and issues its loads in batches of 8 independent requests
-  for (int s = tid; s < K; s += kNT) bmask[s] = 0u;
-  __syncthreads();
-  {
-    const int r = tid & (kBM - 1), par = tid >> 8;
-    const int64_t p = p0 + r;
-    const bool in = p < n_pos;
-    for (int s0 = par; s0 < K; s0 += 16) {
-      int v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = (in && s0 + 2 * j < K) ? nbr[(int64_t)(s0 + 2 * j) * n_pos + p] : -1;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (s0 + 2 * j < K) {
-          rows[(s0 + 2 * j) * kBM + r] = v[j] >= 0 ? (uint32_t)v[j] * row_bytes : kAbsent;
-          if (v[j] >= 0) bmask[s0 + 2 * j] = 1u;
-        }
-      }
-    }
-  }
-  __syncthreads();
-  // 2. ordered list of the offsets present in the tile
-  if (w == 0) {
-    int base = 0;
-    for (int s0 = 0; s0 < K; s0 += 64) {
-      const int s = s0 + lane;
-      const bool a = s < K && bmask[s] != 0;
-      const uint64_t b = __ballot(a);
-      if (a) act[base + __popcll(b & ((1ull << lane) - 1ull))] = (uint8_t)s;
-      base += __popcll(b);
-    }
-    if (lane == 0) n_act_p[0] = base;
-  }
-  __syncthreads();
-  const int n_act = n_act_p[0];
-  // 3. compact the row table to the active offsets (slot j <- offset act[j] >= j; each thread
-  //    moves its own column in increasing j, so no entry is overwritten before it is read)
-  if (tid < kBM)
-    for (int j = 0; j < n_act; ++j) rows[j * kBM + tid] = rows[act[j] * kBM + tid];
-  __syncthreads();
-  const int nchunk = (n_act * ca + kBK - 1) / kBK;
-  const int cg8 = ca / 8;
+  const int wg = xcd_slot(blockIdx.x, plan.G);
+  const int64_t u_beg = wg * plan.units / plan.G, u_end = (wg + 1) * plan.units / plan.G;
+  const int cap = pad_k(ca), cg = cap / 8, cbp = pad16(cb);
+  const uint32_t stage0 = lds_addr(stages), junk_a = lds_addr(junk);
+  const uint32_t bstep = 64u * (uint32_t)cbp;  // packed kappa: +4 channel groups per chunk
+  const ChunkOrder order(cap, g);
 
   // Gathered rows are fetched with buffer DMA (32-bit offsets; an offset past the end of src
-  // writes zeros, which covers absent neighbours and the padding of the last chunk).
+  // writes zeros, which covers absent neighbours).
   const __amdgpu_buffer_rsrc_t src_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src), (short)0, (int)src_bytes, kBufferWord3);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src), (short)0, (int)src_bytes, kRawBufferWord3);
 
-  // DMA duty of this wavefront per chunk: row blocks w and w + 8, kappa blocks w and w + 8.
-  // This lane group's 8-channel run sits at flat position c*32 + 8g -> (slot, channel).  Per
-  // row block the byte offset of this lane's row for the current slot, and the next slot's,
-  // read ahead so that crossing into it needs no LDS round trip; per kappa block a byte offset
-  // into Bp.  Offsets advance by one chunk per issue and are recomputed only when the run
-  // crosses into the next offset.
-  int r_slot = 0, r_ch = 8 * g;
-  while (r_ch >= ca && r_slot < n_act) r_ch -= ca, ++r_slot;
-  const uint32_t stage0 = lds_addr(stages), junk_a = lds_addr(junk);
-  uint32_t arow[2], nrow[2], boff[2];
-  bool bok[2];
-  int s_cur = 0, s_nxt = 0, pslot = -1;
-  const uint32_t bstep = 64u * (uint32_t)cb;  // packed kappa: +4 channel groups per chunk
+  for (int64_t u = u_beg; u < u_end;) {
+    const int64_t t = u / K;
+    const int sa = (int)(u - t * K), sb = (int)(u_end - t * K < K ? u_end - t * K : K);
+    const int64_t p0 = plan.row0 + (t / plan.nt) * BM;
+    const int n0 = (int)(t % plan.nt) * G::BN;
 
-#define SSB_PREFETCH()                                                                              \
-  do {                                                                                              \
-    pslot = r_slot + 1;                                                                             \
-    const bool pl_ = pslot < n_act;                                                                 \
-    s_nxt = pl_ ? act[pslot] : 0;                                                                   \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                   \
-      nrow[j] = pl_ ? rows[pslot * kBM + 16 * (w + 8 * j) + r16] : kAbsent;                         \
-  } while (0)
-
-#define SSB_REFRESH()                                                                               \
-  do {                                                                                              \
-    const bool live_ = r_slot < n_act;                                                              \
-    if (r_slot == pslot) {                                                                          \
-      s_cur = s_nxt;                                                                                \
-      _Pragma("unroll") for (int j = 0; j < 2; ++j) arow[j] = nrow[j];                              \
-    } else {                                                                                        \
-      s_cur = live_ ? act[r_slot] : 0;                                                              \
-      _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                 \
-        arow[j] = live_ ? rows[r_slot * kBM + 16 * (w + 8 * j) + r16] : kAbsent;                    \
-    }                                                                                               \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j) {                                                 \
-      const int nb_ = w + 8 * j;                                                                    \
-      const int n_ = n0 + 16 * nb_ + r16;                                                           \
-      bok[j] = nb_ < NB && live_ && n_ < cb;                                                        \
-      boff[j] = bok[j] ? (((uint32_t)s_cur * cg8 + (uint32_t)(r_ch >> 3)) * (uint32_t)cb + n_) * 16u : 0u; \
-    }                                                                                               \
-    SSB_PREFETCH();                                                                                 \
-  } while (0)
-
-  // DMA q (0, 1: row blocks; 2, 3: kappa slots) of the chunk going into LDS stage k_
-#define SSB_DMA(q_, k_)                                                                             \
-  do {                                                                                              \
-    const int q__ = (q_);                                                                           \
-    const uint32_t sbase_ = stage0 + (k_) * G::STAGE;                                               \
-    if (q__ < 2) {                                                                                  \
-      dma16_buf(src_rsrc, arow[q__ & 1] + 2u * r_ch, sbase_ + (w + 8 * (q__ & 1)) * 1024);          \
-    } else {                                                                                        \
-      const int nb_ = w + 8 * (q__ & 1);                                                            \
-      dma16_off(Bp, boff[q__ & 1], nb_ < NB ? sbase_ + G::ABYTES + nb_ * 1024 : junk_a);            \
-    }                                                                                               \
-  } while (0)
-
-#define SSB_ADVANCE()                                                                               \
-  do {                                                                                              \
-    r_ch += kBK;                                                                                    \
-    if (r_ch >= ca) {                                                                               \
-      while (r_ch >= ca) r_ch -= ca, ++r_slot;                                                      \
-      SSB_REFRESH();                                                                                \
-    } else {                                                                                        \
-      _Pragma("unroll") for (int j = 0; j < 2; ++j) boff[j] += bok[j] ? bstep : 0u;                 \
-    }                                                                                               \
-  } while (0)
-
-#define SSB_ISSUE(k_)                                                                               \
-  do {                                                                                              \
-    _Pragma("unroll") for (int q = 0; q < L; ++q) SSB_DMA(q, k_);                                   \
-    SSB_ADVANCE();                                                                                  \
-  } while (0)
-
-  // fragments of the chunk in stage k_: this wavefront's four row blocks and its column blocks
-#define SSB_READ(da_, db_, WNX, NOFF, k_)                                                           \
-  do {                                                                                              \
-    const char* sb_ = stages + (k_) * G::STAGE;                                                     \
-    _Pragma("unroll") for (int mb = 0; mb < 4; ++mb)                                                \
-      da_[mb] = *reinterpret_cast<const uint4*>(sb_ + (4 * wm + mb) * 1024 + 16 * lane);            \
-    _Pragma("unroll") for (int nb = 0; nb < WNX; ++nb)                                              \
-      db_[nb] = *reinterpret_cast<const uint4*>(sb_ + G::ABYTES + ((NOFF) + nb) * 1024 + 16 * lane); \
-  } while (0)
-
-  SSB_REFRESH();
-
-  f4 acc[4][WN0];
+    f4 acc[MR][WN0];
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < MR; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < WN0; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int nb = 0; nb < WN0; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
 
-  if (nchunk > 0) SSB_ISSUE(0);
-  if (nchunk > 1) SSB_ISSUE(1);
-  if (nchunk > 2) SSB_ISSUE(2);
+    const int npan = (sb - sa + G::PANEL - 1) / G::PANEL;  // panels of near-equal numbers of offsets
+    for (int pn = 0; pn < npan; ++pn) {
+      const int s0 = sa + (sb - sa) * pn / npan, ns = sa + (sb - sa) * (pn + 1) / npan - s0;
+      const int n_act = load_panel<BM>(nbr, n_pos, p0, s0, ns, (uint32_t)row_bytes, rows, bmask, act, n_act_p);
+      const int nchunk = order.chunks(n_act);
 
-#define SSB_MMA(nb_, AC, BC)                                                                        \
+      // the chunk being fetched: this wavefront's rows and kappa position (byte offsets)
+      ChunkWalk walk;
+      uint32_t arow[NRB], bbase;
+      auto refresh = [&](int slot, int ch) {
+        const bool live = slot < n_act;
+        const int j = live ? act[slot] : 0;
+#pragma unroll
+        for (int q = 0; q < NRB; ++q)
+          arow[q] = live ? rows[j * BM + 16 * (MR == 1 ? wm : w + 8 * q) + r16] + 2u * ch : kAbsentRow32;
+        bbase = live ? ((uint32_t)((s0 + j) * cg + (ch >> 3)) * (uint32_t)cbp + (uint32_t)(n0 + r16)) * 16u : 0u;
+      };
+      // DMA q of this wavefront for the chunk going into the stage at LDS address sbase: q < LA row
+      // block w + 8 q, else kappa block w + 8 (q - LA)
+      auto dma = [&](int q, uint32_t sbase) {
+        if (q < LA) {
+          if (MR > 1 || w < 4)
+            dma16_tile(src_rsrc, arow[NRB == 2 ? q & 1 : 0], sbase + (w + 8 * q) * 1024);
+          else
+            dma16_tile(src_rsrc, kAbsentRow32, junk_a);
+        } else {
+          const int nb = w + 8 * (q - LA);
+          if (nb < NB)
+            dma16_off(Bp, bbase + (uint32_t)nb * 256u, sbase + G::ABYTES + nb * 1024);
+          else
+            dma16_tile(src_rsrc, kAbsentRow32, junk_a);
+        }
+      };
+      auto advance = [&]() {
+        walk.advance(order, n_act, g,
+                     [&]() {
+#pragma unroll
+                       for (int q = 0; q < NRB; ++q) arow[q] += 64u;
+                       bbase += bstep;
+                     },
+                     refresh);
+      };
+      walk.seek(order, n_act, g, refresh);
+      wait_vm<0>();  // the waits below count this panel's DMAs alone
+#pragma unroll
+      for (int c = 0; c < kD - 1; ++c)
+        if (c < nchunk) {
+#pragma unroll
+          for (int q = 0; q < L; ++q) dma(q, stage0 + c * G::STAGE);
+          advance();
+        }
+
+#define SSB_FRAG(da_, db_, u_, sb_, NOFF)                                                           \
   do {                                                                                              \
-    bf16x8 bv_;                                                                                     \
-    __builtin_memcpy(&bv_, &BC[nb_], 16);                                                           \
-    _Pragma("unroll") for (int mb = 0; mb < 4; ++mb) {                                              \
-      bf16x8 av_;                                                                                   \
-      __builtin_memcpy(&av_, &AC[mb], 16);                                                          \
-      acc[mb][nb_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av_, bv_, acc[mb][nb_], 0, 0, 0);      \
-    }                                                                                               \
+    if ((u_) < MR)                                                                                  \
+      da_[(u_) % MR] = *reinterpret_cast<const uint4*>((sb_) + (MR * wm + (u_)) * 1024 + 16 * lane); \
+    else if ((u_) - MR < WN1 || wn == 0)                                                            \
+      db_[(u_) - MR] = *reinterpret_cast<const uint4*>((sb_) + G::ABYTES + ((NOFF) + (u_) - MR) * 1024 + 16 * lane); \
   } while (0)
 
   // Iteration c (stage k = c % kD): wait for this wavefront's DMA of chunk c+1, publish it with a
   // barrier (which also retires every LDS read of the stage refilled next: it was read two
-  // chunks ago), read the fragments of chunk c+1, then the MFMAs of chunk c with the DMAs of
-  // chunk c+kD-1 spread between the column blocks (DMA q after column block q), so that the
-  // texture path drains while the matrix cores run.
-#define SSB_BODY(k_, AC, BC, AN, BN, WNX, NOFF)                                                     \
+  // chunks ago), then the MFMAs of chunk c with the fragment reads of chunk c+1 and the DMAs of
+  // chunk c+kD-1 spread between the column blocks, so that the texture path drains while the matrix
+  // cores run.
+#define SSB_BODY(k_, AC, BC, AN, BN_, WNX, NOFF)                                                    \
   {                                                                                                 \
     const int cc_ = c + (k_);                                                                       \
     if (cc_ >= nchunk) break;                                                                       \
@@ -276,41 +177,37 @@ __global__ __launch_bounds__(kNT) void gather_bf16_kernel(const uint16_t* __rest
     __syncthreads();                                                                                \
     const bool rd_ = cc_ + 1 < nchunk;                                                              \
     const bool iss_ = cc_ + kD - 1 < nchunk;                                                        \
-    constexpr int ks_ = ((k_) + kD - 1) % kD;                                                       \
+    const uint32_t si_ = stage0 + ((k_) + kD - 1) % kD * G::STAGE;                                  \
     const char* sbr_ = stages + (((k_) + 1) % kD) * G::STAGE;                                       \
+    constexpr int NR = MR + WNX, RPB = (NR + WNX - 1) / WNX, DPB = (L + WNX - 1) / WNX;             \
     __builtin_amdgcn_sched_barrier(0);                                                              \
     _Pragma("unroll") for (int nb = 0; nb < WNX; ++nb) {                                            \
-      SSB_MMA(nb, AC, BC);                                                                          \
+      if (nb < WN1 || wn == 0) /* the wider group's last block: a scalar branch */                  \
+        _Pragma("unroll") for (int mb = 0; mb < MR; ++mb)                                           \
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, AC[mb]), \
+                                                                __builtin_bit_cast(bf16x8, BC[nb]), acc[mb][nb], 0, 0, 0); \
       __builtin_amdgcn_sched_barrier(0);                                                            \
       if (rd_) {                                                                                    \
-        /* two fragment reads of chunk c+1 per column block: row blocks first, then kappa */        \
-        _Pragma("unroll") for (int u = 2 * nb; u < 2 * nb + 2; ++u) {                               \
-          if (u < 4)                                                                                \
-            AN[u & 3] = *reinterpret_cast<const uint4*>(sbr_ + (4 * wm + (u & 3)) * 1024 + 16 * lane); \
-          else if (u - 4 < WNX)                                                                     \
-            BN[(u - 4) % WNX] = *reinterpret_cast<const uint4*>(sbr_ + G::ABYTES + ((NOFF) + (u - 4) % WNX) * 1024 + 16 * lane); \
-        }                                                                                           \
+        _Pragma("unroll") for (int u = RPB * nb; u < (RPB * nb + RPB < NR ? RPB * nb + RPB : NR); ++u) \
+          SSB_FRAG(AN, BN_, u, sbr_, NOFF);                                                         \
       }                                                                                             \
-      if (nb < L && iss_) SSB_DMA(nb, ks_);                                                         \
+      if (iss_) {                                                                                   \
+        _Pragma("unroll") for (int q = DPB * nb; q < (DPB * nb + DPB < L ? DPB * nb + DPB : L); ++q) \
+          dma(q, si_);                                                                              \
+      }                                                                                             \
       __builtin_amdgcn_sched_barrier(0);                                                            \
     }                                                                                               \
-    if (rd_) {                                                                                      \
-      _Pragma("unroll") for (int u = 2 * WNX; u < 4 + WNX; ++u)                                     \
-        BN[(u - 4) % WNX] = *reinterpret_cast<const uint4*>(sbr_ + G::ABYTES + ((NOFF) + (u - 4) % WNX) * 1024 + 16 * lane); \
-    }                                                                                               \
-    _Pragma("unroll") for (int q = WNX; q < L; ++q)                                                 \
-      if (iss_) SSB_DMA(q, ks_);                                                                    \
-    if (iss_) SSB_ADVANCE();                                                                        \
+    if (iss_) advance();                                                                            \
   }
 
   // Four chunks per trip; the first body past the last chunk leaves the loop.
 #define SSB_LOOP(WNX, NOFF)                                                                         \
   {                                                                                                 \
-    uint4 fa0[4], fb0[WNX], fa1[4], fb1[WNX];                                                       \
+    uint4 fa0[MR], fb0[WNX], fa1[MR], fb1[WNX];                                                     \
     if (nchunk > 0) {                                                                               \
       if (nchunk > 2) wait_vm<2 * L>(); else wait_vm<0>();                                          \
       __syncthreads();                                                                              \
-      SSB_READ(fa0, fb0, WNX, NOFF, 0);                                                             \
+      _Pragma("unroll") for (int u = 0; u < MR + WNX; ++u) SSB_FRAG(fa0, fb0, u, stages, NOFF);     \
     }                                                                                               \
     for (int c = 0;; c += kD) {                                                                     \
       SSB_BODY(0, fa0, fb0, fa1, fb1, WNX, NOFF)                                                    \
@@ -319,209 +216,279 @@ __global__ __launch_bounds__(kNT) void gather_bf16_kernel(const uint16_t* __rest
       SSB_BODY(3, fa1, fb1, fa0, fb0, WNX, NOFF)                                                    \
     }                                                                                               \
   }
-
-  static_assert(kD == 4, "the unrolled chunk loop is written for four stages");
-  if constexpr (WN0 == WN1) {
-    SSB_LOOP(WN0, wn * WN0)
-  } else {
-    if (wn == 0) {
-      SSB_LOOP(WN0, 0)
-    } else {
-      SSB_LOOP(WN1, WN0)
-    }
-  }
+      static_assert(kD == 4, "the unrolled chunk loop is written for four stages");
+      SSB_LOOP(WN0, wn * WN0)
 #undef SSB_LOOP
 #undef SSB_BODY
-#undef SSB_MMA
-#undef SSB_READ
-#undef SSB_ISSUE
-#undef SSB_ADVANCE
-#undef SSB_DMA
-#undef SSB_REFRESH
-#undef SSB_PREFETCH
+#undef SSB_FRAG
+    }
 
-  // Epilogue: each wavefront stages its rows, 32 at a time, as bf16 in LDS (row pitch padded so
-  // the 2-byte writes of the four row groups fall in distinct banks) and writes them back as
-  // 16-byte pieces of its column range of the output rows.
-  static_assert(kNT / 64 * 32 * G::PITCH <= kD * G::STAGE, "epilogue staging must fit the stage area");
-  __syncthreads();  // every wavefront is done with the stage area
-  char* const ep = stages + w * 32 * G::PITCH;
-  const int nbc = wn == 0 ? WN0 : WN1;
-  const int col0 = n0 + 16 * WN0 * wn;
-  const bool vec = (cb & 7) == 0;
+    int el = lane;
+    asm volatile("" : "+v"(el));  // opaque: the address arithmetic below must not live through the chunk loop
+    const int eg = el >> 4, er = el & 15;
+    const int nbc = wn == 0 ? WN0 : WN1;
+    const int c0 = 16 * WN0 * wn;
+    if (sa == 0 && sb == K) {
+      // Whole tile: each wavefront stages its rows, up to 32 at a time, as bf16 in LDS (row pitch padded
+      // so the 2-byte writes of the four row groups fall in distinct banks) and writes them back as
+      // 16-byte pieces of its column range of the output rows.
+      constexpr int RP = MR < 2 ? 1 : 2;  // row blocks staged at a time
+      static_assert(kTileThreads / 64 * 16 * RP * G::PITCH <= kD * G::STAGE, "epilogue staging must fit the stage area");
+      __syncthreads();  // every wavefront is done with the stage area
+      char* const ep = stages + w * 16 * RP * G::PITCH;
+      const bool vec = (cb & 7) == 0;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+      for (int part_ = 0; part_ < MR / RP; ++part_) {
 #pragma unroll
-    for (int m2 = 0; m2 < 2; ++m2) {
-      const int mb = 2 * half + m2;
+        for (int m2 = 0; m2 < RP; ++m2)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+          for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int nb = 0; nb < WN0; ++nb)
-          if (nb < nbc)
-            *reinterpret_cast<uint16_t*>(ep + (16 * m2 + 4 * g + i) * G::PITCH + (16 * nb + r16) * 2) =
-                f32_to_bf16_rne(acc[mb][nb][i]);
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int pieces = 2 * nbc;  // 16-byte pieces per staged row
-    for (int e = lane; e < 32 * pieces; e += 64) {
-      const int r = e / pieces, q = e - r * pieces;
-      const int64_t p = p0 + 64 * wm + 32 * half + r;
-      const int col = col0 + 8 * q;
-      if (p >= n_pos || col >= cb) continue;
-      const int64_t row = order ? order[p] : p;
-      uint16_t* dst = out + row * cb + col;
-      const char* srcp = ep + r * G::PITCH + q * 16;
-      if (vec) {
-        *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(srcp);
-      } else {
-        const int n = cb - col < 8 ? cb - col : 8;
-        for (int j = 0; j < n; ++j) dst[j] = reinterpret_cast<const uint16_t*>(srcp)[j];
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  if constexpr (kStats) {
-    // Norm statistics of the stored (bf16) values, per column of the tile: each lane adds its 16
-    // rows in row order, the four lane groups are added pairwise (the same sum in every lane),
-    // then the four row groups in order; stats[(col * row tiles + row tile) * 2 + q] in fp64
-    static_assert(4 * NB * 16 * 16 <= kD * G::STAGE, "the statistics exchange must fit the stage area");
-    __syncthreads();  // every wavefront is done with its staged rows
-    double* red = reinterpret_cast<double*>(stages);  // [4 row groups][NB * 16 columns][2]
-#pragma unroll
-    for (int nb = 0; nb < WN0; ++nb) {
-      if (nb >= nbc) break;
-      double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int64_t p = p0 + 64 * wm + 16 * mb + 4 * g + i;
-          if (p < n_pos) {
-            const double v = bf16_to_f32(f32_to_bf16_rne(acc[mb][nb][i]));
-            s1 += v;
-            s2 = fma(v, v, s2);
+            for (int nb = 0; nb < WN0; ++nb)
+              if (nb < nbc)
+                *reinterpret_cast<uint16_t*>(ep + (16 * m2 + 4 * eg + i) * G::PITCH + (16 * nb + er) * 2) =
+                    f32_to_bf16_rne(acc[RP * part_ + m2][nb][i]);
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int pieces = 2 * nbc;  // 16-byte pieces per staged row
+        for (int e = el; e < 16 * RP * pieces; e += 64) {
+          const int r = e / pieces, q = e - r * pieces;
+          const int64_t p = p0 + 16 * MR * wm + 16 * RP * part_ + r;
+          const int col = n0 + c0 + 8 * q;
+          if (p >= n_pos || col >= cb) continue;
+          uint16_t* dst = out + p * cb + col;
+          const char* srcp = ep + r * G::PITCH + q * 16;
+          if (vec) {
+            *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(srcp);
+          } else {
+            const int n = cb - col < 8 ? cb - col : 8;
+            for (int j = 0; j < n; ++j) dst[j] = reinterpret_cast<const uint16_t*>(srcp)[j];
           }
         }
-      s1 += __shfl_xor(s1, 16, 64);
-      s2 += __shfl_xor(s2, 16, 64);
-      s1 += __shfl_xor(s1, 32, 64);
-      s2 += __shfl_xor(s2, 32, 64);
-      if (g == 0) {
-        const int c = 16 * WN0 * wn + 16 * nb + r16;
-        red[(wm * NB * 16 + c) * 2] = s1;
-        red[(wm * NB * 16 + c) * 2 + 1] = s2;
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       }
-    }
-    __syncthreads();
-    const int64_t mt = t / gridDim.y;
-    for (int c = tid; c < NB * 16; c += kNT) {
-      const int col = n0 + c;
-      if (col >= cb) continue;
-      double a = 0.0, b = 0.0;
+    } else {
+      float* dst = part + (int64_t)(2 * wg + (u == u_beg ? 0 : 1)) * BM * G::BN;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        a += red[(j * NB * 16 + c) * 2];
-        b += red[(j * NB * 16 + c) * 2 + 1];
-      }
-      stats[((int64_t)col * gridDim.x + mt) * 2] = a;
-      stats[((int64_t)col * gridDim.x + mt) * 2 + 1] = b;
+      for (int mb = 0; mb < MR; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int nb = 0; nb < WN0; ++nb)
+            if (nb < nbc)
+              dst[(16 * (wm * MR + mb) + 4 * eg + i) * G::BN + c0 + 16 * nb + er] = acc[mb][nb][i];
     }
+    u = t * K + sb;
   }
 }
 
-// Bp[s][k/8][n][k%8] from kappa given as Bt[s'][n][k] (transposed = 0) or as W[s'][k][n]
-// (transposed = 1), s' = s or K-1-s (mirror); one thread per 16-byte output vector.
-__global__ void pack_b_kernel(const uint16_t* __restrict__ W, int K, int ca, int cb, int transposed, int mirror,
-                              uint16_t* __restrict__ Bp) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int cg8 = ca / 8;
-  const int64_t total = (int64_t)K * cg8 * cb;
-  if (v >= total) return;
-  const int n = (int)(v % cb);
-  const int kg = (int)((v / cb) % cg8);
-  const int64_t s = mirror ? K - 1 - v / ((int64_t)cb * cg8) : v / ((int64_t)cb * cg8);
-  uint4 o;
-  if (!transposed) {
-    o = *reinterpret_cast<const uint4*>(W + (s * cb + n) * ca + 8 * kg);
+// Adds the pieces of the tiles that more than one workgroup held, in workgroup order.  A block takes
+// 1024 consecutive values of one tile.
+__global__ __launch_bounds__(256) void bf16_fixup(const float* __restrict__ part, TilePlan plan, int K, int BM, int BN,
+                                                  int cb, int64_t n_pos, uint16_t* __restrict__ out) {
+  const int64_t t = blockIdx.x;
+  const int64_t i0 = unit_owner(plan, t * K), i1 = unit_owner(plan, t * K + K - 1);
+  if (i0 == i1) return;
+  const int e = (blockIdx.y * 256 + threadIdx.x) * 4, r = e / BN, c = e - r * BN;
+  const int64_t p = plan.row0 + (t / plan.nt) * BM + r;
+  const int col = (int)(t % plan.nt) * BN + c;
+  if (r >= BM || p >= n_pos || col >= cb) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t i = i0; i <= i1; ++i) {
+    const int64_t slot = 2 * i + (i * plan.units / plan.G / K == t ? 0 : 1);
+    const float4 x = *reinterpret_cast<const float4*>(part + slot * BM * BN + e);
+    v[0] += x.x, v[1] += x.y, v[2] += x.z, v[3] += x.w;
+  }
+  uint16_t* o = out + p * cb + col;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (col + k < cb) o[k] = f32_to_bf16_rne(v[k]);
+}
+
+// One launch for both operands.  Blocks below row_blocks: rows [n][ca] -> [n][pad32(ca)], zeros past ca, a
+// thread per 8 channels (row_blocks = 0: the rows are read in place).  The others: Bp[s][k / 8][n][k % 8]
+// (pad_k(ca) / 8 groups of pad16(cb) columns, zeros past the ends) from kappa given as Bt[s'][n][k]
+// (transposed = 0) or as W[s'][k][n] (transposed = 1), s' = s or K-1-s (mirror), a thread per 16 bytes.
+__global__ __launch_bounds__(256) void pack_operands(const uint16_t* __restrict__ src, int64_t n_src, int ca,
+                                                     unsigned row_blocks, const uint16_t* __restrict__ W, int K, int cb,
+                                                     int transposed, int mirror, uint16_t* __restrict__ Ap,
+                                                     uint16_t* __restrict__ Bp) {
+  uint16_t e[8];
+  uint4 v;
+  if (blockIdx.x < row_blocks) {
+    const int per = pad32(ca) / 8;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n_src * per) return;
+    const int64_t r = i / per;
+    const int k0 = (int)(i - r * per) * 8;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) e[j] = k0 + j < ca ? src[r * ca + k0 + j] : (uint16_t)0;
+    __builtin_memcpy(&v, e, 16);
+    *reinterpret_cast<uint4*>(Ap + i * 8) = v;
+    return;
+  }
+  const int cg = pad_k(ca) / 8, cbp = pad16(cb);
+  const int64_t i = (int64_t)(blockIdx.x - row_blocks) * 256 + threadIdx.x;
+  if (i >= (int64_t)K * cg * cbp) return;
+  const int n = (int)(i % cbp), kg = (int)((i / cbp) % cg), k0 = 8 * kg;
+  const int64_t s = i / ((int64_t)cbp * cg), sw = mirror ? K - 1 - s : s;
+  if (!transposed && (ca & 7) == 0 && n < cb && k0 < ca) {
+    v = *reinterpret_cast<const uint4*>(W + (sw * cb + n) * ca + k0);
   } else {
-    uint16_t e[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) e[j] = W[(s * ca + 8 * kg + j) * cb + n];
-    __builtin_memcpy(&o, e, 16);
+    for (int j = 0; j < 8; ++j)
+      e[j] = n < cb && k0 + j < ca ? W[transposed ? (sw * ca + k0 + j) * cb + n : (sw * cb + n) * ca + k0 + j]
+                                   : (uint16_t)0;
+    __builtin_memcpy(&v, e, 16);
   }
-  *reinterpret_cast<uint4*>(Bp + v * 8) = o;
+  *reinterpret_cast<uint4*>(Bp + i * 8) = v;
 }
 
-template <int NB>
-int launch_bf16(const void* src, int64_t src_bytes, int ca, const void* Bp, int cb, const int32_t* nbr, const int32_t* order,
-                int64_t n_pos, int K, void* out, hipStream_t st, NormSink* sink) {
-  const size_t smem = bf16_smem<NB>(K);
-  auto kern = sink ? gather_bf16_kernel<NB, true> : gather_bf16_kernel<NB, false>;
-  SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  dim3 grid(cdiv(n_pos, kBM), cdiv(cb, NB * 16));
-  double* stats = nullptr;
-  if (sink) {
-    SSC_TRY(norm_sink_take(sink, grid.x, st));
-    stats = (double*)sink->ws;
+// The launches of a call: plan[0], and plan[1] for the rows a last round of tall tiles would leave most
+// compute units idle on (n = 1: none).
+struct Bf16Shape {
+  int nb, n, mr[2];
+  TilePlan plan[2];
+};
+
+size_t ap_bytes(int64_t n_src, int ca) { return ca % 8 == 0 ? 0 : align256((size_t)n_src * pad32(ca) * 2); }
+// (the column blocks of the last tile past cb16 read on past the end: up to 4 KB)
+size_t bp_bytes(int ca, int cb, int K) { return align256((size_t)K * pad_k(ca) * pad16(cb) * 2 + 4096); }
+size_t part_bytes(const TilePlan& p, int mr, int nb, int K) {
+  return whole_tiles(p, K) ? 0 : align256((size_t)2 * p.G * 64 * mr * 16 * nb * 4);
+}
+size_t shape_bytes(const Bf16Shape& s, int64_t n_src, int ca, int cb, int K) {
+  size_t part = 0;
+  for (int i = 0; i < s.n; ++i) part = std::max(part, part_bytes(s.plan[i], s.mr[i], s.nb, K));
+  return ap_bytes(n_src, ca) + bp_bytes(ca, cb, K) + part;
+}
+
+// A 32-channel chunk of an MR x NB tile takes about 0.15 + 0.012 MR NB us (measured 0.77 at 4 x 13).
+double chunk_us(int mr, int nb) { return 0.15 + 0.012 * mr * nb; }
+
+// The cheapest of whole and cut tiles of each height for rows row0 .. n_pos - 1 (a cut costs the pieces'
+// traffic and one more launch); plans whose pieces fit `room` bytes come first.
+TilePlan best_plan(int64_t row0, int64_t n_pos, int nt, int nb, int K, double chunks, size_t room, int* mr, double* cost) {
+  TilePlan best{}, p;
+  bool best_fits = false;
+  for (int i = 0; i < 6; ++i) {
+    const int m = 4 >> (i >> 1);
+    p.row0 = row0;
+    p.mt = (int)cdiv(n_pos - row0, 64 * m);
+    p.nt = nt;
+    const int64_t tiles = (int64_t)p.mt * nt;
+    p.units = tiles * K;
+    double c = chunks * chunk_us(m, nb);
+    if (i & 1) {
+      p.G = (int)std::min<int64_t>(kTileWG, p.units);
+      c = c * tiles / p.G + 8.0 + (double)part_bytes(p, m, nb, K) / 4e6;
+    } else {
+      p.G = (int)tiles;
+      c *= cdiv(tiles, kTileWG);
+    }
+    const bool fits = part_bytes(p, m, nb, K) <= room;
+    if (i == 0 || (fits && !best_fits) || (fits == best_fits && c < *cost))
+      best = p, best_fits = fits, *cost = c, *mr = m;
   }
-  kern<<<grid, kNT, smem, st>>>((const uint16_t*)src, src_bytes, ca, (const uint16_t*)Bp, cb, nbr, order, n_pos, K,
-                                (uint16_t*)out, stats);
-  SSC_HIP(hipGetLastError());
-  return SSCONV_OK;
+  return best;
 }
 
 // Column blocks per tile: the instantiated width that covers cb in the fewest, most even tiles.
 int bf16_nb(int cb) {
-  const int blocks = (cb + 15) / 16;
-  const int tiles = (blocks + 13) / 14;
-  const int per = (blocks + tiles - 1) / tiles;
-  return per <= 4 ? 4 : per <= 8 ? 8 : per <= 13 ? 13 : 14;
+  const int blocks = (cb + 15) / 16, tiles = (blocks + 13) / 14, per = (blocks + tiles - 1) / tiles;
+  return per <= 2 ? 2 : per <= 4 ? 4 : per <= 7 ? 7 : per <= 8 ? 8 : per <= 13 ? 13 : 14;
 }
 
-size_t bf16_smem_for(int nb, int K) {
-  switch (nb) {
-    case 4: return bf16_smem<4>(K);
-    case 8: return bf16_smem<8>(K);
-    case 13: return bf16_smem<13>(K);
-    default: return bf16_smem<14>(K);
+Bf16Shape bf16_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+  Bf16Shape s, two;
+  s.nb = two.nb = bf16_nb(cb);
+  const int nt = (int)cdiv(cb, 16 * s.nb);
+  const double chunks = pad_k(ca) / 32.0 * K;
+  const size_t used = ap_bytes(n_src, ca) + bp_bytes(ca, cb, K);
+  const size_t room = used < SSCONV_NOALLOC_SCRATCH_BYTES ? SSCONV_NOALLOC_SCRATCH_BYTES - used : 0;
+  double cost, tail;
+  s.n = 1;
+  s.plan[0] = best_plan(0, n_pos, nt, s.nb, K, chunks, room, &s.mr[0], &cost);
+  // full rounds of 256-row tiles, then the other rows by a plan of their own (about 6 us for the launch)
+  const int64_t rounds = n_pos / 256 * nt / kTileWG, mt = rounds * kTileWG / nt;
+  if (mt == 0 || mt * 256 >= n_pos) return s;
+  two.n = 2;
+  two.mr[0] = 4;
+  two.plan[0] = {(int)(mt * nt), (int)mt, nt, 0, mt * nt * K};
+  two.plan[1] = best_plan(mt * 256, n_pos, nt, s.nb, K, chunks, room, &two.mr[1], &tail);
+  return rounds * chunks * chunk_us(4, s.nb) + tail + 6.0 < cost ? two : s;
+}
+
+template <int NB, int MR>
+int launch_bf16(const TilePlan& plan, const void* src, int64_t src_bytes, int row_bytes, int ca, const void* Bp, int cb,
+                const int32_t* nbr, int64_t n_pos, int K, float* part, void* out, hipStream_t st) {
+  const size_t smem = GB<NB, MR>::smem(K);
+  auto kern = gather_bf16_kernel<NB, MR>;
+  SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  kern<<<plan.G, kTileThreads, smem, st>>>((const uint16_t*)src, src_bytes, row_bytes, ca, (const uint16_t*)Bp, cb, nbr,
+                                           n_pos, K, plan, part, (uint16_t*)out);
+  if (!whole_tiles(plan, K)) {
+    const int BM = 64 * MR, BN = 16 * NB;
+    bf16_fixup<<<dim3((unsigned)(plan.mt * plan.nt), cdiv(BM * BN, 1024)), 256, 0, st>>>(part, plan, K, BM, BN, cb, n_pos,
+                                                                                         (uint16_t*)out);
   }
+  SSC_HIP(hipGetLastError());
+  return SSCONV_OK;
 }
 
 }  // namespace
 
 bool gather_bf16_supported(int64_t n_src, int ca, int cb, int K) {
   // 32-bit byte offsets: every gathered row and every packed kappa entry below 2^31
-  return ca % 8 == 0 && ca >= 8 && cb >= 1 && K >= 1 && K <= kMaxK && n_src >= 0 &&
-         n_src * ca * 2 < ((int64_t)1 << 31) && (int64_t)K * ca * cb * 2 < ((int64_t)1 << 31) &&
-         bf16_smem_for(bf16_nb(cb), K) <= (size_t)kLdsLimit;
+  return ca >= 1 && cb >= 1 && K >= 1 && K <= kTileMaxK && n_src >= 0 &&
+         n_src * (ca % 8 == 0 ? ca : pad32(ca)) * 2 < ((int64_t)1 << 31) && bp_bytes(ca, cb, K) < ((size_t)1 << 31);
 }
 
-int pack_b_bf16(const void* W, int K, int ca, int cb, bool transposed, bool mirror, void* Bp, hipStream_t st) {
-  const int64_t total = (int64_t)K * (ca / 8) * cb;
-  if (total == 0) return SSCONV_OK;
-  pack_b_kernel<<<cdiv(total, 256), 256, 0, st>>>((const uint16_t*)W, K, ca, cb, transposed ? 1 : 0, mirror ? 1 : 0,
-                                                   (uint16_t*)Bp);
-  SSC_HIP(hipGetLastError());
-  return SSCONV_OK;
+size_t gather_bf16_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+  return shape_bytes(bf16_shape(n_src, ca, cb, n_pos, K), n_src, ca, cb, K);
 }
 
-int gather_bf16(const void* src, int64_t n_src, int ca, const void* Bp, int cb, const int32_t* nbr,
-                const int32_t* order, int64_t n_pos, int K, void* out, hipStream_t st, NormSink* sink) {
+int gather_bf16(const void* src, int64_t n_src, int ca, const void* W, bool transposed, bool mirror, int cb,
+                const int32_t* nbr, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc) {
   if (n_pos == 0) return SSCONV_OK;
-  if (!gather_bf16_supported(n_src, ca, cb, K))
-    return fail(SSCONV_E_INVALID, "bf16 gather kernel does not support this shape (K=%d)", K);
-  const int64_t sb = n_src * ca * 2;
-  switch (bf16_nb(cb)) {
-    case 4: return launch_bf16<4>(src, sb, ca, Bp, cb, nbr, order, n_pos, K, out, st, sink);
-    case 8: return launch_bf16<8>(src, sb, ca, Bp, cb, nbr, order, n_pos, K, out, st, sink);
-    case 13: return launch_bf16<13>(src, sb, ca, Bp, cb, nbr, order, n_pos, K, out, st, sink);
-    default: return launch_bf16<14>(src, sb, ca, Bp, cb, nbr, order, n_pos, K, out, st, sink);
+  const Bf16Shape s = bf16_shape(n_src, ca, cb, n_pos, K);
+  char* ws = nullptr;
+  SSC_TRY(scratch_take(sc, (void**)&ws, shape_bytes(s, n_src, ca, cb, K), st));
+  const bool pad = ca % 8 != 0;
+  uint16_t* Ap = (uint16_t*)ws;
+  uint16_t* Bp = (uint16_t*)(ws + ap_bytes(n_src, ca));
+  float* part = (float*)(ws + ap_bytes(n_src, ca) + bp_bytes(ca, cb, K));
+  const unsigned row_blocks = pad ? cdiv(n_src * (pad32(ca) / 8), 256) : 0;
+  const unsigned b_blocks = cdiv((int64_t)K * (pad_k(ca) / 8) * pad16(cb), 256);
+  pack_operands<<<row_blocks + b_blocks, 256, 0, st>>>((const uint16_t*)src, n_src, ca, row_blocks, (const uint16_t*)W, K,
+                                                       cb, transposed ? 1 : 0, mirror ? 1 : 0, Ap, Bp);
+  int rc = hipGetLastError() == hipSuccess ? SSCONV_OK : fail(SSCONV_E_HIP, "operand packing launch failed");
+  const void* A = pad ? (const void*)Ap : src;
+  const int row_bytes = 2 * (pad ? pad32(ca) : ca);
+  for (int i = 0; i < s.n && rc == SSCONV_OK; ++i) {
+#define SSB_GO(NB_, MR_) \
+  rc = launch_bf16<NB_, MR_>(s.plan[i], A, n_src * row_bytes, row_bytes, ca, Bp, cb, nbr, n_pos, K, part, out, st)
+#define SSB_NB(NB_)                      \
+  if (s.mr[i] == 4) SSB_GO(NB_, 4);      \
+  else if (s.mr[i] == 2) SSB_GO(NB_, 2); \
+  else SSB_GO(NB_, 1);                   \
+  break
+    switch (s.nb) {
+      case 2: SSB_NB(2);
+      case 4: SSB_NB(4);
+      case 7: SSB_NB(7);
+      case 8: SSB_NB(8);
+      case 13: SSB_NB(13);
+      default: SSB_NB(14);
+    }
+#undef SSB_NB
+#undef SSB_GO
   }
+  scratch_give(sc, ws, st);
+  return rc;
 }
 
 }  // namespace ssconv

@@ -19,16 +19,13 @@ int gather_mfma(const void* src, int64_t n_src, ssconv_dtype dt, int ca, const v
                 const int32_t* order, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc = nullptr,
                 NormSink* sink = nullptr);
 
-// bf16 kernel with 256-row tiles and packed kappa (gather_bf16.hip).
+// bf16 pipeline kernel (gather_bf16.hip): any channel counts whose operands stay below 2 GB.
 bool gather_bf16_supported(int64_t n_src, int ca, int cb, int K);
-
-// Bp[s][k/8][n][k%8] (bf16) from Bt[s'][n][k] (transposed = false) or from W[s'][k][n]
-// (transposed = true), s' = s, or K-1-s when mirrored; for k < ca, n < cb; ca a multiple of 8.
-int pack_b_bf16(const void* W, int K, int ca, int cb, bool transposed, bool mirror, void* Bp, hipStream_t st);
-
-// out[order ? order[p] : p][:] = sum_s Bt[s] (cb x ca) . src[nbr[s][p]] with Bt given packed as above;
-// src holds n_src rows.  sink (optional): the tiles also leave the Norm statistics of out there.
-int gather_bf16(const void* src, int64_t n_src, int ca, const void* Bp, int cb, const int32_t* nbr,
-                const int32_t* order, int64_t n_pos, int K, void* out, hipStream_t st, NormSink* sink = nullptr);
+// Scratch of a call (padded rows, packed kappa, pieces of tiles).
+size_t gather_bf16_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K);
+// out[p][:] = sum_s B[s] (cb x ca) . src[nbr[s][p]] for p < n_pos; B[s][n][k] = W[s'][n][k], or
+// W[s'][k][n] when transposed, s' = s or K-1-s (mirror); src holds n_src rows.
+int gather_bf16(const void* src, int64_t n_src, int ca, const void* W, bool transposed, bool mirror, int cb,
+                const int32_t* nbr, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc);
 
 }  // namespace ssconv

@@ -21,7 +21,7 @@
 
 #include "conv.hpp"
 #include "gather_split.hpp"
-#include "lds_dma.hpp"
+#include "gather_tile.hpp"
 
 namespace ssconv {
 namespace {
@@ -29,20 +29,8 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kNT = 512;                     // 8 wavefronts, two per SIMD
-constexpr int kMaxK = 128;
-constexpr int kLdsLimit = 160 * 1024;
-constexpr int kMaxWG = 256;                  // one workgroup per compute unit
-constexpr uint32_t kAbsent = 0x80000000u;    // row offset past any operand: the DMA writes zeros
-constexpr int kBufferWord3 = 0x00020000;     // buffer descriptor word 3 for gfx9-family raw loads
-
 // Split rows: [row][ceil(ca / 32)][3 parts][32 channels] bf16, zero past ca; 192 bytes per 32 channels.
 __host__ __device__ __forceinline__ int chunks32(int ca) { return (ca + 31) / 32; }
-__host__ __device__ __forceinline__ int pad8(int c) { return (c + 7) & ~7; }
-// channels of a kappa row: whole 8-channel groups, and whole chunks where the last one is padded (a rest of 24)
-__host__ __device__ __forceinline__ int pad_k(int c) { return pad8(c) % 32 == 24 ? pad8(c) + 8 : pad8(c); }
-__host__ __device__ __forceinline__ int pad16(int c) { return (c + 15) & ~15; }
-
 __device__ __forceinline__ void split3(float x, uint16_t* p) {
   p[0] = f32_to_bf16_rne(x);
   const float r1 = x - bf16_to_f32(p[0]);
@@ -105,21 +93,6 @@ __global__ __launch_bounds__(256) void split_operands(const float* __restrict__ 
   store_parts(e, B3 + (sc * 3 * cbp + n) * 8, (int64_t)cbp * 8);
 }
 
-// Workgroup i -> slot such that each XCD (i % 8) runs a contiguous range of slots.
-__device__ __forceinline__ int xcd_slot(int i, int n) {
-  const int x = i & 7, j = i >> 3, q = n >> 3, r = n & 7;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-}
-
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16_buf(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t lds) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(lds);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(l), "v"(off), "s"(rsrc)
-               : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
 // One output by plain fp32 multiply-adds: what a value that the split cannot carry (infinite, NaN,
 // above bf16's largest, or so small that its third part would be lost) makes of an output is
 // computed again this way.
@@ -151,28 +124,20 @@ struct GS {
   static constexpr int S = MR == 4 ? 2 : 3;                  // LDS stages
   static constexpr int LA = (12 * MR + 7) / 8, LB = (3 * NB + 7) / 8, L = LA + LB;  // DMAs per wavefront per chunk
   static constexpr int NRB = MR == 4 ? 2 : 1;                // row blocks a wavefront fetches
-  static constexpr int MISC = 1024 + kMaxK * 5 + 16;         // junk block, offset flags, offset list, count
-  static constexpr int PANEL = (kLdsLimit - S * STAGE - MISC) / (BM * 4);  // offsets whose row table fits
+  static constexpr int PANEL = (kTileLds - S * STAGE - kTileMisc) / (BM * 4);  // offsets whose row table fits
   static constexpr size_t smem(int K) {
-    return (size_t)S * STAGE + MISC + (size_t)(K < PANEL ? K : PANEL) * BM * 4;
+    return (size_t)S * STAGE + kTileMisc + (size_t)(K < PANEL ? K : PANEL) * BM * 4;
   }
 };
 
-struct SplitPlan {
-  int G;           // workgroups
-  int mt, nt;      // row and column tiles
-  int64_t units;   // mt * nt * K: (tile, offset)
-};
-
-// Workgroup i takes the units [i * units / G, (i + 1) * units / G) of the (tile, offset) sequence, so
-// that every workgroup has the same number of offsets whatever the tile count.  A tile's first
+// A tile's first
 // piece (mostly the whole tile) is written to out; a workgroup that starts inside a tile leaves that piece
 // in part, slot i, and split_fixup adds the pieces in order.
 template <int NB, int MR>
-__global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __restrict__ A3, int64_t a_bytes, int ca,
+__global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16_t* __restrict__ A3, int64_t a_bytes, int ca,
                                                            const uint16_t* __restrict__ B3, int cb,
                                                            const int32_t* __restrict__ nbr, int64_t n_pos, int K,
-                                                           SplitPlan plan, float* __restrict__ part,
+                                                           TilePlan plan, float* __restrict__ part,
                                                            const float* __restrict__ src, SplitKernel B,
                                                            float* __restrict__ out) {
   using G = GS<NB, MR>;
@@ -180,9 +145,9 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* stages = smem;
   char* junk = smem + S * G::STAGE;
-  uint32_t* bmask = reinterpret_cast<uint32_t*>(junk + 1024);   // [kMaxK]
-  uint8_t* act = reinterpret_cast<uint8_t*>(bmask + kMaxK);     // [kMaxK]
-  int* n_act_p = reinterpret_cast<int*>(act + kMaxK);           // [4]
+  uint32_t* bmask = reinterpret_cast<uint32_t*>(junk + 1024);   // [kTileMaxK]
+  uint8_t* act = reinterpret_cast<uint8_t*>(bmask + kTileMaxK);     // [kTileMaxK]
+  int* n_act_p = reinterpret_cast<int*>(act + kTileMaxK);           // [4]
   uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);    // [PANEL][BM] byte offsets of gathered rows
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15;
@@ -194,14 +159,9 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
   const uint32_t row_bytes = (uint32_t)cc * 192u;
   const uint32_t stage0 = lds_addr(stages), junk_a = lds_addr(junk);
   const __amdgpu_buffer_rsrc_t a_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A3), (short)0, (int)a_bytes, kBufferWord3);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A3), (short)0, (int)a_bytes, kRawBufferWord3);
   const uint32_t bstep = 4u * 48u * (uint32_t)cbp;   // kappa: +4 channel groups per chunk
-  // A row's channels are read in whole 32-channel chunks (their 64-byte parts are aligned; straddling
-  // ones cost the texture path a second access per row) and a rest of 8 or 16, of which 4 or 2
-  // offsets share a chunk; 24 channels are padded to a chunk.
-  const int rest = cap % 32, full = cap / 32, quad = rest ? 32 / rest : 1;
-  const int g_slot = rest ? 8 * g / rest : 0, g_ch = rest ? 32 * full + 8 * g % rest : 0;
-
+  const ChunkOrder order(cap, g);
   uint32_t boff[G::LB];  // kappa block e = w + 8 j: part e % 3 of column block e / 3
 #pragma unroll
   for (int j = 0; j < G::LB; ++j) boff[j] = (uint32_t)((w + 8 * j) % 3 * cbp + (w + 8 * j) / 3 * 16) * 16u;
@@ -209,7 +169,7 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
   for (int64_t u = u_beg; u < u_end;) {
     const int64_t t = u / K;
     const int sa = (int)(u - t * K), sb = (int)(u_end - t * K < K ? u_end - t * K : K);
-    const int64_t p0 = (t / plan.nt) * BM;
+    const int64_t p0 = plan.row0 + (t / plan.nt) * BM;
     const int n0 = (int)(t % plan.nt) * G::BN;
 
     f4 acc[MR][G::WN0];
@@ -222,50 +182,11 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
     const int npan = (sb - sa + G::PANEL - 1) / G::PANEL;
     for (int pn = 0; pn < npan; ++pn) {
       const int s0 = sa + (sb - sa) * pn / npan, s1 = sa + (sb - sa) * (pn + 1) / npan, ns = s1 - s0;
-      // 1. rows of the tile at every offset of the panel (byte offsets, kAbsent: no neighbour) and the
-      //    offsets that occur at all, in order
-      __syncthreads();  // the previous panel (or tile) is done with the table and the stages
-      for (int s = tid; s < ns; s += kNT) bmask[s] = 0u;
-      __syncthreads();
-      {
-        constexpr int STEP = kNT / BM;  // offsets read side by side
-        int et = tid;
-        asm volatile("" : "+v"(et));
-        const int r = et % BM;
-        const int64_t p = p0 + r;
-        const bool in = p < n_pos;
-        for (int j0 = et / BM; j0 < ns; j0 += 8 * STEP) {
-          int v[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            v[j] = in && j0 + STEP * j < ns ? nbr[(int64_t)(s0 + j0 + STEP * j) * n_pos + p] : -1;
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            if (j0 + STEP * j < ns) {
-              rows[(j0 + STEP * j) * BM + r] = v[j] >= 0 ? (uint32_t)v[j] * row_bytes : kAbsent;
-              if (v[j] >= 0) bmask[j0 + STEP * j] = 1u;
-            }
-        }
-      }
-      __syncthreads();
-      if (w == 0) {
-        int base = 0;
-        for (int j0 = 0; j0 < ns; j0 += 64) {
-          const int j = j0 + lane;
-          const bool a = j < ns && bmask[j] != 0;
-          const uint64_t b = __ballot(a);
-          if (a) act[base + __popcll(b & ((1ull << lane) - 1ull))] = (uint8_t)j;
-          base += __popcll(b);
-        }
-        if (lane == 0) n_act_p[0] = base;
-      }
-      __syncthreads();
-      const int n_act = __builtin_amdgcn_readfirstlane(n_act_p[0]);
-      const int nchunk = n_act * full + (rest ? (n_act + quad - 1) / quad : 0);
+      const int n_act = load_panel<BM>(nbr, n_pos, p0, s0, ns, row_bytes, rows, bmask, act, n_act_p);
+      const int nchunk = order.chunks(n_act);
 
-      // 2. the chunk being fetched: full ones of slot r_slot at channel 32 r_f + 8 g, then the rests of
-      //    the `quad` slots from r_base on, lane group g taking its share
-      int r_base = 0, r_slot = 0, r_f = 0;
+      // the chunk being fetched: this wavefront's rows, this lane group's channels, kappa position
+      ChunkWalk walk;
       uint32_t arow[NRB], bbase, achan;
       auto refresh = [&](int slot, int ch) {
         const bool live = slot < n_act;
@@ -273,16 +194,8 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
         achan = (uint32_t)(ch >> 5) * 192u + (ch & 31) * 2u;
 #pragma unroll
         for (int q = 0; q < NRB; ++q)
-          arow[q] = live ? rows[j * BM + 16 * ((w + 8 * q) % (4 * MR)) + r16] : kAbsent;
+          arow[q] = live ? rows[j * BM + 16 * ((w + 8 * q) % (4 * MR)) + r16] : kAbsentRow32;
         bbase = live ? ((uint32_t)((s0 + j) * cg + (ch >> 3)) * 3u * (uint32_t)cbp + (uint32_t)(n0 + r16)) * 16u : 0u;
-      };
-      auto seek = [&]() {  // to the chunk at (r_base, r_slot, r_f = 0)
-        const int end = r_base + quad < n_act ? r_base + quad : n_act;
-        if (full == 0) r_slot = end;
-        if (r_slot < end)
-          refresh(r_slot, 8 * g);
-        else if (rest)
-          refresh(r_base + g_slot, g_ch);
       };
       // DMA q of this wavefront for the chunk going into stage k: q < LA a row block's part, else a
       // part of a kappa block
@@ -291,39 +204,25 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
           // row block w + 8 (q % 2) part q / 2 of 16 blocks; block w part q of 8; block w % 4 part w / 4 + 2 q of 4
           const uint32_t row = arow[MR == 4 ? q & 1 : 0] + achan;
           if constexpr (MR == 4)
-            dma16_buf(a_rsrc, row + (q >> 1) * 64u, sbase + w * 3072 + (q & 1) * 24576 + (q >> 1) * 1024);
+            dma16_tile(a_rsrc, row + (q >> 1) * 64u, sbase + w * 3072 + (q & 1) * 24576 + (q >> 1) * 1024);
           else if constexpr (MR == 2)
-            dma16_buf(a_rsrc, row + q * 64u, sbase + w * 3072 + q * 1024);
+            dma16_tile(a_rsrc, row + q * 64u, sbase + w * 3072 + q * 1024);
           else if (q == 0 || w < 4)
-            dma16_buf(a_rsrc, row + (wn + 2 * q) * 64u, sbase + wm * 3072 + (wn + 2 * q) * 1024);
+            dma16_tile(a_rsrc, row + (wn + 2 * q) * 64u, sbase + wm * 3072 + (wn + 2 * q) * 1024);
           else
-            dma16_buf(a_rsrc, kAbsent, junk_a);
+            dma16_tile(a_rsrc, kAbsentRow32, junk_a);
         } else {
           const int j = q - G::LA;
           if (8 * j + 8 <= 3 * NB || w < 3 * NB - 8 * j)
             dma16_off(B3, bbase + boff[j], sbase + G::ABYTES + (w + 8 * j) * 1024);
           else if (S > 2)
-            dma16_buf(a_rsrc, kAbsent, junk_a);
+            dma16_tile(a_rsrc, kAbsentRow32, junk_a);
         }
       };
       auto advance = [&]() {
-        const int end = r_base + quad < n_act ? r_base + quad : n_act;
-        if (r_slot < end) {
-          if (++r_f < full) {
-            achan += 192u;
-            bbase += bstep;
-            return;
-          }
-          r_f = 0;
-          ++r_slot;
-          if (r_slot == end && !rest) r_base = end;
-        } else {  // after the rests
-          r_base = r_slot = end;
-          r_f = 0;
-        }
-        seek();
+        walk.advance(order, n_act, g, [&]() { achan += 192u, bbase += bstep; }, refresh);
       };
-      seek();
+      walk.seek(order, n_act, g, refresh);
       wait_vm<0>();  // the waits below count this panel's DMAs alone
       for (int c = 0; c < S - 1 && c < nchunk; ++c) {
 #pragma unroll
@@ -331,7 +230,7 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
         advance();
       }
 
-      // 3. iteration c: this wavefront's DMAs of chunk c have landed, one barrier publishes them (and
+      // iteration c: this wavefront's DMAs of chunk c have landed, one barrier publishes them (and
       //    retires the reads of the stage refilled next); the fragments are read one step ahead of the
       //    MFMAs that use them, the DMAs of chunk c + S - 1 go out between the first steps
 #define SSG_RDA(d_, mb_)                                                                            \
@@ -416,7 +315,7 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
 #undef SSG_RDB
     }
 
-    // 4. the tile, or this workgroup's share of it
+    // the tile, or this workgroup's share of it
     const bool whole = sa == 0 && sb == K;
     // (the lane index again, opaque: its address arithmetic would otherwise be hoisted out of the tile
     // loop and hold some 60 registers through the chunk loop)
@@ -468,21 +367,15 @@ __global__ __launch_bounds__(kNT) void gather_split_kernel(const uint16_t* __res
 
 // Adds the pieces of the tiles that more than one workgroup held, in workgroup order.  A block takes
 // 1024 consecutive values of one tile.
-__global__ __launch_bounds__(256) void split_fixup(const float* __restrict__ part, SplitPlan plan, int K, int BM,
+__global__ __launch_bounds__(256) void split_fixup(const float* __restrict__ part, TilePlan plan, int K, int BM,
                                                    int BN, int cb, const int32_t* __restrict__ nbr, int64_t n_pos,
                                                    const float* __restrict__ src, int ca, SplitKernel B,
                                                    float* __restrict__ out) {
-  const int64_t t = blockIdx.x, ua = t * K, ub = ua + K - 1;
-  auto owner = [&](int64_t u) {
-    int64_t i = u * plan.G / plan.units;
-    while ((i + 1) * plan.units / plan.G <= u) ++i;
-    while (i * plan.units / plan.G > u) --i;
-    return i;
-  };
-  const int64_t i0 = owner(ua), i1 = owner(ub);
+  const int64_t t = blockIdx.x;
+  const int64_t i0 = unit_owner(plan, t * K), i1 = unit_owner(plan, t * K + K - 1);
   if (i0 == i1) return;
   const int e = (blockIdx.y * 256 + threadIdx.x) * 4, r = e / BN, c = e - r * BN;
-  const int64_t p = (t / plan.nt) * BM + r;
+  const int64_t p = plan.row0 + (t / plan.nt) * BM + r;
   const int col = (int)(t % plan.nt) * BN + c;
   if (r >= BM || p >= n_pos || col >= cb) return;
   float* o = out + p * cb + col;
@@ -507,14 +400,12 @@ __global__ __launch_bounds__(256) void split_fixup(const float* __restrict__ par
 
 struct SplitShape {
   int nb, mr;
-  SplitPlan plan;
+  TilePlan plan;
 };
 
-size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 size_t a3_bytes(int64_t n_src, int ca) { return align256((size_t)n_src * chunks32(ca) * 192); }
 // (the column blocks of the last tile past cb16 read on past the end: up to 2 KB)
 size_t b3_bytes(int ca, int cb, int K) { return align256((size_t)K * pad_k(ca) * pad16(cb) * 6 + 2048); }
-bool whole_tiles(const SplitPlan& p, int K) { return p.units % ((int64_t)p.G * K) == 0; }
 size_t part_bytes(const SplitShape& s, int K) {
   return whole_tiles(s.plan, K) ? 0 : (size_t)s.plan.G * 64 * s.mr * 16 * s.nb * 4;
 }
@@ -534,6 +425,7 @@ SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   SplitShape best, s;
   s.nb = per <= 2 ? 2 : per <= 4 ? 4 : per;
   s.plan.nt = (int)cdiv(cb, 16 * s.nb);
+  s.plan.row0 = 0;
   const double chunks = pad_k(ca) / 32.0 * K;
   double best_cost = 0.0;
   bool best_fits = false;
@@ -545,11 +437,11 @@ SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
     const bool cut = i & 1;
     double cost = chunks * (0.3 + 0.0625 * s.mr * s.nb);
     if (cut) {
-      s.plan.G = (int)std::min<int64_t>(kMaxWG, s.plan.units);
+      s.plan.G = (int)std::min<int64_t>(kTileWG, s.plan.units);
       cost = cost * nt / s.plan.G + 8.0 + (double)part_bytes(s, K) / 4e6;
     } else {
       s.plan.G = (int)std::min<int64_t>(nt, INT32_MAX);
-      cost *= cdiv(nt, kMaxWG);
+      cost *= cdiv(nt, kTileWG);
     }
     const bool fits = shape_bytes(s, n_src, ca, cb, K) <= SSCONV_NOALLOC_SCRATCH_BYTES;
     if (i == 0 || (fits && !best_fits) || (fits == best_fits && cost < best_cost))
@@ -565,7 +457,7 @@ int launch(const SplitShape& s, const uint16_t* A3, int64_t a_bytes, int ca, con
   auto kern = gather_split_kernel<NB, MR>;
   const size_t smem = GS<NB, MR>::smem(K);
   SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  kern<<<s.plan.G, kNT, smem, st>>>(A3, a_bytes, ca, B3, cb, nbr, n_pos, K, s.plan, part, src, B, out);
+  kern<<<s.plan.G, kTileThreads, smem, st>>>(A3, a_bytes, ca, B3, cb, nbr, n_pos, K, s.plan, part, src, B, out);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
 }
@@ -573,7 +465,7 @@ int launch(const SplitShape& s, const uint16_t* A3, int64_t a_bytes, int ca, con
 }  // namespace
 
 bool gather_split_supported(int64_t n_src, int ca, int cb, int K) {
-  return ca >= 1 && cb >= 1 && K >= 1 && K <= kMaxK && n_src >= 1 && a3_bytes(n_src, ca) < ((size_t)1 << 31) &&
+  return ca >= 1 && cb >= 1 && K >= 1 && K <= kTileMaxK && n_src >= 1 && a3_bytes(n_src, ca) < ((size_t)1 << 31) &&
          b3_bytes(ca, cb, K) < ((size_t)1 << 31);
 }
 
