@@ -48,41 +48,42 @@ struct GB {
   static constexpr int LA = (4 * MR + 7) / 8, LB = (NB + 7) / 8, L = LA + LB;  // DMAs per wavefront per chunk
   static constexpr int NRB = MR == 4 ? 2 : 1;               // row blocks a wavefront fetches
   static constexpr int PITCH = WN0 * 32 + 16;               // bytes per staged output row in the epilogue
-  static constexpr int FIT = (kTileLds - kD * STAGE - kTileMisc) / (BM * 4);
-  static constexpr int PANEL = FIT < kTileMaxK ? FIT : kTileMaxK;  // offsets whose row table fits
-  static constexpr size_t smem(int K) {
-    return (size_t)kD * STAGE + kTileMisc + (size_t)(K < PANEL ? K : PANEL) * BM * 4;
-  }
+  static constexpr int ROOM = kTileLds - kD * STAGE - kTileMisc;  // for the tables of a panel of offsets
 };
 
-// Pieces of tiles that more than one workgroup holds go to part (fp32, slot 2 i: the first tile of
-// workgroup i, 2 i + 1: its last) and are added in order by bf16_fixup; whole tiles go to out.
-template <int NB, int MR>
-__global__ __launch_bounds__(kTileThreads) void gather_bf16_kernel(const uint16_t* __restrict__ src, int64_t src_bytes,
-                                                                   int row_bytes, int ca,
-                                                                   const uint16_t* __restrict__ Bp, int cb,
-                                                                   const int32_t* __restrict__ nbr, int64_t n_pos, int K,
-                                                                   TilePlan plan, float* __restrict__ part,
-                                                                   uint16_t* __restrict__ out) {
+// The wavefronts of column group wn (WNX blocks from block noff of the tile on).  Each group has its own
+// copy of the tile loop: merged behind the chunk loop, the groups' accumulators cost 20 copies a chunk or
+// spills.  The barriers are the same in both.
+template <int NB, int MR, int WNX>
+__device__ __forceinline__ void gather_bf16_body(const uint16_t* __restrict__ src, int64_t src_bytes,
+                                                 int row_bytes, int ca, const uint16_t* __restrict__ Bp, int cb,
+                                                 const int32_t* __restrict__ nbr, int64_t n_pos, int K, const TilePlan& plan,
+                                                 float* __restrict__ part, uint16_t* __restrict__ out, int noff) {
   using G = GB<NB, MR>;
-  constexpr int BM = G::BM, WN0 = G::WN0, WN1 = G::WN1, L = G::L, LA = G::LA, NRB = G::NRB;
+  constexpr int BM = G::BM, L = G::L, LA = G::LA, NRB = G::NRB;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* stages = smem;                                           // kD * STAGE bytes
   char* junk = smem + kD * G::STAGE;                             // 1 KB sink
   uint32_t* bmask = reinterpret_cast<uint32_t*>(junk + 1024);    // [kTileMaxK]
   uint8_t* act = reinterpret_cast<uint8_t*>(bmask + kTileMaxK);  // [kTileMaxK]
   int* n_act_p = reinterpret_cast<int*>(act + kTileMaxK);        // [4]
-  uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);     // [PANEL][BM] byte offsets of gathered rows
+  uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);     // [panel + 1][BM] byte offsets of gathered rows
+  uint2* const tab = reinterpret_cast<uint2*>(rows + (plan.panel + 1) * BM);  // chunk table
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, scalar
-  const int wm = w & 3, wn = w >> 2;  // row group and column group; SIMD w % 4 hosts (wm, 0), (wm, 1)
+  const int wm = w & 3;  // row group
   const int wg = xcd_slot(blockIdx.x, plan.G);
   const int64_t u_beg = wg * plan.units / plan.G, u_end = (wg + 1) * plan.units / plan.G;
   const int cap = pad_k(ca), cg = cap / 8, cbp = pad16(cb);
   const uint32_t stage0 = lds_addr(stages), junk_a = lds_addr(junk);
-  const uint32_t bstep = 64u * (uint32_t)cbp;  // packed kappa: +4 channel groups per chunk
-  const ChunkOrder order(cap, g);
+  const ChunkOrder order(cap);
+  // DMA duty per chunk: row blocks w, w + 8 and kappa blocks w, w + 8; a wavefront without one fetches an
+  // absent row into the junk block, so that all have the same number in flight
+  const uint32_t* const my_rows = rows + 16 * (MR == 1 ? wm : w) + r16;
+  uint32_t bmask_w[G::LB];
+#pragma unroll
+  for (int j = 0; j < G::LB; ++j) bmask_w[j] = w + 8 * j < NB ? ~0u : 0u;
 
   // Gathered rows are fetched with buffer DMA (32-bit offsets; an offset past the end of src
   // writes zeros, which covers absent neighbours).
@@ -95,130 +96,103 @@ __global__ __launch_bounds__(kTileThreads) void gather_bf16_kernel(const uint16_
     const int64_t p0 = plan.row0 + (t / plan.nt) * BM;
     const int n0 = (int)(t % plan.nt) * G::BN;
 
-    f4 acc[MR][WN0];
+    f4 acc[MR][WNX];
 #pragma unroll
     for (int mb = 0; mb < MR; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < WN0; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int nb = 0; nb < WNX; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
 
-    const int npan = (sb - sa + G::PANEL - 1) / G::PANEL;  // panels of near-equal numbers of offsets
+    const int npan = (sb - sa + plan.panel - 1) / plan.panel;  // panels of near-equal numbers of offsets
     for (int pn = 0; pn < npan; ++pn) {
       const int s0 = sa + (sb - sa) * pn / npan, ns = sa + (sb - sa) * (pn + 1) / npan - s0;
       const int n_act = load_panel<BM>(nbr, n_pos, p0, s0, ns, (uint32_t)row_bytes, rows, bmask, act, n_act_p);
       const int nchunk = order.chunks(n_act);
+      if (nchunk == 0) continue;
+      chunk_table(order, n_act, nchunk, act, ns, BM * 4, s0, cg, (uint32_t)cbp * 16u, tab);
 
-      // the chunk being fetched: this wavefront's rows and kappa position (byte offsets)
-      ChunkWalk walk;
-      uint32_t arow[NRB], bbase;
-      auto refresh = [&](int slot, int ch) {
-        const bool live = slot < n_act;
-        const int j = live ? act[slot] : 0;
+      // position of the chunk being fetched (rows, kappa) and the table entry of the one after it
+      uint32_t arow[NRB], bpos;
+      uint2 ent = tab[g];
+      const uint2* next = tab + g;
+      const uint32_t col = (uint32_t)(n0 + r16) * 16u;
+      auto advance = [&]() {
 #pragma unroll
         for (int q = 0; q < NRB; ++q)
-          arow[q] = live ? rows[j * BM + 16 * (MR == 1 ? wm : w + 8 * q) + r16] + 2u * ch : kAbsentRow32;
-        bbase = live ? ((uint32_t)((s0 + j) * cg + (ch >> 3)) * (uint32_t)cbp + (uint32_t)(n0 + r16)) * 16u : 0u;
+          arow[q] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(my_rows + 128 * q) + (ent.x & 0x3ffffu)) +
+                    (ent.x >> 18) * 16u;
+        bpos = ent.y + col;
+        next += 4;
+        ent = *next;
       };
-      // DMA q of this wavefront for the chunk going into the stage at LDS address sbase: q < LA row
-      // block w + 8 q, else kappa block w + 8 (q - LA)
+      // DMA q of this wavefront for the chunk going into the stage at LDS address sbase
       auto dma = [&](int q, uint32_t sbase) {
         if (q < LA) {
-          if (MR > 1 || w < 4)
-            dma16_tile(src_rsrc, arow[NRB == 2 ? q & 1 : 0], sbase + (w + 8 * q) * 1024);
-          else
-            dma16_tile(src_rsrc, kAbsentRow32, junk_a);
+          dma16_tile(src_rsrc, MR == 1 && w >= 4 ? kAbsentRow32 : arow[NRB == 2 ? q & 1 : 0],
+                     MR == 1 && w >= 4 ? junk_a : sbase + (w + 8 * q) * 1024);
         } else {
-          const int nb = w + 8 * (q - LA);
-          if (nb < NB)
-            dma16_off(Bp, bbase + (uint32_t)nb * 256u, sbase + G::ABYTES + nb * 1024);
-          else
-            dma16_tile(src_rsrc, kAbsentRow32, junk_a);
+          const int j = q - LA;
+          dma16_off(Bp, (bpos + (uint32_t)(w + 8 * j) * 256u) & bmask_w[j],
+                    w + 8 * j < NB ? sbase + G::ABYTES + (w + 8 * j) * 1024 : junk_a);
         }
       };
-      auto advance = [&]() {
-        walk.advance(order, n_act, g,
-                     [&]() {
-#pragma unroll
-                       for (int q = 0; q < NRB; ++q) arow[q] += 64u;
-                       bbase += bstep;
-                     },
-                     refresh);
-      };
-      walk.seek(order, n_act, g, refresh);
+      advance();
       wait_vm<0>();  // the waits below count this panel's DMAs alone
 #pragma unroll
-      for (int c = 0; c < kD - 1; ++c)
-        if (c < nchunk) {
+      for (int c = 0; c < kD - 1; ++c) {
 #pragma unroll
-          for (int q = 0; q < L; ++q) dma(q, stage0 + c * G::STAGE);
-          advance();
-        }
+        for (int q = 0; q < L; ++q) dma(q, stage0 + c * G::STAGE);
+        advance();
+      }
 
-#define SSB_FRAG(da_, db_, u_, sb_, NOFF)                                                           \
+#define SSB_FRAG(da_, db_, u_, sb_)                                                                 \
   do {                                                                                              \
     if ((u_) < MR)                                                                                  \
       da_[(u_) % MR] = *reinterpret_cast<const uint4*>((sb_) + (MR * wm + (u_)) * 1024 + 16 * lane); \
-    else if ((u_) - MR < WN1 || wn == 0)                                                            \
-      db_[(u_) - MR] = *reinterpret_cast<const uint4*>((sb_) + G::ABYTES + ((NOFF) + (u_) - MR) * 1024 + 16 * lane); \
+    else                                                                                            \
+      db_[(u_) - MR] = *reinterpret_cast<const uint4*>((sb_) + G::ABYTES + (noff + (u_) - MR) * 1024 + 16 * lane); \
   } while (0)
 
   // Iteration c (stage k = c % kD): wait for this wavefront's DMA of chunk c+1, publish it with a
-  // barrier (which also retires every LDS read of the stage refilled next: it was read two
-  // chunks ago), then the MFMAs of chunk c with the fragment reads of chunk c+1 and the DMAs of
+  // barrier (which also retires every LDS read of the stage refilled next: it was consumed by the
+  // MFMAs two chunks ago), then the MFMAs of chunk c with the fragment reads of chunk c+1 and the DMAs of
   // chunk c+kD-1 spread between the column blocks, so that the texture path drains while the matrix
-  // cores run.
-#define SSB_BODY(k_, AC, BC, AN, BN_, WNX, NOFF)                                                    \
+  // cores run.  Past the last chunk the fetches are of absent rows: no conditions in the loop.
+#define SSB_BODY(k_, AC, BC, AN, BN_)                                                               \
   {                                                                                                 \
-    const int cc_ = c + (k_);                                                                       \
-    if (cc_ >= nchunk) break;                                                                       \
-    if (cc_ + kD - 2 < nchunk)                                                                      \
-      wait_vm<(kD - 3) * L>();                                                                      \
-    else                                                                                            \
-      wait_vm<0>();                                                                                 \
-    __syncthreads();                                                                                \
-    const bool rd_ = cc_ + 1 < nchunk;                                                              \
-    const bool iss_ = cc_ + kD - 1 < nchunk;                                                        \
+    if (c + (k_) >= nchunk) break;                                                                  \
+    wait_vm<(kD - 3) * L>();                                                                        \
+    asm volatile("s_barrier" ::: "memory");                                                         \
     const uint32_t si_ = stage0 + ((k_) + kD - 1) % kD * G::STAGE;                                  \
     const char* sbr_ = stages + (((k_) + 1) % kD) * G::STAGE;                                       \
     constexpr int NR = MR + WNX, RPB = (NR + WNX - 1) / WNX, DPB = (L + WNX - 1) / WNX;             \
     __builtin_amdgcn_sched_barrier(0);                                                              \
     _Pragma("unroll") for (int nb = 0; nb < WNX; ++nb) {                                            \
-      if (nb < WN1 || wn == 0) /* the wider group's last block: a scalar branch */                  \
-        _Pragma("unroll") for (int mb = 0; mb < MR; ++mb)                                           \
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, AC[mb]), \
-                                                                __builtin_bit_cast(bf16x8, BC[nb]), acc[mb][nb], 0, 0, 0); \
+      _Pragma("unroll") for (int mb = 0; mb < MR; ++mb)                                             \
+        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, AC[mb]),   \
+                                                              __builtin_bit_cast(bf16x8, BC[nb]), acc[mb][nb], 0, 0, 0); \
       __builtin_amdgcn_sched_barrier(0);                                                            \
-      if (rd_) {                                                                                    \
-        _Pragma("unroll") for (int u = RPB * nb; u < (RPB * nb + RPB < NR ? RPB * nb + RPB : NR); ++u) \
-          SSB_FRAG(AN, BN_, u, sbr_, NOFF);                                                         \
-      }                                                                                             \
-      if (iss_) {                                                                                   \
-        _Pragma("unroll") for (int q = DPB * nb; q < (DPB * nb + DPB < L ? DPB * nb + DPB : L); ++q) \
-          dma(q, si_);                                                                              \
-      }                                                                                             \
+      _Pragma("unroll") for (int u = RPB * nb; u < (RPB * nb + RPB < NR ? RPB * nb + RPB : NR); ++u) \
+        SSB_FRAG(AN, BN_, u, sbr_);                                                                 \
+      _Pragma("unroll") for (int q = DPB * nb; q < (DPB * nb + DPB < L ? DPB * nb + DPB : L); ++q)  \
+        dma(q, si_);                                                                                \
+      if (nb == (L + DPB - 1) / DPB - 1) advance();                                                 \
       __builtin_amdgcn_sched_barrier(0);                                                            \
     }                                                                                               \
-    if (iss_) advance();                                                                            \
   }
 
-  // Four chunks per trip; the first body past the last chunk leaves the loop.
-#define SSB_LOOP(WNX, NOFF)                                                                         \
-  {                                                                                                 \
-    uint4 fa0[MR], fb0[WNX], fa1[MR], fb1[WNX];                                                     \
-    if (nchunk > 0) {                                                                               \
-      if (nchunk > 2) wait_vm<2 * L>(); else wait_vm<0>();                                          \
-      __syncthreads();                                                                              \
-      _Pragma("unroll") for (int u = 0; u < MR + WNX; ++u) SSB_FRAG(fa0, fb0, u, stages, NOFF);     \
-    }                                                                                               \
-    for (int c = 0;; c += kD) {                                                                     \
-      SSB_BODY(0, fa0, fb0, fa1, fb1, WNX, NOFF)                                                    \
-      SSB_BODY(1, fa1, fb1, fa0, fb0, WNX, NOFF)                                                    \
-      SSB_BODY(2, fa0, fb0, fa1, fb1, WNX, NOFF)                                                    \
-      SSB_BODY(3, fa1, fb1, fa0, fb0, WNX, NOFF)                                                    \
-    }                                                                                               \
-  }
       static_assert(kD == 4, "the unrolled chunk loop is written for four stages");
-      SSB_LOOP(WN0, wn * WN0)
-#undef SSB_LOOP
+      uint4 fa0[MR], fb0[WNX], fa1[MR], fb1[WNX];
+      wait_vm<2 * L>();
+      asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+      for (int u = 0; u < MR + WNX; ++u) SSB_FRAG(fa0, fb0, u, stages);
+      for (int c = 0;; c += kD) {  // four chunks per trip; the first body past the last chunk leaves the loop
+        SSB_BODY(0, fa0, fb0, fa1, fb1)
+        SSB_BODY(1, fa1, fb1, fa0, fb0)
+        SSB_BODY(2, fa0, fb0, fa1, fb1)
+        SSB_BODY(3, fa1, fb1, fa0, fb0)
+      }
+      wait_vm<0>();  // the fetches past the end land before the stages are used again
 #undef SSB_BODY
 #undef SSB_FRAG
     }
@@ -226,8 +200,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_bf16_kernel(const uint16_
     int el = lane;
     asm volatile("" : "+v"(el));  // opaque: the address arithmetic below must not live through the chunk loop
     const int eg = el >> 4, er = el & 15;
-    const int nbc = wn == 0 ? WN0 : WN1;
-    const int c0 = 16 * WN0 * wn;
+    const int c0 = 16 * noff;
     if (sa == 0 && sb == K) {
       // Whole tile: each wavefront stages its rows, up to 32 at a time, as bf16 in LDS (row pitch padded
       // so the 2-byte writes of the four row groups fall in distinct banks) and writes them back as
@@ -244,14 +217,13 @@ __global__ __launch_bounds__(kTileThreads) void gather_bf16_kernel(const uint16_
 #pragma unroll
           for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int nb = 0; nb < WN0; ++nb)
-              if (nb < nbc)
-                *reinterpret_cast<uint16_t*>(ep + (16 * m2 + 4 * eg + i) * G::PITCH + (16 * nb + er) * 2) =
-                    f32_to_bf16_rne(acc[RP * part_ + m2][nb][i]);
+            for (int nb = 0; nb < WNX; ++nb)
+              *reinterpret_cast<uint16_t*>(ep + (16 * m2 + 4 * eg + i) * G::PITCH + (16 * nb + er) * 2) =
+                  f32_to_bf16_rne(acc[RP * part_ + m2][nb][i]);
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int pieces = 2 * nbc;  // 16-byte pieces per staged row
+        constexpr int pieces = 2 * WNX;  // 16-byte pieces per staged row
         for (int e = el; e < 16 * RP * pieces; e += 64) {
           const int r = e / pieces, q = e - r * pieces;
           const int64_t p = p0 + 16 * MR * wm + 16 * RP * part_ + r;
@@ -277,12 +249,28 @@ __global__ __launch_bounds__(kTileThreads) void gather_bf16_kernel(const uint16_
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int nb = 0; nb < WN0; ++nb)
-            if (nb < nbc)
-              dst[(16 * (wm * MR + mb) + 4 * eg + i) * G::BN + c0 + 16 * nb + er] = acc[mb][nb][i];
+          for (int nb = 0; nb < WNX; ++nb)
+            dst[(16 * (wm * MR + mb) + 4 * eg + i) * G::BN + c0 + 16 * nb + er] = acc[mb][nb][i];
     }
     u = t * K + sb;
   }
+}
+
+// Pieces of tiles that more than one workgroup holds go to part (fp32, slot 2 i: the first tile of
+// workgroup i, 2 i + 1: its last) and are added in order by bf16_fixup; whole tiles go to out.
+template <int NB, int MR>
+__global__ __launch_bounds__(kTileThreads) void gather_bf16_kernel(const uint16_t* __restrict__ src, int64_t src_bytes,
+                                                                   int row_bytes, int ca,
+                                                                   const uint16_t* __restrict__ Bp, int cb,
+                                                                   const int32_t* __restrict__ nbr, int64_t n_pos, int K,
+                                                                   TilePlan plan, float* __restrict__ part,
+                                                                   uint16_t* __restrict__ out) {
+  using G = GB<NB, MR>;
+  const int wn = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);  // SIMD w % 4 hosts both column groups
+  if (wn == 0)
+    gather_bf16_body<NB, MR, G::WN0>(src, src_bytes, row_bytes, ca, Bp, cb, nbr, n_pos, K, plan, part, out, 0);
+  else
+    gather_bf16_body<NB, MR, G::WN1>(src, src_bytes, row_bytes, ca, Bp, cb, nbr, n_pos, K, plan, part, out, G::WN0);
 }
 
 // Adds the pieces of the tiles that more than one workgroup held, in workgroup order.  A block takes
@@ -417,15 +405,17 @@ Bf16Shape bf16_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   if (mt == 0 || mt * 256 >= n_pos) return s;
   two.n = 2;
   two.mr[0] = 4;
-  two.plan[0] = {(int)(mt * nt), (int)mt, nt, 0, mt * nt * K};
+  two.plan[0] = {(int)(mt * nt), (int)mt, nt, 0, 0, mt * nt * K};
   two.plan[1] = best_plan(mt * 256, n_pos, nt, s.nb, K, chunks, room, &two.mr[1], &tail);
   return rounds * chunks * chunk_us(4, s.nb) + tail + 6.0 < cost ? two : s;
 }
 
 template <int NB, int MR>
-int launch_bf16(const TilePlan& plan, const void* src, int64_t src_bytes, int row_bytes, int ca, const void* Bp, int cb,
+int launch_bf16(TilePlan plan, const void* src, int64_t src_bytes, int row_bytes, int ca, const void* Bp, int cb,
                 const int32_t* nbr, int64_t n_pos, int K, float* part, void* out, hipStream_t st) {
-  const size_t smem = GB<NB, MR>::smem(K);
+  using G = GB<NB, MR>;
+  plan.panel = panel_offsets(G::ROOM, G::BM, pad_k(ca), K);
+  const size_t smem = (size_t)(kTileLds - G::ROOM) + panel_bytes(plan.panel, G::BM, pad_k(ca));
   auto kern = gather_bf16_kernel<NB, MR>;
   SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   kern<<<plan.G, kTileThreads, smem, st>>>((const uint16_t*)src, src_bytes, row_bytes, ca, (const uint16_t*)Bp, cb, nbr,
@@ -443,7 +433,8 @@ int launch_bf16(const TilePlan& plan, const void* src, int64_t src_bytes, int ro
 
 bool gather_bf16_supported(int64_t n_src, int ca, int cb, int K) {
   // 32-bit byte offsets: every gathered row and every packed kappa entry below 2^31
-  return ca >= 1 && cb >= 1 && K >= 1 && K <= kTileMaxK && n_src >= 0 &&
+  // and a panel of at least two offsets
+  return ca >= 1 && ca <= 8192 && cb >= 1 && K >= 1 && K <= kTileMaxK && n_src >= 0 &&
          n_src * (ca % 8 == 0 ? ca : pad32(ca)) * 2 < ((int64_t)1 << 31) && bp_bytes(ca, cb, K) < ((size_t)1 << 31);
 }
 

@@ -124,10 +124,7 @@ struct GS {
   static constexpr int S = MR == 4 ? 2 : 3;                  // LDS stages
   static constexpr int LA = (12 * MR + 7) / 8, LB = (3 * NB + 7) / 8, L = LA + LB;  // DMAs per wavefront per chunk
   static constexpr int NRB = MR == 4 ? 2 : 1;                // row blocks a wavefront fetches
-  static constexpr int PANEL = (kTileLds - S * STAGE - kTileMisc) / (BM * 4);  // offsets whose row table fits
-  static constexpr size_t smem(int K) {
-    return (size_t)S * STAGE + kTileMisc + (size_t)(K < PANEL ? K : PANEL) * BM * 4;
-  }
+  static constexpr int ROOM = kTileLds - S * STAGE - kTileMisc;  // for the tables of a panel of offsets
 };
 
 // A tile's first
@@ -148,7 +145,8 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
   uint32_t* bmask = reinterpret_cast<uint32_t*>(junk + 1024);   // [kTileMaxK]
   uint8_t* act = reinterpret_cast<uint8_t*>(bmask + kTileMaxK);     // [kTileMaxK]
   int* n_act_p = reinterpret_cast<int*>(act + kTileMaxK);           // [4]
-  uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);    // [PANEL][BM] byte offsets of gathered rows
+  uint32_t* rows = reinterpret_cast<uint32_t*>(n_act_p + 4);    // [panel + 1][BM] byte offsets of gathered rows
+  uint2* const tab = reinterpret_cast<uint2*>(rows + (plan.panel + 1) * BM);  // chunk table
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -160,8 +158,8 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
   const uint32_t stage0 = lds_addr(stages), junk_a = lds_addr(junk);
   const __amdgpu_buffer_rsrc_t a_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A3), (short)0, (int)a_bytes, kRawBufferWord3);
-  const uint32_t bstep = 4u * 48u * (uint32_t)cbp;   // kappa: +4 channel groups per chunk
-  const ChunkOrder order(cap, g);
+  const ChunkOrder order(cap);
+  const uint32_t* const my_rows = rows + 16 * (MR == 1 ? wm : w) + r16;
   uint32_t boff[G::LB];  // kappa block e = w + 8 j: part e % 3 of column block e / 3
 #pragma unroll
   for (int j = 0; j < G::LB; ++j) boff[j] = (uint32_t)((w + 8 * j) % 3 * cbp + (w + 8 * j) / 3 * 16) * 16u;
@@ -179,30 +177,35 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
       for (int nb = 0; nb < G::WN0; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
 
     // panels of near-equal numbers of offsets whose row table fits the LDS
-    const int npan = (sb - sa + G::PANEL - 1) / G::PANEL;
+    const int npan = (sb - sa + plan.panel - 1) / plan.panel;
     for (int pn = 0; pn < npan; ++pn) {
-      const int s0 = sa + (sb - sa) * pn / npan, s1 = sa + (sb - sa) * (pn + 1) / npan, ns = s1 - s0;
+      const int s0 = sa + (sb - sa) * pn / npan, ns = sa + (sb - sa) * (pn + 1) / npan - s0;
       const int n_act = load_panel<BM>(nbr, n_pos, p0, s0, ns, row_bytes, rows, bmask, act, n_act_p);
       const int nchunk = order.chunks(n_act);
+      if (nchunk == 0) continue;
+      chunk_table(order, n_act, nchunk, act, ns, BM * 4, s0, cg, (uint32_t)cbp * 48u, tab);
 
-      // the chunk being fetched: this wavefront's rows, this lane group's channels, kappa position
-      ChunkWalk walk;
-      uint32_t arow[NRB], bbase, achan;
-      auto refresh = [&](int slot, int ch) {
-        const bool live = slot < n_act;
-        const int j = live ? act[slot] : 0;
-        achan = (uint32_t)(ch >> 5) * 192u + (ch & 31) * 2u;
+      // position of the chunk being fetched (rows, kappa) and the table entry of the one after it
+      uint32_t arow[NRB], bbase;
+      uint2 ent = tab[g];
+      const uint2* next = tab + g;
+      const uint32_t colb = (uint32_t)(n0 + r16) * 16u;
+      auto advance = [&]() {
+        const uint32_t c8 = ent.x >> 18;  // channel / 8: its chunk of 192 bytes, 16 bytes within each part
 #pragma unroll
         for (int q = 0; q < NRB; ++q)
-          arow[q] = live ? rows[j * BM + 16 * ((w + 8 * q) % (4 * MR)) + r16] : kAbsentRow32;
-        bbase = live ? ((uint32_t)((s0 + j) * cg + (ch >> 3)) * 3u * (uint32_t)cbp + (uint32_t)(n0 + r16)) * 16u : 0u;
+          arow[q] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(my_rows + 128 * q) + (ent.x & 0x3ffffu)) +
+                    (c8 >> 2) * 192u + (c8 & 3u) * 16u;
+        bbase = ent.y + colb;
+        next += 4;
+        ent = *next;
       };
       // DMA q of this wavefront for the chunk going into stage k: q < LA a row block's part, else a
       // part of a kappa block
       auto dma = [&](int q, uint32_t sbase) {
         if (q < G::LA) {
           // row block w + 8 (q % 2) part q / 2 of 16 blocks; block w part q of 8; block w % 4 part w / 4 + 2 q of 4
-          const uint32_t row = arow[MR == 4 ? q & 1 : 0] + achan;
+          const uint32_t row = arow[MR == 4 ? q & 1 : 0];
           if constexpr (MR == 4)
             dma16_tile(a_rsrc, row + (q >> 1) * 64u, sbase + w * 3072 + (q & 1) * 24576 + (q >> 1) * 1024);
           else if constexpr (MR == 2)
@@ -219,12 +222,9 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
             dma16_tile(a_rsrc, kAbsentRow32, junk_a);
         }
       };
-      auto advance = [&]() {
-        walk.advance(order, n_act, g, [&]() { achan += 192u, bbase += bstep; }, refresh);
-      };
-      walk.seek(order, n_act, g, refresh);
+      advance();
       wait_vm<0>();  // the waits below count this panel's DMAs alone
-      for (int c = 0; c < S - 1 && c < nchunk; ++c) {
+      for (int c = 0; c < S - 1; ++c) {
 #pragma unroll
         for (int q = 0; q < G::L; ++q) dma(q, stage0 + c * G::STAGE);
         advance();
@@ -232,7 +232,8 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
 
       // iteration c: this wavefront's DMAs of chunk c have landed, one barrier publishes them (and
       //    retires the reads of the stage refilled next); the fragments are read one step ahead of the
-      //    MFMAs that use them, the DMAs of chunk c + S - 1 go out between the first steps
+      //    MFMAs that use them, the DMAs of chunk c + S - 1 go out between the first steps (past the last
+      //    chunk: of absent rows, so that the loop has no conditions)
 #define SSG_RDA(d_, mb_)                                                                            \
   _Pragma("unroll") for (int p = 0; p < 3; ++p)                                                     \
     d_[p] = *reinterpret_cast<const uint4*>(sb_ + ((wm * MR + (mb_)) * 3 + p) * 1024 + 16 * lane)
@@ -247,12 +248,8 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
     constexpr int NS = 2 * MR * NP;             /* places for DMAs: two per step */                 \
     int k_ = 0, ki_ = S - 1;                                                                        \
     for (int c = 0; c < nchunk; ++c) {                                                              \
-      if (c + S - 2 < nchunk)                                                                       \
-        wait_vm<(S - 2) * G::L>();                                                                  \
-      else                                                                                          \
-        wait_vm<0>();                                                                               \
-      __syncthreads();                                                                              \
-      const bool iss_ = c + S - 1 < nchunk;                                                         \
+      wait_vm<(S - 2) * G::L>();                                                                    \
+      asm volatile("s_barrier" ::: "memory");                                                       \
       const char* sb_ = stages + k_ * G::STAGE;                                                     \
       const uint32_t si_ = stage0 + ki_ * G::STAGE;                                                 \
       uint4 fa[2][3], fb[WNX][3];                                                                   \
@@ -275,7 +272,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
           _Pragma("unroll") for (int th = 0; th < 2; ++th) {                                        \
             const int place = (mb * NP + np) * 2 + th;                                              \
             _Pragma("unroll") for (int q = place * G::L / NS; q < (place + 1) * G::L / NS; ++q)     \
-              if (iss_) dma(q, si_);                                                                \
+              dma(q, si_);                                                                          \
             /* the step before: its small terms, long done, join the sum */                         \
             if (th == 1 && mb * NP + np > 0) {                                                      \
               const int pmb = np > 0 ? mb : mb - 1, pnp = np > 0 ? np - 1 : NP - 1;                 \
@@ -298,7 +295,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
           }                                                                                         \
         }                                                                                           \
       }                                                                                             \
-      if (iss_) advance();                                                                          \
+      advance();                                                                                    \
       _Pragma("unroll") for (int nb = 2 * NP - 2; nb < WNX; ++nb)                                   \
         acc[MR - 1][nb] += low_[(MR * NP - 1) & 1][nb - 2 * NP + 2];                                \
       k_ = k_ + 1 == S ? 0 : k_ + 1;                                                                \
@@ -310,6 +307,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
       } else {
         if (wn == 0) SSG_LOOP(G::WN0, 0) else SSG_LOOP(G::WN1, G::WN0)
       }
+      wait_vm<0>();  // the fetches past the end land before the stages are used again
 #undef SSG_LOOP
 #undef SSG_RDA
 #undef SSG_RDB
@@ -451,13 +449,16 @@ SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
 }
 
 template <int NB, int MR>
-int launch(const SplitShape& s, const uint16_t* A3, int64_t a_bytes, int ca, const uint16_t* B3, int cb,
+int launch(const SplitShape& sh, const uint16_t* A3, int64_t a_bytes, int ca, const uint16_t* B3, int cb,
            const int32_t* nbr, int64_t n_pos, int K, float* part, const float* src, const SplitKernel& B, float* out,
            hipStream_t st) {
   auto kern = gather_split_kernel<NB, MR>;
-  const size_t smem = GS<NB, MR>::smem(K);
+  using G = GS<NB, MR>;
+  TilePlan plan = sh.plan;
+  plan.panel = panel_offsets(G::ROOM, G::BM, pad_k(ca), K);
+  const size_t smem = (size_t)(kTileLds - G::ROOM) + panel_bytes(plan.panel, G::BM, pad_k(ca));
   SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  kern<<<s.plan.G, kTileThreads, smem, st>>>(A3, a_bytes, ca, B3, cb, nbr, n_pos, K, s.plan, part, src, B, out);
+  kern<<<plan.G, kTileThreads, smem, st>>>(A3, a_bytes, ca, B3, cb, nbr, n_pos, K, plan, part, src, B, out);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
 }
@@ -465,7 +466,7 @@ int launch(const SplitShape& s, const uint16_t* A3, int64_t a_bytes, int ca, con
 }  // namespace
 
 bool gather_split_supported(int64_t n_src, int ca, int cb, int K) {
-  return ca >= 1 && cb >= 1 && K >= 1 && K <= kTileMaxK && n_src >= 1 && a3_bytes(n_src, ca) < ((size_t)1 << 31) &&
+  return ca >= 1 && ca <= 4096 && cb >= 1 && K >= 1 && K <= kTileMaxK && n_src >= 1 && a3_bytes(n_src, ca) < ((size_t)1 << 31) &&
          b3_bytes(ca, cb, K) < ((size_t)1 << 31);
 }
 

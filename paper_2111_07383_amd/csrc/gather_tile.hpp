@@ -27,7 +27,7 @@ inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // (tile, offset) sequence (units = mt * nt * K), so that every workgroup has the same number of offsets
 // whatever the tile count.
 struct TilePlan {
-  int G, mt, nt;
+  int G, mt, nt, panel;  // panel: offsets whose tables fit the LDS at a time
   int64_t row0, units;
 };
 inline bool whole_tiles(const TilePlan& p, int K) { return p.units % ((int64_t)p.G * K) == 0; }
@@ -59,8 +59,8 @@ __device__ __forceinline__ void dma16_tile(__amdgpu_buffer_rsrc_t rsrc, uint32_t
 #pragma clang diagnostic pop
 
 // The rows (byte offsets, kAbsentRow32: no neighbour) of tile rows p0 .. p0 + BM - 1 at offsets s0 .. s0 + ns
-// - 1 into rows[ns][BM], and the ordered list act of the offsets that occur at all; returns their number.
-// Begins and ends with a barrier.
+// - 1 into rows[ns + 1][BM] (the last row: all absent), and the ordered list act of the offsets that occur
+// at all; returns their number.  Begins and ends with a barrier.
 template <int BM>
 __device__ __forceinline__ int load_panel(const int32_t* __restrict__ nbr, int64_t n_pos, int64_t p0, int s0, int ns,
                                           uint32_t row_bytes, uint32_t* rows, uint32_t* bmask, uint8_t* act,
@@ -70,6 +70,7 @@ __device__ __forceinline__ int load_panel(const int32_t* __restrict__ nbr, int64
   const int lane = tid & 63;
   __syncthreads();  // the previous panel (or tile) is done with the table and the stages
   for (int s = tid; s < ns; s += kTileThreads) bmask[s] = 0u;
+  if (tid < BM) rows[ns * BM + tid] = kAbsentRow32;
   __syncthreads();
   {
     constexpr int STEP = kTileThreads / BM;  // offsets read side by side, 8 requests in flight per thread
@@ -110,44 +111,58 @@ __device__ __forceinline__ int load_panel(const int32_t* __restrict__ nbr, int64
 // `quad` (4 or 2) offsets, lane group g reading its share.  Whole chunks start at multiples of 64 bytes
 // of the row: chunks that straddle two such pieces cost the texture path a second access per row.
 struct ChunkOrder {
-  int full, rest, quad, g_slot, g_ch;
-  __device__ __forceinline__ ChunkOrder(int cap, int g)
-      : full(cap / 32), rest(cap % 32), quad(rest ? 32 / rest : 1), g_slot(rest ? 8 * g / rest : 0),
-        g_ch(rest ? 32 * full + 8 * g % rest : 0) {}
-  __device__ __forceinline__ int chunks(int n_act) const { return n_act * full + (rest ? (n_act + quad - 1) / quad : 0); }
-};
-// Where the next chunk to fetch is: whole chunk f of offset slot (slot < end of its group), else the rests
-// of the group that starts at base.
-struct ChunkWalk {
-  int base = 0, slot = 0, f = 0;
-  // start(o, n_act, refresh): refresh(slot, channel) for this lane group of the first chunk
-  template <typename R>
-  __device__ __forceinline__ void seek(const ChunkOrder& o, int n_act, int g, R&& refresh) {
-    const int end = base + o.quad < n_act ? base + o.quad : n_act;
-    if (o.full == 0) slot = end;
-    if (slot < end)
-      refresh(slot, 8 * g);
-    else if (o.rest)
-      refresh(base + o.g_slot, o.g_ch);
+  int full, rest, quad;
+  __host__ __device__ __forceinline__ explicit ChunkOrder(int cap)
+      : full(cap / 32), rest(cap % 32), quad(rest ? 32 / rest : 1) {}
+  __host__ __device__ __forceinline__ int chunks(int n_act) const {
+    return n_act * full + (rest ? (n_act + quad - 1) / quad : 0);
   }
-  // next chunk: step() within an offset, refresh() otherwise
-  template <typename S, typename R>
-  __device__ __forceinline__ void advance(const ChunkOrder& o, int n_act, int g, S&& step, R&& refresh) {
-    const int end = base + o.quad < n_act ? base + o.quad : n_act;
-    if (slot < end) {
-      if (++f < o.full) {
-        step();
-        return;
-      }
-      f = 0;
-      ++slot;
-      if (slot == end && !o.rest) base = end;
+  // offset slot and first channel of lane group g in chunk c (slot >= n_act: nothing)
+  __device__ __forceinline__ void at(int c, int g, int n_act, int* slot, int* ch) const {
+    const int per = quad * full + (rest ? 1 : 0), grp = c / per, i = c - grp * per, base = grp * quad;
+    const int m = base + quad < n_act ? quad : n_act - base;
+    if (i < m * full) {
+      *slot = base + i / full;
+      *ch = 32 * (i % full) + 8 * g;
     } else {
-      base = slot = end;
-      f = 0;
+      *slot = base + 8 * g / rest;
+      *ch = 32 * full + 8 * g % rest;
     }
-    seek(o, n_act, g, refresh);
   }
 };
+
+// What the chunk loop reads instead of working positions out: entry [c][g] of chunk c and lane group g =
+// {byte offset of the offset's row table | channel / 8 << 18, byte offset of the kappa group}; chunks past
+// the last are absent rows.  (Positions kept in registers and advanced by branches took 350 instructions a
+// chunk of 28 MFMAs, which bound the bf16 kernel.)
+constexpr int kChunkAhead = 8;  // absent entries past the last chunk
+__device__ __forceinline__ void chunk_table(const ChunkOrder& o, int n_act, int nchunk, const uint8_t* act, int absent,
+                                            int bm4, int s0, int cg, uint32_t group_bytes, uint2* tab) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  for (int i = tid; i < 4 * (nchunk + kChunkAhead); i += kTileThreads) {
+    const int c = i >> 2, g = i & 3;
+    int slot = n_act, ch = 0;
+    if (c < nchunk) o.at(c, g, n_act, &slot, &ch);
+    uint2 e = make_uint2((uint32_t)(absent * bm4), 0u);
+    if (slot < n_act) {
+      const int j = act[slot];
+      e = make_uint2((uint32_t)(j * bm4) | (uint32_t)(ch >> 3) << 18, (uint32_t)((s0 + j) * cg + (ch >> 3)) * group_bytes);
+    }
+    tab[i] = e;
+  }
+  __syncthreads();
+}
+
+// Offsets per panel whose row table (BM rows each, and one of absent rows) and chunk table fit `room` bytes of
+// LDS, and the bytes they take.
+inline int panel_offsets(int room, int BM, int cap, int K) {
+  const int per = BM * 4 + 32 * (cap / 32 + 1), fixed = BM * 4 + 32 * kChunkAhead;
+  const int n = (room - fixed) / per;
+  return n < 0 ? 0 : n < K ? n : K;
+}
+inline size_t panel_bytes(int panel, int BM, int cap) {
+  return (size_t)(panel + 1) * BM * 4 + 32 * ((size_t)panel * (cap / 32 + 1) + kChunkAhead);
+}
 
 }  // namespace ssconv
