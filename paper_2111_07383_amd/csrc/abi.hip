@@ -148,12 +148,26 @@ extern "C" int ssconv_backward(const void* feats, const void* grad_out, ssconv_d
   const bool fork = both && L.pair_feats;
   const bool fork_tail = both && !L.pair_feats && rb->n_in > 0 && dtype == SSCONV_F32;
   bool need_join = fork;
-  if (fork) SSC_TRY(aux_fork(stream, &dw_stream));
+  BwdRows rows;
+  if (grad_coeffs) {
+    const int rr = bwd_rows(feats, grad_out, dtype, cin, cout, rb, &rows, stream);
+    if (rr != SSCONV_OK) {
+      if (rows.ws) dev_free(rows.ws, stream);
+      return rr;
+    }
+  }
+  if (fork) {
+    const int fr = aux_fork(stream, &dw_stream);
+    if (fr != SSCONV_OK) {
+      if (rows.ws) dev_free(rows.ws, stream);
+      return fr;
+    }
+  }
   int rc = SSCONV_OK;
   if (grad_coeffs) {
     float* dW = nullptr;
     hipStream_t tail = dw_stream;
-    rc = conv_backward_dw(feats, grad_out, dtype, cin, cout, rb, sa.out, sa.in, ws, L, &dW, dw_stream,
+    rc = conv_backward_dw(feats, grad_out, dtype, cin, cout, rb, sa.out, sa.in, ws, L, rows, &dW, dw_stream,
                           fork_tail ? &tail : nullptr);
     if (fork_tail && tail != stream) {
       dw_stream = tail;
@@ -166,12 +180,13 @@ extern "C" int ssconv_backward(const void* feats, const void* grad_out, ssconv_d
       if (hipMemsetAsync(grad_feats, 0, (size_t)rb->n_in * cin * dtype_bytes(dtype), stream) != hipSuccess)
         rc = fail(SSCONV_E_HIP, "hipMemsetAsync failed");
     } else {
-      rc = conv_backward_feats(grad_out, dtype, cin, cout, rb, W, grad_feats, ws, L, stream);
+      rc = conv_backward_feats(grad_out, dtype, cin, cout, rb, W, grad_feats, ws, L, rows, stream);
     }
   }
   if (need_join) {
     const int jr = aux_join(stream, dw_stream);  // always joined, so nothing stays pending on the side stream
     if (rc == SSCONV_OK) rc = jr;
   }
+  if (rows.ws) dev_free(rows.ws, stream);
   return rc;
 }

@@ -25,6 +25,7 @@
 #include "norm.hpp"
 #include "gather_mfma.hpp"
 #include "gather_split.hpp"
+#include "gather_tile.hpp"
 #include "kgrad_mfma.hpp"
 
 namespace ssconv {
@@ -353,6 +354,14 @@ static bool use_split(const CallScratch* sc, int64_t n_src, int ca, int cb, int6
   return !(sc && sc->fixed()) || gather_split_bytes(n_src, ca, cb, n_pos, K) <= sc->left();
 }
 
+// Forwards below 2^35 multiply-adds keep the fp32 MFMA kernel and its bits: what follows a convolution may
+// decide by sign (ReLU, gates), so that any change of rounding can turn single decisions over, and a small
+// call gains little (2.5k sites, 3x3x3, 104 -> 128: 52 -> 35 us; 36k sites, 5x5x5, 104 -> 104, 49 G: 1100 ->
+// 490).  Gradients are linear in what they sum and take the faster kernel at every size.
+static bool split_forward(const ssconv_rulebook* rb, int cin, int cout) {
+  return debug_gather_variant() == 13 || (double)rb->n_out * rb->K * cin * cout >= 34359738368.0;
+}
+
 // Records the timing-hook events (ssconv_debug_set option 4) around one kernel launch.
 struct KernelTimer {
   hipEvent_t start = nullptr, stop = nullptr;
@@ -372,7 +381,7 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
   // the pair-list path needs its Y buffer; with a fixed scratch region too small for it the
   // output-stationary kernel runs instead (same sums, another order of the fp32 additions)
   const bool pair_fits = !(sc && sc->fixed()) || pair_path_bytes(rb, cin, cout, rb->n_out) <= sc->left();
-  if (dt == SSCONV_F32 && pair_fits && pair_path_wins(rb, dt, cin, cout, rb->n_out)) {
+  if (dt == SSCONV_F32 && pair_fits && pair_path_wins(rb, dt, cin, cout, rb->n_out, true)) {
     void* ws = nullptr;
     SSC_TRY(scratch_take(sc, &ws, pair_path_bytes(rb, cin, cout, rb->n_out), st));
     int rc;
@@ -383,7 +392,7 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
     scratch_give(sc, ws, st);
     return rc;
   }
-  if (dt == SSCONV_F32 && use_split(sc, rb->n_in, cin, cout, rb->n_out, rb->K)) {
+  if (dt == SSCONV_F32 && split_forward(rb, cin, cout) && use_split(sc, rb->n_in, cin, cout, rb->n_out, rb->K)) {
     KernelTimer timer(st);
     return gather_split((const float*)feats, rb->n_in, cin, {(const float*)W, 0, 0}, cout, rb->nbr, rb->n_out, rb->K,
                         (float*)out, st, sc);
@@ -438,23 +447,69 @@ int dw_nsplit(const ssconv_rulebook* rb) {
   return (int)ns;
 }
 
-static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+// Bytes of a row as the tile kernel gradient reads it, and of the copy it takes where it cannot be read in place.
+static int64_t kgrad_row_bytes(ssconv_dtype dt, int c) {
+  return dt == SSCONV_F32 ? split_row_bytes(c) : 2 * (int64_t)(c % 8 == 0 ? c : pad32(c));
+}
+static size_t kgrad_copy_bytes(ssconv_dtype dt, int64_t n, int c) {
+  return dt == SSCONV_BF16 && c % 8 == 0 ? 0 : align256((size_t)n * kgrad_row_bytes(dt, c));
+}
 
-// The bf16 kernel gradient cuts the pair lists into work units, one per compute unit (measured on
-// the 128^3 208-channel layer: 512 units ran the gradient no faster and doubled the partials to add).
-constexpr int kKgradUnits = 256;
+// The kernel gradient on the bf16 matrix cores: every row offset below 2^31.  Overrides 6 and 12 keep the
+// other bf16 kernels (12 where it has the channels in columns), 7 the fp32 one that loads rows into registers.
+static bool use_kgrad_tiles(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
+  const int64_t v = debug_gather_variant();
+  // splitting costs a pass over the rows: not where each is gathered a few times only (60 -> 120 channels, 99k
+  // pairs of 79k rows: 22 us and 15 for the split against 36 on the fp32 ring kernel; 17k of 1.9k: 9 and 4
+  // against 20)
+  if (dt == SSCONV_F32 && rb->n_pairs < 6 * (rb->n_in + rb->n_out)) return false;
+  if (dt == SSCONV_F32 ? v == 7 : v == 6 || (v == 12 && kgrad_supported(dt, cin, cout))) return false;
+  return rb->K <= kKgradMaxK && rb->n_in > 0 && rb->n_out > 0 &&
+         rb->n_in * kgrad_row_bytes(dt, cin) < ((int64_t)1 << 31) && rb->n_out * kgrad_row_bytes(dt, cout) < ((int64_t)1 << 31);
+}
 
 static bool use_kgrad_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
+  if (use_kgrad_tiles(rb, dt, cin, cout)) return true;
   if (dt == SSCONV_F32) return kgrad_f32_units_ok(rb, cin, cout);
   return debug_gather_variant() != 6 && kgrad_supported(dt, cin, cout) && rb->K <= kKgradMaxK &&
          (int64_t)rb->n_in * cin * 2 < ((int64_t)1 << 31) && (int64_t)rb->n_out * cout * 2 < ((int64_t)1 << 31);
 }
 
-// Work units of the kernel gradient: bf16 ~256 (one workgroup each, launched in row order), fp32
-// enough wavefront tasks for one round of the wavefront slots.
+// Work units of the kernel gradient: as many slices of every offset on the tile kernel (and the bf16 one in
+// columns, override 12), launched slice by slice; on the fp32 ring kernel slices of about equal length, enough
+// wavefront tasks for one round of the wavefront slots.
 static KgradUnits plan_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
-  if (dt == SSCONV_F32) return kgrad_units(rb, kgrad_f32_units_want(rb, cin, cout), false);
-  return kgrad_units(rb, kKgradUnits, true);
+  if (dt == SSCONV_F32 && !use_kgrad_tiles(rb, dt, cin, cout))
+    return kgrad_units(rb, kgrad_f32_units_want(rb, cin, cout));
+  KgradUnits u;
+  u.K = rb->K;
+  u.even = kgrad_tile(rb, dt == SSCONV_F32 ? 3 : 1, cin, cout).slices;
+  for (int s = 0; s <= rb->K; ++s) u.uoff[s] = s * u.even;
+  u.nunits = u.uoff[rb->K];
+  if (dt == SSCONV_BF16)
+    for (int i = 0; i < u.nunits && i < kKgradMaxUnits; ++i) u.order[i] = (uint16_t)(i % u.K * u.even + i / u.K);
+  return u;
+}
+
+int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
+             BwdRows* r, hipStream_t st) {
+  if (!use_kgrad_tiles(rb, dt, cin, cout)) return SSCONV_OK;
+  const size_t gb = kgrad_copy_bytes(dt, rb->n_out, cout), fb = kgrad_copy_bytes(dt, rb->n_in, cin);
+  if (gb + fb > 0) SSC_TRY(dev_alloc(&r->ws, gb + fb, st));
+  uint16_t* gc = gb ? (uint16_t*)r->ws : nullptr;
+  uint16_t* fc = fb ? (uint16_t*)((char*)r->ws + gb) : nullptr;
+  const int64_t ng = gc ? rb->n_out : 0, nf = fc ? rb->n_in : 0;
+  int rc;
+  if (dt == SSCONV_F32)
+    rc = split_rows((const float*)grad_out, ng, cout, gc, (const float*)feats, nf, cin, fc, st);
+  else
+    rc = pad_rows_bf16((const uint16_t*)grad_out, ng, cout, gc, (const uint16_t*)feats, nf, cin, fc, st);
+  const int64_t gs = kgrad_row_bytes(dt, cout), fs = kgrad_row_bytes(dt, cin);
+  r->parts = dt == SSCONV_F32 ? 3 : 1;
+  r->grad_out = {gc ? gc : grad_out, rb->n_out * gs, (int)gs};
+  r->feats = {fc ? fc : feats, rb->n_in * fs, (int)fs};
+  r->grad_out_copy = gc;
+  return rc;
 }
 
 BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
@@ -468,7 +523,7 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
     nparts = (size_t)L.nsplit * K;
   }
   size_t o = 0;
-  L.pair_feats = dt == SSCONV_F32 && rb->n_in > 0 && pair_path_wins(rb, dt, cout, cin, rb->n_in);
+  L.pair_feats = dt == SSCONV_F32 && rb->n_in > 0 && pair_path_wins(rb, dt, cout, cin, rb->n_in, false);
   L.nbrT = o;  // inverse neighbour map: only generated output sets on the gather kernels need one
   if (!rb->submanifold && !L.pair_feats) o += align256(K * (size_t)rb->n_in * 4);
   L.pair = o;
@@ -488,7 +543,8 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
 // holds exactly when x = y - d(K-1-s), d(K-1-s) = -d(s), on the same site set), so it runs on the
 // forward map with kappa^T stored in reversed offset order and no inverse map is built.
 int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
-                        const void* W, void* grad_feats, char* ws, const BwdLayout& L, hipStream_t st) {
+                        const void* W, void* grad_feats, char* ws, const BwdLayout& L, const BwdRows& rows,
+                        hipStream_t st) {
   if (rb->n_in == 0) return SSCONV_OK;
   if (L.pair_feats) {
     // kappa^T in the same offset order: the pairs of R_s are walked with their roles swapped
@@ -517,7 +573,7 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
   if (dt == SSCONV_F32 && use_split(nullptr, rb->n_out, cout, cin, rb->n_in, K)) {
     KernelTimer timer(st);
     return gather_split((const float*)grad_out, rb->n_out, cout, {(const float*)W, 1, mirror ? 1 : 0}, cin, nbrT,
-                        rb->n_in, K, (float*)grad_feats, st, nullptr);
+                        rb->n_in, K, (float*)grad_feats, st, nullptr, rows.grad_out_copy);
   }
   if (dt == SSCONV_F32) {
     transpose_kernel<float><<<cdiv(nw, 256), 256, 0, st>>>((const float*)W, K, cout, cin, mirror, (float*)Wt);
@@ -527,7 +583,8 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
   }
   if (use_bf16_kernel(nullptr, dt, rb->n_out, cout, cin, rb->n_in, K)) {
     KernelTimer timer(st);
-    return gather_bf16(grad_out, rb->n_out, cout, W, true, mirror, cin, nbrT, rb->n_in, K, grad_feats, st, nullptr);
+    return gather_bf16(grad_out, rb->n_out, cout, W, true, mirror, cin, nbrT, rb->n_in, K, grad_feats, st, nullptr,
+                       rows.grad_out_copy);
   }
   transpose_kernel<uint16_t><<<cdiv(nw, 256), 256, 0, st>>>((const uint16_t*)W, K, cout, cin, mirror, (uint16_t*)Wt);
   SSC_HIP(hipGetLastError());
@@ -537,7 +594,7 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
 
 int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout,
                      const ssconv_rulebook* rb, const FieldTab& fout, const FieldTab& fin, char* ws,
-                     const BwdLayout& L, float** dW_out, hipStream_t st, hipStream_t* tail) {
+                     const BwdLayout& L, const BwdRows& rows, float** dW_out, hipStream_t st, hipStream_t* tail) {
   float* part = (float*)(ws + L.part);
   float* dW = (float*)(ws + L.dW);
   *dW_out = dW;
@@ -546,7 +603,13 @@ int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, i
   const int64_t n = (int64_t)K * cin * cout;
   if (use_kgrad_units(rb, dt, cin, cout)) {
     const KgradUnits units = plan_units(rb, dt, cin, cout);
-    if (dt == SSCONV_F32)
+    PlainGrad plain;
+    if (rows.parts) {
+      SSC_TRY(kgrad_tiles(rows.grad_out, rows.feats, rows.parts, cin, cout, rb, kgrad_tile(rb, rows.parts, cin, cout),
+                          units, part, st));
+      if (rows.parts == 3)
+        plain = {(const float*)grad_out, (const float*)feats, reinterpret_cast<const int2*>(rb->pairs), rb->pair_off_dev};
+    } else if (dt == SSCONV_F32)
       SSC_TRY(kgrad_f32(grad_out, feats, cin, cout, rb, units, part, st));
     else
       SSC_TRY(kgrad_bf16(grad_out, rb->n_out, feats, rb->n_in, cin, cout, rb, units, part, st));
@@ -555,7 +618,7 @@ int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, i
       SSC_TRY(aux_fork(st, &rst));
       *tail = rst;
     }
-    return reduce_units(part, units, cin, cout, fout, fin, dW, rst);
+    return reduce_units(part, units, cin, cout, fout, fin, dW, rst, plain);
   }
   if (kgrad_supported(dt, cin, cout))
     SSC_TRY(kgrad_partials(grad_out, feats, dt, cin, cout, rb, kgrad_plan(rb, dt, cin, cout), part, st));

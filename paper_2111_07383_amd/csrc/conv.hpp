@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "kgrad_tile.hpp"
 
 namespace ssconv {
 
@@ -13,9 +14,20 @@ struct BwdLayout {
   bool pair_feats = false;  // feature gradient on the pair-list path
 };
 
+// The rows of a backward call as the tile kernels read them (split, or padded where the channels are not a
+// multiple of 8), made once for the kernel and the feature gradient; parts = 0: not on the tile kernels.
+struct BwdRows {
+  int parts = 0;
+  KgradRows grad_out, feats;
+  const uint16_t* grad_out_copy = nullptr;  // grad_out.p where it is a copy
+  void* ws = nullptr;                       // from the device memory cache; the caller gives it back
+};
+int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
+             BwdRows* r, hipStream_t st);
+
 // Pair-list GEMM for sparse fp32 layers (pair_gemm.hip).
 bool pair_path_supported(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb);
-bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst);
+bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst, bool forward);
 size_t pair_path_bytes(const ssconv_rulebook* rb, int ca, int cb, int64_t n_dst);
 // sink (optional): the reduce pass also leaves the Norm statistics of dst there (norm.hpp).
 int pair_gemm(const void* src, int ca, const void* Bt, int cb, const ssconv_rulebook* rb, int sel_in, void* dst,
@@ -30,13 +42,15 @@ int conv_forward_norm(const void* feats, ssconv_dtype dt, int cin, const ssconv_
                       const FieldTab& f, double eps, void* y, void* z, hipStream_t st);
 BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout);
 int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
-                        const void* W, void* grad_feats, char* ws, const BwdLayout& L, hipStream_t st);
+                        const void* W, void* grad_feats, char* ws, const BwdLayout& L, const BwdRows& rows,
+                        hipStream_t st);
 // Kernel gradient dW in the field-pair-blocked layout (dw_block_pos) of the fields fout, fin.
 // With tail given, a balanced-unit kernel gradient forks its reduction onto the library's second
 // stream (aux_fork after the partials are queued on st) and *tail receives the stream dW is
 // complete on (st when nothing was forked); the caller joins it.
 int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout,
                      const ssconv_rulebook* rb, const FieldTab& fout, const FieldTab& fin, char* ws,
-                     const BwdLayout& L, float** dW_out, hipStream_t st, hipStream_t* tail = nullptr);
+                     const BwdLayout& L, const BwdRows& rows, float** dW_out, hipStream_t st,
+                     hipStream_t* tail = nullptr);
 
 }  // namespace ssconv

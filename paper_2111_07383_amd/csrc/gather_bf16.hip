@@ -296,28 +296,45 @@ __global__ __launch_bounds__(256) void bf16_fixup(const float* __restrict__ part
     if (col + k < cb) o[k] = f32_to_bf16_rne(v[k]);
 }
 
-// One launch for both operands.  Blocks below row_blocks: rows [n][ca] -> [n][pad32(ca)], zeros past ca, a
-// thread per 8 channels (row_blocks = 0: the rows are read in place).  The others: Bp[s][k / 8][n][k % 8]
-// (pad_k(ca) / 8 groups of pad16(cb) columns, zeros past the ends) from kappa given as Bt[s'][n][k]
-// (transposed = 0) or as W[s'][k][n] (transposed = 1), s' = s or K-1-s (mirror), a thread per 16 bytes.
+// Thread i copies 8 channels of one row of [n][ca] to [n][pad32(ca)], zeros past ca.
+__device__ __forceinline__ void pad_row(const uint16_t* __restrict__ src, int64_t n, int ca, int64_t i,
+                                        uint16_t* __restrict__ Ap) {
+  const int per = pad32(ca) / 8;
+  if (i >= n * per) return;
+  const int64_t r = i / per;
+  const int k0 = (int)(i - r * per) * 8;
+  uint16_t e[8];
+  uint4 v;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) e[j] = k0 + j < ca ? src[r * ca + k0 + j] : (uint16_t)0;
+  __builtin_memcpy(&v, e, 16);
+  *reinterpret_cast<uint4*>(Ap + i * 8) = v;
+}
+
+// Rows of two sources in one launch.
+__global__ __launch_bounds__(256) void pad_rows_kernel(const uint16_t* __restrict__ x, int64_t nx, int cx, unsigned x_blocks,
+                                                       uint16_t* __restrict__ xp, const uint16_t* __restrict__ y, int64_t ny,
+                                                       int cy, uint16_t* __restrict__ yp) {
+  if (blockIdx.x < x_blocks)
+    pad_row(x, nx, cx, (int64_t)blockIdx.x * 256 + threadIdx.x, xp);
+  else
+    pad_row(y, ny, cy, (int64_t)(blockIdx.x - x_blocks) * 256 + threadIdx.x, yp);
+}
+
+// One launch for both operands.  Blocks below row_blocks pad the rows (row_blocks = 0: they are read in
+// place).  The others: Bp[s][k / 8][n][k % 8] (pad_k(ca) / 8 groups of pad16(cb) columns, zeros past the
+// ends) from kappa given as Bt[s'][n][k] (transposed = 0) or as W[s'][k][n] (transposed = 1), s' = s or
+// K-1-s (mirror), a thread per 16 bytes.
 __global__ __launch_bounds__(256) void pack_operands(const uint16_t* __restrict__ src, int64_t n_src, int ca,
                                                      unsigned row_blocks, const uint16_t* __restrict__ W, int K, int cb,
                                                      int transposed, int mirror, uint16_t* __restrict__ Ap,
                                                      uint16_t* __restrict__ Bp) {
-  uint16_t e[8];
-  uint4 v;
   if (blockIdx.x < row_blocks) {
-    const int per = pad32(ca) / 8;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_src * per) return;
-    const int64_t r = i / per;
-    const int k0 = (int)(i - r * per) * 8;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) e[j] = k0 + j < ca ? src[r * ca + k0 + j] : (uint16_t)0;
-    __builtin_memcpy(&v, e, 16);
-    *reinterpret_cast<uint4*>(Ap + i * 8) = v;
+    pad_row(src, n_src, ca, (int64_t)blockIdx.x * 256 + threadIdx.x, Ap);
     return;
   }
+  uint16_t e[8];
+  uint4 v;
   const int cg = pad_k(ca) / 8, cbp = pad16(cb);
   const int64_t i = (int64_t)(blockIdx.x - row_blocks) * 256 + threadIdx.x;
   if (i >= (int64_t)K * cg * cbp) return;
@@ -431,6 +448,15 @@ int launch_bf16(TilePlan plan, const void* src, int64_t src_bytes, int row_bytes
 
 }  // namespace
 
+int pad_rows_bf16(const uint16_t* x, int64_t nx, int cx, uint16_t* xp, const uint16_t* y, int64_t ny, int cy, uint16_t* yp,
+                  hipStream_t st) {
+  const unsigned xb = cdiv(nx * (pad32(cx) / 8), 256), yb = cdiv(ny * (pad32(cy) / 8), 256);
+  if (xb + yb == 0) return SSCONV_OK;
+  pad_rows_kernel<<<xb + yb, 256, 0, st>>>(x, nx, cx, xb, xp, y, ny, cy, yp);
+  SSC_HIP(hipGetLastError());
+  return SSCONV_OK;
+}
+
 bool gather_bf16_supported(int64_t n_src, int ca, int cb, int K) {
   // 32-bit byte offsets: every gathered row and every packed kappa entry below 2^31
   // and a panel of at least two offsets
@@ -443,12 +469,13 @@ size_t gather_bf16_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
 }
 
 int gather_bf16(const void* src, int64_t n_src, int ca, const void* W, bool transposed, bool mirror, int cb,
-                const int32_t* nbr, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc) {
+                const int32_t* nbr, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc,
+                const uint16_t* padded) {
   if (n_pos == 0) return SSCONV_OK;
   const Bf16Shape s = bf16_shape(n_src, ca, cb, n_pos, K);
   char* ws = nullptr;
   SSC_TRY(scratch_take(sc, (void**)&ws, shape_bytes(s, n_src, ca, cb, K), st));
-  const bool pad = ca % 8 != 0;
+  const bool pad = ca % 8 != 0 && !padded;
   uint16_t* Ap = (uint16_t*)ws;
   uint16_t* Bp = (uint16_t*)(ws + ap_bytes(n_src, ca));
   float* part = (float*)(ws + ap_bytes(n_src, ca) + bp_bytes(ca, cb, K));
@@ -457,8 +484,8 @@ int gather_bf16(const void* src, int64_t n_src, int ca, const void* W, bool tran
   pack_operands<<<row_blocks + b_blocks, 256, 0, st>>>((const uint16_t*)src, n_src, ca, row_blocks, (const uint16_t*)W, K,
                                                        cb, transposed ? 1 : 0, mirror ? 1 : 0, Ap, Bp);
   int rc = hipGetLastError() == hipSuccess ? SSCONV_OK : fail(SSCONV_E_HIP, "operand packing launch failed");
-  const void* A = pad ? (const void*)Ap : src;
-  const int row_bytes = 2 * (pad ? pad32(ca) : ca);
+  const void* A = padded ? (const void*)padded : pad ? (const void*)Ap : src;
+  const int row_bytes = 2 * (padded || pad ? pad32(ca) : ca);
   for (int i = 0; i < s.n && rc == SSCONV_OK; ++i) {
 #define SSB_GO(NB_, MR_) \
   rc = launch_bf16<NB_, MR_>(s.plan[i], A, n_src * row_bytes, row_bytes, ca, Bp, cb, nbr, n_pos, K, part, out, st)

@@ -24,8 +24,14 @@ bool gather_bf16_supported(int64_t n_src, int ca, int cb, int K);
 // Scratch of a call (padded rows, packed kappa, pieces of tiles).
 size_t gather_bf16_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K);
 // out[p][:] = sum_s B[s] (cb x ca) . src[nbr[s][p]] for p < n_pos; B[s][n][k] = W[s'][n][k], or
-// W[s'][k][n] when transposed, s' = s or K-1-s (mirror); src holds n_src rows.
+// W[s'][k][n] when transposed, s' = s or K-1-s (mirror); src holds n_src rows; padded
+// (optional, channels not in multiples of 8): its rows padded by pad_rows_bf16.
 int gather_bf16(const void* src, int64_t n_src, int ca, const void* W, bool transposed, bool mirror, int cb,
-                const int32_t* nbr, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc);
+                const int32_t* nbr, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc,
+                const uint16_t* padded = nullptr);
+
+// Rows [n][c] -> [n][c rounded up to 32], zeros past c, of two sources (either may have no rows).
+int pad_rows_bf16(const uint16_t* x, int64_t nx, int cx, uint16_t* xp, const uint16_t* y, int64_t ny, int cy, uint16_t* yp,
+                  hipStream_t st);
 
 }  // namespace ssconv

@@ -50,33 +50,48 @@ __device__ __forceinline__ void store_parts(const uint16_t (*e)[3], uint16_t* ds
   }
 }
 
-// Both operands in one launch: blocks below row_blocks split the gathered rows (a thread takes 8
-// channels of one row), the others kappa into B3[s][pad_k(ca) / 8][3 parts][cb16][8] (zeros
-// past the end), a thread one 8-channel run of one column.
+// Thread i splits 8 channels of one row.
+__device__ __forceinline__ void split_row(const float* __restrict__ src, int64_t n, int ca, int64_t i,
+                                          uint16_t* __restrict__ A3) {
+  const int cc = chunks32(ca), per = 4 * cc;
+  if (i >= n * per) return;
+  const int64_t r = i / per;
+  const int q = (int)(i - r * per), c0 = 8 * q;
+  const float* s = src + r * ca + c0;
+  float v[8];
+  uint16_t e[8][3];
+  if ((ca & 3) == 0 && c0 + 8 <= ca) {
+    const float4 a = *reinterpret_cast<const float4*>(s), b = *reinterpret_cast<const float4*>(s + 4);
+    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = c0 + j < ca ? s[j] : 0.f;
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) split3(v[j], e[j]);
+  store_parts(e, A3 + (r * cc + (q >> 2)) * 96 + 8 * (q & 3), 32);
+}
+
+// Rows of two sources in one launch.
+__global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ x, int64_t nx, int cx, unsigned x_blocks,
+                                                         uint16_t* __restrict__ x3, const float* __restrict__ y,
+                                                         int64_t ny, int cy, uint16_t* __restrict__ y3) {
+  if (blockIdx.x < x_blocks)
+    split_row(x, nx, cx, (int64_t)blockIdx.x * 256 + threadIdx.x, x3);
+  else
+    split_row(y, ny, cy, (int64_t)(blockIdx.x - x_blocks) * 256 + threadIdx.x, y3);
+}
+
+// Both operands in one launch: blocks below row_blocks split the gathered rows, the others kappa into
+// B3[s][pad_k(ca) / 8][3 parts][cb16][8] (zeros past the end), a thread one 8-channel run of one column.
 __global__ __launch_bounds__(256) void split_operands(const float* __restrict__ src, int64_t n_src, int ca,
                                                       unsigned row_blocks, SplitKernel B, int K, int cb,
                                                       uint16_t* __restrict__ A3, uint16_t* __restrict__ B3) {
-  uint16_t e[8][3];
   if (blockIdx.x < row_blocks) {
-    const int cc = chunks32(ca), per = 4 * cc;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_src * per) return;
-    const int64_t r = i / per;
-    const int q = (int)(i - r * per), c0 = 8 * q;
-    const float* s = src + r * ca + c0;
-    float v[8];
-    if ((ca & 3) == 0 && c0 + 8 <= ca) {
-      const float4 a = *reinterpret_cast<const float4*>(s), b = *reinterpret_cast<const float4*>(s + 4);
-      v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = c0 + j < ca ? s[j] : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) split3(v[j], e[j]);
-    store_parts(e, A3 + (r * cc + (q >> 2)) * 96 + 8 * (q & 3), 32);
+    split_row(src, n_src, ca, (int64_t)blockIdx.x * 256 + threadIdx.x, A3);
     return;
   }
+  uint16_t e[8][3];
   const int cg = pad_k(ca) / 8, cbp = pad16(cb);
   const int64_t i = (int64_t)(blockIdx.x - row_blocks) * 256 + threadIdx.x;
   if (i >= (int64_t)K * cg * cbp) return;
@@ -95,7 +110,7 @@ __global__ __launch_bounds__(256) void split_operands(const float* __restrict__ 
 
 // One output by plain fp32 multiply-adds: what a value that the split cannot carry (infinite, NaN,
 // above bf16's largest, or so small that its third part would be lost) makes of an output is
-// computed again this way.
+// computed again this way (doubtful).
 __device__ __forceinline__ float plain_dot(const float* __restrict__ src, int ca, const SplitKernel& B, int cb,
                                            const int32_t* __restrict__ nbr, int64_t n_pos, int K, int64_t p, int n) {
   float acc = 0.f;
@@ -107,10 +122,6 @@ __device__ __forceinline__ float plain_dot(const float* __restrict__ src, int ca
       acc = fmaf(src[(int64_t)r * ca + k], B.transposed ? B.W[(sw * ca + k) * cb + n] : B.W[(sw * cb + n) * ca + k], acc);
   }
   return acc;
-}
-__device__ __forceinline__ bool doubtful(float v) {
-  const float a = fabsf(v);
-  return !(a <= 3.0e38f) || (a > 0.f && a < 7.9e-31f);  // 2^-100
 }
 
 // Tile of BM = 64 MR output rows x 16 NB columns.  Row group wm = w % 4 (MR 16-row blocks), column
@@ -474,18 +485,31 @@ size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   return shape_bytes(split_shape(n_src, ca, cb, n_pos, K), n_src, ca, cb, K);
 }
 
+int64_t split_row_bytes(int ca) { return (int64_t)chunks32(ca) * 192; }
+
+int split_rows(const float* x, int64_t nx, int cx, uint16_t* x3, const float* y, int64_t ny, int cy, uint16_t* y3,
+               hipStream_t st) {
+  const unsigned xb = cdiv(nx * 4 * chunks32(cx), 256), yb = cdiv(ny * 4 * chunks32(cy), 256);
+  if (xb + yb == 0) return SSCONV_OK;
+  split_rows_kernel<<<xb + yb, 256, 0, st>>>(x, nx, cx, xb, x3, y, ny, cy, y3);
+  SSC_HIP(hipGetLastError());
+  return SSCONV_OK;
+}
+
 int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, int cb, const int32_t* nbr,
-                 int64_t n_pos, int K, float* out, hipStream_t st, CallScratch* sc) {
+                 int64_t n_pos, int K, float* out, hipStream_t st, CallScratch* sc, const uint16_t* rows3) {
   if (n_pos == 0) return SSCONV_OK;
   const SplitShape s = split_shape(n_src, ca, cb, n_pos, K);
   char* ws = nullptr;
-  SSC_TRY(scratch_take(sc, (void**)&ws, shape_bytes(s, n_src, ca, cb, K), st));
-  uint16_t* A3 = (uint16_t*)ws;
-  uint16_t* B3 = (uint16_t*)(ws + a3_bytes(n_src, ca));
-  float* part = (float*)(ws + a3_bytes(n_src, ca) + b3_bytes(ca, cb, K));
-  const unsigned row_blocks = cdiv(n_src * 4 * chunks32(ca), 256);
+  const size_t a3 = rows3 ? 0 : a3_bytes(n_src, ca);
+  SSC_TRY(scratch_take(sc, (void**)&ws, a3 + b3_bytes(ca, cb, K) + part_bytes(s, K), st));
+  uint16_t* const split = (uint16_t*)ws;
+  const uint16_t* A3 = rows3 ? rows3 : split;
+  uint16_t* B3 = (uint16_t*)(ws + a3);
+  float* part = (float*)(ws + a3 + b3_bytes(ca, cb, K));
+  const unsigned row_blocks = rows3 ? 0 : cdiv(n_src * 4 * chunks32(ca), 256);
   const unsigned b_blocks = cdiv((int64_t)K * (pad_k(ca) / 8) * pad16(cb), 256);
-  split_operands<<<row_blocks + b_blocks, 256, 0, st>>>(src, n_src, ca, row_blocks, B, K, cb, A3, B3);
+  split_operands<<<row_blocks + b_blocks, 256, 0, st>>>(src, n_src, ca, row_blocks, B, K, cb, split, B3);
   int rc = hipGetLastError() == hipSuccess ? SSCONV_OK : fail(SSCONV_E_HIP, "operand split launch failed");
   const int64_t ab = (int64_t)n_src * chunks32(ca) * 192;
 #define SSG_GO(NB_, MR_) rc = launch<NB_, MR_>(s, A3, ab, ca, B3, cb, nbr, n_pos, K, part, src, B, out, st)

@@ -29,6 +29,7 @@
 #include <utility>
 #include <vector>
 
+#include "gather_tile.hpp"
 #include "kgrad_mfma.hpp"
 #include "lds_dma.hpp"
 
@@ -102,13 +103,6 @@ __device__ __forceinline__ void dma16_buf_q(int q, __amdgpu_buffer_rsrc_t rsrc, 
     case 5: dma16_buf<80>(rsrc, off, lds); break;
     default: dma16_buf<96>(rsrc, off, lds); break;
   }
-}
-
-// Workgroups are dispatched round-robin over the 8 XCDs: launch index i runs on XCD i % 8, which
-// takes slot positions (i % 8) * ceil(n / 8) + i / 8, a contiguous range per XCD.
-__device__ __forceinline__ int xcd_slot(int i, int n) {
-  const int x = i & 7, j = i >> 3, q = n >> 3, r = n & 7;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
 }
 
 __device__ __forceinline__ s4 tr_read(uint32_t lds) {
@@ -341,7 +335,7 @@ __global__ __launch_bounds__(256) void kgrad_bf16_kernel(const uint16_t* __restr
 // per unit.
 template <int VEC>
 __global__ __launch_bounds__(256) void reduce_units_kernel(const float* __restrict__ part, KgradUnits units, int cin,
-                                                           int cout, FieldTab fout, FieldTab fin,
+                                                           int cout, FieldTab fout, FieldTab fin, PlainGrad plain,
                                                            float* __restrict__ dW) {
   const int e = (blockIdx.x * blockDim.x + threadIdx.x) * VEC;
   const int s = blockIdx.y;
@@ -372,17 +366,27 @@ __global__ __launch_bounds__(256) void reduce_units_kernel(const float* __restri
       for (int k = 0; k < VEC; ++k) acc[k] += u + j < u1 ? v[j][k] : 0.f;
   }
   const int o = e / cin;
+  if (plain.pairs) {
+#pragma unroll
+    for (int k = 0; k < VEC; ++k)
+      if (doubtful(acc[k])) {
+        float a = 0.f;
+        for (int64_t p = plain.pair_off[s]; p < plain.pair_off[s + 1]; ++p)
+          a = fmaf(plain.grad_out[(int64_t)plain.pairs[p].x * cout + o], plain.feats[(int64_t)plain.pairs[p].y * cin + e + k - o * cin], a);
+        acc[k] = a;
+      }
+  }
 #pragma unroll
   for (int k = 0; k < VEC; ++k) dW[dw_block_pos(fout, fin, units.K, cin, s, o, e + k - o * cin)] = acc[k];
 }
 
 }  // namespace
 
-KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, bool ordered) {
+KgradUnits kgrad_units(const ssconv_rulebook* rb, int want) {
   KgradUnits u;
   u.K = rb->K;
   const int K = rb->K;
-  const int cap = ordered ? kKgradMaxUnits : kKgradMaxUnitsF32;
+  const int cap = kKgradMaxUnitsF32;
   int64_t total = 0;
   for (int s = 0; s < K; ++s) total += rb->pair_off[s + 1] - rb->pair_off[s];
   want = std::min(std::max(want, K), cap);
@@ -411,26 +415,17 @@ KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, bool ordered) {
   u.uoff[0] = 0;
   for (int s = 0; s < K; ++s) u.uoff[s + 1] = u.uoff[s] + n[s];
   u.nunits = u.uoff[K];
-  if (!ordered) return u;
-  // launch order: by the centre of each unit's slice along R_s (pairs are sorted by output row),
-  // ties by offset -- a stable order, so the launch is deterministic
-  std::vector<std::pair<double, int>> key(u.nunits);
-  for (int s = 0; s < K; ++s)
-    for (int j = 0; j < n[s]; ++j) key[u.uoff[s] + j] = {(j + 0.5) / n[s], u.uoff[s] + j};
-  std::stable_sort(key.begin(), key.end(),
-                   [](const std::pair<double, int>& a, const std::pair<double, int>& b) { return a.first < b.first; });
-  for (int i = 0; i < u.nunits; ++i) u.order[i] = (uint16_t)key[i].second;
   return u;
 }
 
 int reduce_units(const float* part, const KgradUnits& units, int cin, int cout, const FieldTab& fout,
-                 const FieldTab& fin, float* dW, hipStream_t st) {
+                 const FieldTab& fin, float* dW, hipStream_t st, const PlainGrad& plain) {
   const int64_t n = (int64_t)cin * cout;
   if (n == 0 || units.K == 0) return SSCONV_OK;
   if (cin % 4 == 0)
-    reduce_units_kernel<4><<<dim3(cdiv(n / 4, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, dW);
+    reduce_units_kernel<4><<<dim3(cdiv(n / 4, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, plain, dW);
   else
-    reduce_units_kernel<1><<<dim3(cdiv(n, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, dW);
+    reduce_units_kernel<1><<<dim3(cdiv(n, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, plain, dW);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
 }

@@ -18,24 +18,21 @@ inline bool kgrad_supported(ssconv_dtype dt, int cin, int cout) {
 
 KgradPlan kgrad_plan(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout);
 
-// Work units of the bf16 kernel gradient: offset s owns units uoff[s] .. uoff[s+1]-1, which cut
-// its pair list R_s into near-equal slices (passed to the kernels by value).
-// Units are launched in `order`: sorted by the position of their slice along the output rows
-// and handed out XCD-contiguously, so the units of all offsets over one stretch of rows run on
-// one XCD together and share its L2 for the gathered rows.
+// Work units of the kernel gradient: offset s owns units uoff[s] .. uoff[s+1]-1, which cut its pair list R_s
+// into near-equal slices (passed to the kernels by value).
 constexpr int kKgradMaxK = 125;  // ksize <= 5
-constexpr int kKgradMaxUnits = 512;      // bf16 (launch order recorded)
+constexpr int kKgradMaxUnits = 512;      // bf16 (launch order recorded for the kernel in columns)
 constexpr int kKgradMaxUnitsF32 = 4096;  // fp32 (one wavefront per unit and tile)
 struct KgradUnits {
   int K = 0, nunits = 0;
+  int even = 0;  // > 0: every offset has this many units, launched slice by slice
   int uoff[kKgradMaxK + 1] = {};
   uint16_t order[kKgradMaxUnits] = {};
 };
 
-// Units for the rule book: about `want` in total (at least one per offset, at most
-// kKgradMaxUnits when `ordered`, else kKgradMaxUnitsF32), distributed over the offsets in
-// proportion to their pair counts (largest remainders); `ordered` also records the launch order.
-KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, bool ordered);
+// Units of the fp32 ring kernel: about `want` in total (at least one per offset, at most kKgradMaxUnitsF32),
+// distributed over the offsets in proportion to their pair counts (largest remainders).
+KgradUnits kgrad_units(const ssconv_rulebook* rb, int want);
 
 // fp32 kernel gradient over work units (per-wavefront LDS ring): usable when every row offset
 // fits 31 bits; the unit count that fills one round of wavefront slots.
@@ -54,8 +51,15 @@ int kgrad_bf16(const void* grad_out, int64_t n_out, const void* feats, int64_t n
 
 // dW[s][:] = sum over the units of offset s of part[u][:] (n = cout * cin per unit), fixed order.
 // dW (field-pair-blocked, dw_block_pos) from the unit partials, each offset's in unit order.
+// With plain.pairs given (partials from split fp32 rows), a sum that the parts cannot carry is computed
+// again from grad_out and feats by plain fp32 multiply-adds.
+struct PlainGrad {
+  const float *grad_out = nullptr, *feats = nullptr;
+  const int2* pairs = nullptr;
+  const int64_t* pair_off = nullptr;
+};
 int reduce_units(const float* part, const KgradUnits& units, int cin, int cout, const FieldTab& fout,
-                 const FieldTab& fin, float* dW, hipStream_t st);
+                 const FieldTab& fin, float* dW, hipStream_t st, const PlainGrad& plain = PlainGrad());
 
 // part[split][s][o][i] (fp32) = sum over the split's slice of R_s of grad_out[x][o] feats[y][i].
 int kgrad_partials(const void* grad_out, const void* feats, ssconv_dtype dt, int cin, int cout,

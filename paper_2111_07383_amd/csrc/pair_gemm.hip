@@ -252,19 +252,30 @@ bool pair_path_supported(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int
          rb->n_pairs < ((int64_t)1 << 31) && (int64_t)rb->n_pairs * cb < ((int64_t)1 << 40);
 }
 
-// Cost model, fitted to measured layers (MI355X): the output-stationary kernel does the products of
-// every destination row at every offset, present or not (a tile holds nearly every offset), at ~185
-// TFLOP/s, plus ~20 us; this path does the useful products at ~80 TFLOP/s or, mostly, moves Y (written
-// and read) and the gathered rows, 2.6 ps per pair and column and 1.05 ps per pair and channel, plus ~30
-// us of launches.  60 -> 120 channels, 3x3x3: 99k pairs on 50k rows 69 us against 130, 612k on 87k 245
-// against 220, 1.87M on 160k 711 against 363; 5x5x5: 1.68M on 87k 686 against 818, 1.96M on 50k 750
-// against 421.  Kernel-selection override 9 forces it, 10 forbids it.
-bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst) {
+// Cost models.  Forward, against the fp32 MFMA kernel (measured rates on MI355X): the output-stationary
+// kernel executes about pairs / density rows of MFMA work at ~100 TFLOP/s, density = pairs / (destination
+// rows x offsets) (a tile of 128 rows holds nearly every offset, so its zero rows follow the density);
+// this path does the useful products at ~80 TFLOP/s and moves Y (written, read) plus the gathered
+// rows at ~4 TB/s, plus ~8 us of launches.
+// Gradient, against the kernel on three bf16 parts, fitted to measured layers: that one does the products of
+// every destination row at every offset at ~185 TFLOP/s, plus ~20 us; this path mostly moves Y and the
+// gathered rows, 2.6 ps per pair and column and 1.05 ps per pair and channel, plus ~30 us of launches (120 ->
+// 60 channels, 3x3x3: 90k pairs on 29k rows 52 us against 87, 612k on 87k 180 against 212, 1.87M on 160k 538
+// against 399; 5x5x5: 1.68M on 87k 533 against 786, 1.96M on 50k 578 against 481).
+// Kernel-selection override 9 forces it, 10 forbids it.
+bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst, bool forward) {
   if (!pair_path_supported(rb, dt, ca, cb) || n_dst <= 0) return false;
   const int64_t v = debug_gather_variant();
   if (v == 9) return true;
   if (v != 0 && v != 11 && v != 12) return false;  // 10 and the others forbid it (11, 12 concern other kernels)
   const double P = (double)rb->n_pairs, prod = 2.0 * ca * cb;
+  if (forward) {
+    const double density = std::min(1.0, P / ((double)n_dst * rb->K));
+    const double flops = P * prod;
+    const double t_os = flops / density / 100e12;
+    const double t_pair = flops / 80e12 + P * (8.0 * cb + 4.0 * ca) / 4e12 + 8e-6;
+    return t_pair < 0.85 * t_os;
+  }
   const double t_os = (double)n_dst * rb->K * prod / 185e12 + 20e-6;
   const double t_pair = P * std::max(prod / 80e12, 2.6e-12 * cb + 1.05e-12 * ca) + 30e-6;
   return t_pair < t_os;

@@ -53,7 +53,7 @@ def test_against_fp64(n, ksize, stride, ca, cb):
     x = torch.randn((rb.n_in, ca), device="cuda", generator=g)
     W = torch.randn((ksize ** 3, cb, ca), device="cuda", generator=g)
     dy = torch.randn((rb.n_out, cb), device="cuda", generator=g)
-    ss.debug_set(3, 10)   # never the pair-list path
+    ss.debug_set(3, 13)   # this kernel at every size, never the pair-list path
     try:
         y = ss.forward(x, rb, W)
         dx, _ = ss.backward(x, dy, rb, W, need_coeffs=False)
@@ -78,7 +78,7 @@ def test_values_the_parts_cannot_carry(n):
     x[200:240] = 0
     W[:, 3] *= 1e-3
     x[210] = 1e-36 * torch.randn(40, device="cuda", generator=g)
-    ss.debug_set(3, 10)
+    ss.debug_set(3, 13)
     try:
         y = ss.forward(x, rb, W)
     finally:

@@ -1,0 +1,90 @@
+"""The kernel gradient on the bf16 matrix cores (bf16 rows, or fp32 rows as three bf16 parts) and the bf16
+gather at channel counts that are not multiples of 8, through the coefficient and feature gradients of
+layers of scalar fields, against fp64.
+
+Channel counts sit at the edges of its tiles (32, 64, 128 and 224 channels, more than one tile) and of the
+padding of rows; pair counts at the edges of its 32-pair chunks and 512-pair blocks."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2111_07383_amd as ss
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(n, ksize, ci, co, dtype, seed=0):
+    rng = np.random.default_rng(seed)
+    cells = np.sort(rng.permutation(20 ** 3)[:n])
+    xyz = np.stack(np.unravel_index(cells, (20,) * 3), 1)
+    coords = torch.from_numpy(np.concatenate([np.zeros((n, 1)), xyz], 1).astype(np.int32)).cuda()
+    rb = ss.build_rulebook(coords, 20, ksize)
+    desc = ss.basis_desc(((0, ci),), ((0, co),), ksize, tuple(float(m) for m in range(ksize // 2 + 1)))
+    g = torch.Generator("cuda").manual_seed(seed)
+    x = torch.randn((n, ci), device="cuda", generator=g).to(dtype)
+    dy = torch.randn((n, co), device="cuda", generator=g).to(dtype)
+    W = torch.randn((ksize ** 3, co, ci), device="cuda", generator=g).to(dtype)
+    return rb, desc, torch.from_numpy(ss.basis_build(desc)).cuda(), x, dy, W
+
+
+def _coeff_grad(rb, basis, nq, x, dy):
+    """(sum, sum of magnitudes) of the coefficient gradient of a scalar layer in fp64."""
+    nbr, K = rb.neighbours(), rb.K
+    B = basis.double().reshape(nq, K)
+    out = torch.zeros((dy.shape[1], x.shape[1], nq), dtype=torch.float64, device=x.device)
+    mag = torch.zeros_like(out)
+    for s in range(K):
+        o = (nbr[s] >= 0).nonzero()[:, 0]
+        a, b = dy[o].double(), x[nbr[s][o].long()].double()
+        out += (a.T @ b)[:, :, None] * B[:, s]
+        mag += (a.abs().T @ b.abs())[:, :, None] * B[:, s].abs()
+    return out.reshape(-1), mag.reshape(-1)
+
+
+# (fp32 layers take the tile kernel from six pairs per row on, the fp32 ring kernel below)
+CASES = [(1, 3, 1, 1), (33, 3, 5, 8), (200, 3, 40, 33), (7900, 3, 64, 65), (8000, 3, 71, 45), (2000, 5, 60, 128),
+         (3000, 3, 129, 100), (7950, 3, 208, 225), (8000, 3, 2, 4)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,ksize,ci,co", CASES)
+def test_coefficient_gradient(n, ksize, ci, co, dtype):
+    """|error| <= (pairs / 32 + K + 64) 2^-24 of the sum of magnitudes: one rounding per 32 pairs and per
+    offset and partial; products are exact (bf16) or kept to 2^-24 (three parts)."""
+    rb, desc, basis, x, dy, W = _layer(n, ksize, ci, co, dtype)
+    nq = ksize // 2 + 1
+    gc = ss.backward(x, dy, rb, W, desc, basis, need_feats=False)[1]
+    assert torch.equal(gc, ss.backward(x, dy, rb, W, desc, basis, need_feats=False)[1])
+    want, mag = _coeff_grad(rb, basis, nq, x, dy)
+    bound = (rb.pair_counts.max() / 32 + rb.K + 64) * 2.0 ** -24 * mag + 1e-30
+    assert ((gc.double() - want).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("n,ksize,ci,co", CASES)
+def test_bf16_ragged_forward_and_feature_gradient(n, ksize, ci, co):
+    """bf16 outputs within one rounding (2^-8) of the value and the fp32 sum's error of the magnitudes."""
+    rb, _, _, x, dy, W = _layer(n, ksize, ci, co, torch.bfloat16)
+    nbr = rb.neighbours()
+    y = ss.forward(x, rb, W)
+    dx = ss.backward(x, dy, rb, W, need_coeffs=False)[0]
+    for got, a, b in ((y, x, W), (dx, dy, W.flip(0).transpose(1, 2).contiguous())):
+        want = torch.zeros((n, b.shape[1]), dtype=torch.float64, device="cuda")
+        mag = torch.zeros_like(want)
+        for s in range(rb.K):
+            o = (nbr[s] >= 0).nonzero()[:, 0]
+            r, k = a.double()[nbr[s][o].long()], b[s].double().T
+            want[o] += r @ k
+            mag[o] += r.abs() @ k.abs()
+        assert ((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -20 * mag).all()
+
+
+def test_values_the_parts_cannot_carry():
+    rb, desc, basis, x, dy, W = _layer(7900, 3, 24, 40, torch.float32)
+    dy *= 1e-3   # sums with the value past bf16's largest stay below fp32's
+    x[7, 3], x[90, 5], dy[11, 2] = float("inf"), 3.4e38, float("nan")
+    gc = ss.backward(x, dy, rb, W, desc, basis, need_feats=False)[1]
+    want = _coeff_grad(rb, basis, 2, x, dy)[0]
+    fine = torch.isfinite(want.float())
+    assert torch.equal(torch.isfinite(gc), fine)
+    assert torch.equal(torch.isnan(gc), torch.isnan(want))
+    assert fine.any() and not fine.all()
