@@ -136,12 +136,12 @@ __global__ __launch_bounds__(256) void bucket_sort_big_kernel(const int32_t* __r
   }
 }
 
-// Sorts every bucket: big must hold n_max + 1 int32 (n_max = the largest number of buckets);
+// Sorts every bucket: big must hold n_max + 1 int32 (n_max = the largest number of buckets), the
+// first of them zero;
 // tiny: most buckets hold at most 8 entries (eight buckets per wavefront).
 inline int sort_buckets(const int64_t* n_rows, int64_t n_rows_host, int64_t n_max, const int64_t* start,
                         const int32_t* cnt, int32_t* a, int32_t* big, bool tiny, hipStream_t st) {
   if (n_max <= 0) return SSCONV_OK;
-  SSC_HIP(hipMemsetAsync(big, 0, 4, st));
   if (tiny)
     bucket_sort_kernel<8><<<cdiv(n_max, 32), 256, 0, st>>>(n_rows, n_rows_host, start, cnt, a, big);
   else

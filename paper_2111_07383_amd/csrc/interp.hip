@@ -278,9 +278,10 @@ extern "C" int ssconv_interpolate_backward(ssconv_rulebook_t rb, const float* gr
   }
   const int64_t ne = m * 8;
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  const size_t o_w = up(ne * 4), o_cnt = o_w + up(ne * 4), o_fill = o_cnt + up(n * 4), o_start = o_fill + up(ne * 4);
+  const size_t o_w = up(ne * 4), o_cnt = o_w + up(ne * 4), o_big = o_cnt + up(n * 4);  // cnt, big: one fill
+  const size_t o_fill = o_big + up((n + 1) * 4), o_start = o_fill + up(ne * 4);
   const size_t o_ent = o_start + up(n * 8), o_tmp = o_ent + up(ne * 4);
-  const size_t o_big = o_tmp + up((size_t)(scan_tmp_elems(n) + 1) * 8), total = o_big + up((n + 1) * 4);
+  const size_t total = o_tmp + up((size_t)(scan_tmp_elems(n) + 1) * 8);
   char* ws = nullptr;
   SSC_TRY(dev_alloc((void**)&ws, total, stream));
   int32_t* rows = (int32_t*)ws;
@@ -292,7 +293,7 @@ extern "C" int ssconv_interpolate_backward(ssconv_rulebook_t rb, const float* gr
   int64_t* tmp = (int64_t*)(ws + o_tmp);
   int32_t* big = (int32_t*)(ws + o_big);
   auto run = [&]() -> int {
-    SSC_HIP(hipMemsetAsync(cnt, 0, (size_t)n * 4, stream));
+    SSC_HIP(hipMemsetAsync(cnt, 0, o_big - o_cnt + 256, stream));
     launch_corners(rb, points, batch, m, origin, voxel, rows, wts, cnt, slot, stream);
     SSC_TRY(exclusive_scan(cnt, n, start, tmp + scan_tmp_elems(n), tmp, stream));
     interp_fill_kernel<<<cdiv(ne, 256), 256, 0, stream>>>(rows, ne, start, slot, ent);

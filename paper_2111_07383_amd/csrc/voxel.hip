@@ -93,21 +93,57 @@ __global__ void vox_fill_kernel(const int32_t* __restrict__ point_row, int64_t n
   idx[start[r] + slot[i]] = (int32_t)i;
 }
 
+// feats_out[r][c..c+V) = (sum over the sorted bucket of feats[i][c..c+V), in point order) / count
+// (V = 4 with 16-byte accesses when C % 4 == 0).  A bucket is a chain of index -> feature loads, so
+// kMeanAhead points are loaded before the first is used (past the bucket's end its last point
+// again, which leaves the sum alone), and the division is by a 32-bit width from a row that is the
+// same in all lanes.  Against one thread per channel and one load at a time: 158k sites of
+// 4 channels 18 -> 14 us, 38k sites of 104 channels 17 -> 9 us.
+constexpr int kMeanAhead = 4;
 
-// feats_out[r][c] = (sum over the sorted bucket of feats[i][c], in point order) / count; one
-// thread per (site, channel), so the threads of a site read its points' rows together.
-__global__ void vox_mean_kernel(const float* __restrict__ feats, int C, const int64_t* __restrict__ n_rows,
-                                const int64_t* __restrict__ start, const int32_t* __restrict__ cnt,
-                                const int32_t* __restrict__ idx, float* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t r = e / C;
-  if (r >= *n_rows) return;
-  const int c = (int)(e - r * C);
+template <int V>
+__global__ __launch_bounds__(256) void vox_mean_kernel(const float* __restrict__ feats, int C,
+                                                       const int64_t* __restrict__ n_rows,
+                                                       const int64_t* __restrict__ start,
+                                                       const int32_t* __restrict__ cnt,
+                                                       const int32_t* __restrict__ idx, float* __restrict__ out) {
+  const int64_t rows = *n_rows;
+  const uint32_t nv = (uint32_t)(C / V);
+  const int64_t e0 = (int64_t)blockIdx.x * 256, i0 = e0 / nv;
+  const uint32_t off = (uint32_t)(e0 - i0 * nv) + threadIdx.x, q0 = off / nv;
+  const int64_t r = i0 + q0;
+  if (r >= rows) return;
+  const int c = (int)(off - q0 * nv) * V;
   const int32_t* a = idx + start[r];
   const int m = cnt[r];
-  float s = 0.f;
-  for (int j = 0; j < m; ++j) s += feats[(int64_t)a[j] * C + c];
-  out[r * C + c] = s / (float)m;
+  float s[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) s[v] = 0.f;
+  for (int j = 0; j < m; j += kMeanAhead) {
+    float f[kMeanAhead][V];
+    int32_t i[kMeanAhead];
+#pragma unroll
+    for (int q = 0; q < kMeanAhead; ++q) i[q] = a[min(j + q, m - 1)];
+#pragma unroll
+    for (int q = 0; q < kMeanAhead; ++q) {
+      const float* p = feats + (int64_t)i[q] * C + c;
+      if constexpr (V == 4) {
+        const float4 x = *reinterpret_cast<const float4*>(p);
+        f[q][0] = x.x, f[q][1] = x.y, f[q][2] = x.z, f[q][3] = x.w;
+      } else {
+        f[q][0] = p[0];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kMeanAhead; ++q)
+#pragma unroll
+      for (int v = 0; v < V; ++v) s[v] = j + q < m ? s[v] + f[q][v] : s[v];
+  }
+  float* o = out + r * C + c;
+  if constexpr (V == 4)
+    *reinterpret_cast<float4*>(o) = make_float4(s[0] / (float)m, s[1] / (float)m, s[2] / (float)m, s[3] / (float)m);
+  else
+    o[0] = s[0] / (float)m;
 }
 
 }  // namespace
@@ -138,32 +174,33 @@ extern "C" int ssconv_voxelize(const float* points, const int32_t* batch, const 
   const hipStream_t st = stream;
   const int64_t nw = (nbits + 31) / 32;
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  const size_t o_bits = 0, o_woff = o_bits + up(nw * 4), o_stmp = o_woff + up(nw * 8);
-  const size_t o_key = o_stmp + up((size_t)(scan_tmp_elems(std::max<int64_t>(nw, n)) + 2) * 8);
-  const size_t o_row = o_key + up(n * 4), o_cnt = o_row + up(n * 4), o_fill = o_cnt + up(n * 4);
-  const size_t o_start = o_fill + up(n * 4), o_idx = o_start + up(n * 8), o_flags = o_idx + up(n * 4);
-  const size_t o_big = o_flags + 256, total_b = o_big + up((n + 1) * 4);
+  // what starts as zero lies together and is cleared by one fill: the bitmap, the counts, the site
+  // count and the flags behind it (read back in one copy), and the length of the big-bucket list.  Whole
+  // blocks of 256 bytes: a length that is not makes two launches of one fill
+  const size_t o_bits = 0, o_cnt = o_bits + up(nw * 4), o_head = o_cnt + up(n * 4), o_big = o_head + 256;
+  const size_t o_woff = o_big + up((n + 1) * 4), o_stmp = o_woff + up(nw * 8);
+  const size_t o_key = o_stmp + up((size_t)(scan_tmp_elems(std::max<int64_t>(nw, n)) + 1) * 8);
+  const size_t o_row = o_key + up(n * 4), o_fill = o_row + up(n * 4);
+  const size_t o_start = o_fill + up(n * 4), o_idx = o_start + up(n * 8), total_b = o_idx + up(n * 4);
   char* ws = nullptr;
   SSC_TRY(dev_alloc((void**)&ws, total_b, st));
   uint32_t* bits = (uint32_t*)(ws + o_bits);
   int64_t* woff = (int64_t*)(ws + o_woff);
   int64_t* stmp = (int64_t*)(ws + o_stmp);
-  int64_t* d_sites = stmp + scan_tmp_elems(std::max<int64_t>(nw, n));
-  int64_t* d_pts = d_sites + 1;
+  int64_t* d_pts = stmp + scan_tmp_elems(std::max<int64_t>(nw, n));
+  int64_t* d_sites = (int64_t*)(ws + o_head);
   uint32_t* key = (uint32_t*)(ws + o_key);
   int32_t* prow = point_row ? point_row : (int32_t*)(ws + o_row);
   int32_t* cnt = (int32_t*)(ws + o_cnt);
   int32_t* slot = (int32_t*)(ws + o_fill);  // each point's slot in its row's bucket
   int64_t* start = (int64_t*)(ws + o_start);
   int32_t* idx = (int32_t*)(ws + o_idx);
-  int* flags = (int*)(ws + o_flags);
+  int* flags = (int*)(d_sites + 1);
   int32_t* big = (int32_t*)(ws + o_big);
 
   int rc = SSCONV_OK;
   auto run = [&]() -> int {
-    SSC_HIP(hipMemsetAsync(bits, 0, (size_t)nw * 4, st));
-    SSC_HIP(hipMemsetAsync(cnt, 0, (size_t)n * 4, st));
-    SSC_HIP(hipMemsetAsync(flags, 0, 4, st));
+    SSC_HIP(hipMemsetAsync(ws, 0, o_big + 256, st));
     vox_cell_kernel<<<cdiv(n, 256), 256, 0, st>>>(points, batch, n, origin[0], origin[1], origin[2], voxel, grid[0],
                                                   grid[1], grid[2], nbatch, key, bits, flags);
     SSC_TRY(exclusive_scan_popc(bits, nw, woff, d_sites, stmp, st));
@@ -174,12 +211,16 @@ extern "C" int ssconv_voxelize(const float* points, const int32_t* batch, const 
       SSC_TRY(exclusive_scan(cnt, n, start, d_pts, stmp, st));
       vox_fill_kernel<<<cdiv(n, 256), 256, 0, st>>>(prow, n, start, slot, idx);
       SSC_TRY(sort_buckets(d_sites, 0, n, start, cnt, idx, big, true, st));
-      vox_mean_kernel<<<cdiv(n * channels, 256), 256, 0, st>>>(feats, channels, d_sites, start, cnt, idx, feats_out);
+      if (channels % 4 == 0 && aligned16(feats) && aligned16(feats_out))
+        vox_mean_kernel<4><<<cdiv(n * channels / 4, 256), 256, 0, st>>>(feats, channels, d_sites, start, cnt, idx,
+                                                                        feats_out);
+      else
+        vox_mean_kernel<1><<<cdiv(n * channels, 256), 256, 0, st>>>(feats, channels, d_sites, start, cnt, idx,
+                                                                    feats_out);
     }
     SSC_HIP(hipGetLastError());
     int64_t host[2] = {0, 0};
-    SSC_HIP(hipMemcpyAsync(&host[0], d_sites, 8, hipMemcpyDeviceToHost, st));
-    SSC_HIP(hipMemcpyAsync(&host[1], flags, 4, hipMemcpyDeviceToHost, st));
+    SSC_HIP(hipMemcpyAsync(host, d_sites, 16, hipMemcpyDeviceToHost, st));
     SSC_HIP(hipStreamSynchronize(st));
     if ((int)host[1] & kFlagBadBatch) return fail(SSCONV_E_BOUNDS, "a batch index lies outside [0, nbatch)");
     *n_sites = host[0];
