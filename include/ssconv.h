@@ -217,10 +217,13 @@ int ssconv_forward(const void* feats, ssconv_dtype dtype, int cin, ssconv_rulebo
  * partials, the pair-list path's buffers) is carved from one fixed region of
  * SSCONV_NOALLOC_SCRATCH_BYTES per device, built into the library and held by
  * every device the library runs on until the process ends.  Scratch use per
- * call: bf16 2*ksize^3*cin*cout bytes; fp32 nothing on the output-stationary
- * kernel (offset splits are reduced until their partials fit) and the
- * pair-list buffers only where they fit (otherwise the output-stationary
- * kernel runs: same sums, another order of the fp32 additions).
+ * call: bf16 the packed kernel (2*ksize^3*cin*cout bytes, channels padded to
+ * whole groups), padded rows where cin is not a multiple of 8, and the pieces
+ * of cut tiles; fp32 the split operands and pieces of large layers, nothing on
+ * the fp32 matrix cores' kernel (offset splits are reduced until their partials
+ * fit) and the pair-list buffers only where they fit.  A kernel whose scratch
+ * does not fit gives way to one that needs less (same sums, another order of
+ * the fp32 additions).
  * Errors: as ssconv_forward, plus SSCONV_E_INVALID when the call would need
  * more scratch than the region holds (bf16 with 2*ksize^3*cin*cout above it).
  * Every call on one device uses that device's one region: calls that overlap
@@ -279,10 +282,10 @@ int ssconv_norm_backward(const ssconv_fields* fields /*host*/, const void* x, co
  * ssconv_forward followed by ssconv_norm_forward(fields_out, y, eps, z) compute
  * them: y is the same (bit for bit), z agrees up to the order of the fp64
  * statistics sums.  The Norm's per-channel sums come out of the kernel that
- * writes y (per row tile of the output-stationary kernels, per row block of the
+ * writes y (per row tile of the fp32 matrix cores' kernel, per row block of the
  * pair-list and offset-split reduces), so y is not read back before the
- * elementwise Norm step; the generic fallback kernel leaves none, and a
- * separate statistics pass then runs.  cout = channels of fields_out (1..1024);
+ * elementwise Norm step; the other kernels leave none, and a separate
+ * statistics pass then runs.  cout = channels of fields_out (1..1024);
  * feats [n_in, cin], W [ksize^3, cout, cin], y and z [n_out, cout], all in
  * `dtype`, 16-byte aligned.  z may alias y (y is then overwritten by z); y
  * stays the input of ssconv_norm_backward.  n_out = 0 is a no-op.  Temporary

@@ -410,10 +410,10 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
 }
 
 // The convolution with the Norm of its output (Sec. 3.3, Eq. 11).  The kernel that writes y also
-// leaves its per-channel sums (the output-stationary kernels per row tile, the pair-list and
+// leaves its per-channel sums (the fp32 output-stationary kernel per row tile, the pair-list and
 // offset-split reduces per row block), so the Norm needs no pass of its own over y before the
-// elementwise one; the other paths (the generic fallback kernel, an input set without rows) leave
-// none and the separate statistics pass runs instead.
+// elementwise one; the other paths (the bf16 and split gathers, the generic fallback kernel, an input
+// set without rows) leave none and the separate statistics pass runs instead.
 int conv_forward_norm(const void* feats, ssconv_dtype dt, int cin, const ssconv_rulebook* rb, const void* W, int cout,
                       const FieldTab& f, double eps, void* y, void* z, hipStream_t st) {
   const int64_t n = rb->n_out;

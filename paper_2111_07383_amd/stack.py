@@ -132,7 +132,7 @@ class DownBlock:
     """The paper's downsampling block: a stride-1 submanifold SS-Conv, steerable Norm (Eq. 11)
     over every output field (gate channels included), the gated nonlinearity (Eq. 12), then
     2x2x2 average pooling (the footnote of Sec. 3.1).  The convolution and its Norm are one call
-    (``forward_norm``: the kernel that writes the convolution output also sums its statistics).
+    (``forward_norm``: in fp32 the kernel that writes the convolution output also sums its statistics).
     Rule books are rebuilt every call."""
     state: LayerState
     dtype: torch.dtype = torch.float32
