@@ -37,27 +37,34 @@ def log(msg):
 # HBM traffic of the gather-GEMM kernel from rocprofv3 counter runs
 # ---------------------------------------------------------------------------
 CSRC = os.path.join(ROOT, "paper_2111_07383_amd", "csrc")
-# kernel symbol and the source files that decide its device code, per compute dtype
-GATHER_KERNEL = {"bf16": ("gather_bf16_kernel", ["gather_bf16.hip", "lds_dma.hpp", "gather_mfma.hpp", "common.hpp"]),
-                 "f32": ("gather_mfma_kernel", ["gather_mfma.hip", "lds_dma.hpp", "gather_mfma.hpp", "common.hpp"])}
+# kernel symbol and the source files that decide its device code, per compute dtype; "f32 large": the 64^3 5x5x5
+# layer, whose fp32 forward is past 2^35 multiply-adds and takes the kernel on the bf16 matrix cores
+GATHER_KERNEL = {"bf16": ("gather_bf16_kernel", ["gather_bf16.hip", "gather_tile.hpp", "lds_dma.hpp", "common.hpp"]),
+                 "f32": ("gather_mfma_kernel", ["gather_mfma.hip", "lds_dma.hpp", "gather_mfma.hpp", "common.hpp"]),
+                 "f32 large": ("gather_split_kernel", ["gather_split.hip", "gather_split.hpp", "gather_tile.hpp",
+                                                       "lds_dma.hpp", "common.hpp"])}
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
 
-def kernel_name(dtype):
-    return GATHER_KERNEL[dtype][0]
+def gather_key(spec):
+    return "f32 large" if spec.index == 2 else spec.dtype
 
 
-def kernel_source_hash(dtype):
+def kernel_name(spec):
+    return GATHER_KERNEL[gather_key(spec)][0]
+
+
+def kernel_source_hash(spec):
     import hashlib
     h = hashlib.sha256()
-    for f in GATHER_KERNEL[dtype][1]:
+    for f in GATHER_KERNEL[gather_key(spec)][1]:
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(f.encode() + b"\0" + fh.read())
     return h.hexdigest()[:16]
 
 
 def traffic_path(spec):
-    return os.path.join(ROOT, "profiles", f"traffic_{kernel_name(spec.dtype)}_{spec.name}.txt")
+    return os.path.join(ROOT, "profiles", f"traffic_{kernel_name(spec)}_{spec.name}.txt")
 
 
 def traffic_from_summary(spec):
@@ -71,7 +78,7 @@ def traffic_from_summary(spec):
         if ":" in line and not line.startswith(" "):
             k, v = line.split(":", 1)
             kv[k.strip()] = v.strip()
-    if kv.get("source_sha256") != kernel_source_hash(spec.dtype):
+    if kv.get("source_sha256") != kernel_source_hash(spec):
         return None, f"{os.path.relpath(path, ROOT)} predates the current kernel source"
     return float(kv["traffic_bytes_per_launch"]), os.path.relpath(path, ROOT)
 
@@ -104,7 +111,7 @@ def write_traffic_summary(args):
     spec = CONFIGS[args.config]
     d = args.traffic_summary
     dc = args.copy_pmc or d
-    kname = kernel_name(spec.dtype)
+    kname = kernel_name(spec)
     mb = args.copy_mb or 256
     fetch = _per_dispatch(_counter_rows(os.path.join(d, "fetch")), kname, "FETCH_SIZE")
     write = _per_dispatch(_counter_rows(os.path.join(d, "write")), kname, "WRITE_SIZE")
@@ -129,7 +136,7 @@ def write_traffic_summary(args):
              "commands (from the repository root, TMPDIR=/tmp, each rocprofv3 run under timeout -s KILL 120):"]
     lines += [f"  {c}" for c in cmds]
     lines += [f"kernel: {kname}",
-              f"source_sha256: {kernel_source_hash(spec.dtype)}",
+              f"source_sha256: {kernel_source_hash(spec)}",
               f"dispatches: {len(fetch)} (FETCH_SIZE run), {len(write)} (WRITE_SIZE run)",
               f"fetch_kib_per_dispatch: {fk:.1f}",
               f"write_kib_per_dispatch: {wk:.1f}",
@@ -945,7 +952,7 @@ def write_stats_summary(args):
     for r in stats[:18]:
         out.append(f"{short(r['Name']):70s} {r['Calls']:>6s} {float(r['AverageNs']) / 1e3:9.1f} "
                    f"{float(r['MinNs']) / 1e3:9.1f} {float(r['MaxNs']) / 1e3:9.1f} {float(r['Percentage']):6.1f}")
-    kname = kernel_name(spec.dtype)
+    kname = kernel_name(spec)
     g = sorted((int(t["Start_Timestamp"]), int(t["End_Timestamp"])) for t in trace if kname in t["Kernel_Name"])
     if g:
         durs = [(e - b) / 1e3 for b, e in g]
@@ -1111,7 +1118,7 @@ def measure(args, i, steps, warmup, dev):
     flops_launch = flops_step / launches_step
     achieved = flops_step * steps / (kern_ms / 1e3) / 1e12
     traffic, tsrc = traffic_from_summary(spec)
-    out["roofline"] = {"kernel": kernel_name(spec.dtype), "bound": "mfma", "achieved": achieved,
+    out["roofline"] = {"kernel": kernel_name(spec), "bound": "mfma", "achieved": achieved,
                        "peak": PEAK[spec.dtype], "unit": "TFLOP/s", "frac": achieved / PEAK[spec.dtype],
                        "traffic": traffic, "traffic_source": tsrc, "avg_launch_ms": avg_ms,
                        "launches_timed": n_timed, "algorithmic_flops_per_launch": flops_launch,
