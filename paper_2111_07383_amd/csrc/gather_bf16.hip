@@ -108,7 +108,7 @@ __device__ __forceinline__ void gather_bf16_body(const uint16_t* __restrict__ sr
       const int n_act = load_panel<BM>(nbr, n_pos, p0, s0, ns, (uint32_t)row_bytes, rows, bmask, act, n_act_p);
       const int nchunk = order.chunks(n_act);
       if (nchunk == 0) continue;
-      chunk_table(order, n_act, nchunk, act, ns, BM * 4, s0, cg, (uint32_t)cbp * 16u, tab);
+      chunk_table(order, n_act, nchunk, act, ns, BM * 4, s0, pad8(ca), cg, (uint32_t)cbp * 16u, tab);
 
       // position of the chunk being fetched (rows, kappa) and the table entry of the one after it
       uint32_t arow[NRB], bpos;

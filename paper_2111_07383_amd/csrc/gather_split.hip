@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
       const int n_act = load_panel<BM>(nbr, n_pos, p0, s0, ns, row_bytes, rows, bmask, act, n_act_p);
       const int nchunk = order.chunks(n_act);
       if (nchunk == 0) continue;
-      chunk_table(order, n_act, nchunk, act, ns, BM * 4, s0, cg, (uint32_t)cbp * 48u, tab);
+      chunk_table(order, n_act, nchunk, act, ns, BM * 4, s0, pad8(ca), cg, (uint32_t)cbp * 48u, tab);
 
       // position of the chunk being fetched (rows, kappa) and the table entry of the one after it
       uint32_t arow[NRB], bbase;

@@ -142,19 +142,24 @@ struct ChunkOrder {
 // {byte offset of the offset's row table | channel / 8 << 18, byte offset of the kappa group}; chunks past
 // the last are absent rows.  (Positions kept in registers and advanced by branches took 350 instructions a
 // chunk of 28 MFMAs, which bound the bf16 kernel.)
+// A lane group past the channels (c8: the channels in whole groups of 8; a rest of 24 is padded) or past the
+// last offset takes absent rows too: rows read in place go on with the next row there, and an infinity or NaN
+// of that row is not undone by kappa's zeros.  Its kappa is the padding, or a group of an offset that the tile
+// holds anyway.
 constexpr int kChunkAhead = 8;  // absent entries past the last chunk
 __device__ __forceinline__ void chunk_table(const ChunkOrder& o, int n_act, int nchunk, const uint8_t* act, int absent,
-                                            int bm4, int s0, int cg, uint32_t group_bytes, uint2* tab) {
+                                            int bm4, int s0, int c8, int cg, uint32_t group_bytes, uint2* tab) {
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   for (int i = tid; i < 4 * (nchunk + kChunkAhead); i += kTileThreads) {
     const int c = i >> 2, g = i & 3;
-    int slot = n_act, ch = 0;
-    if (c < nchunk) o.at(c, g, n_act, &slot, &ch);
     uint2 e = make_uint2((uint32_t)(absent * bm4), 0u);
-    if (slot < n_act) {
-      const int j = act[slot];
-      e = make_uint2((uint32_t)(j * bm4) | (uint32_t)(ch >> 3) << 18, (uint32_t)((s0 + j) * cg + (ch >> 3)) * group_bytes);
+    if (c < nchunk) {
+      int slot, ch;
+      o.at(c, g, n_act, &slot, &ch);
+      const int j = act[slot < n_act ? slot : n_act - 1];
+      if (slot < n_act && ch < c8) e.x = (uint32_t)(j * bm4) | (uint32_t)(ch >> 3) << 18;
+      e.y = (uint32_t)((s0 + j) * cg + (ch >> 3)) * group_bytes;
     }
     tab[i] = e;
   }
