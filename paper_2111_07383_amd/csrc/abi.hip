@@ -145,24 +145,12 @@ extern "C" int ssconv_backward(const void* feats, const void* grad_out, ssconv_d
   // Kernel-selection override 11 switches both forks off.
   hipStream_t dw_stream = stream;
   const bool both = grad_feats && grad_coeffs && rb->n_out > 0 && debug_gather_variant() != 11;
-  const bool fork = both && L.pair_feats;
-  const bool fork_tail = both && !L.pair_feats && rb->n_in > 0 && dtype == SSCONV_F32;
+  const bool fork = both && L.pair_feats();
+  const bool fork_tail = both && !L.pair_feats() && rb->n_in > 0 && dtype == SSCONV_F32;
   bool need_join = fork;
   BwdRows rows;
-  if (grad_coeffs) {
-    const int rr = bwd_rows(feats, grad_out, dtype, cin, cout, rb, &rows, stream);
-    if (rr != SSCONV_OK) {
-      if (rows.ws) dev_free(rows.ws, stream);
-      return rr;
-    }
-  }
-  if (fork) {
-    const int fr = aux_fork(stream, &dw_stream);
-    if (fr != SSCONV_OK) {
-      if (rows.ws) dev_free(rows.ws, stream);
-      return fr;
-    }
-  }
+  if (grad_coeffs) SSC_TRY(bwd_rows(feats, grad_out, dtype, cin, cout, rb, (char*)workspace, L, &rows, stream));
+  if (fork) SSC_TRY(aux_fork(stream, &dw_stream));
   int rc = SSCONV_OK;
   if (grad_coeffs) {
     float* dW = nullptr;
@@ -187,6 +175,5 @@ extern "C" int ssconv_backward(const void* feats, const void* grad_out, ssconv_d
     const int jr = aux_join(stream, dw_stream);  // always joined, so nothing stays pending on the side stream
     if (rc == SSCONV_OK) rc = jr;
   }
-  if (rows.ws) dev_free(rows.ws, stream);
   return rc;
 }

@@ -492,12 +492,11 @@ static KgradUnits plan_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin
 }
 
 int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
-             BwdRows* r, hipStream_t st) {
+             char* ws, const BwdLayout& L, BwdRows* r, hipStream_t st) {
   if (!use_kgrad_tiles(rb, dt, cin, cout)) return SSCONV_OK;
   const size_t gb = kgrad_copy_bytes(dt, rb->n_out, cout), fb = kgrad_copy_bytes(dt, rb->n_in, cin);
-  if (gb + fb > 0) SSC_TRY(dev_alloc(&r->ws, gb + fb, st));
-  uint16_t* gc = gb ? (uint16_t*)r->ws : nullptr;
-  uint16_t* fc = fb ? (uint16_t*)((char*)r->ws + gb) : nullptr;
+  uint16_t* gc = gb ? (uint16_t*)(ws + L.rows) : nullptr;
+  uint16_t* fc = fb ? (uint16_t*)(ws + L.rows + gb) : nullptr;
   const int64_t ng = gc ? rb->n_out : 0, nf = fc ? rb->n_in : 0;
   int rc;
   if (dt == SSCONV_F32)
@@ -523,13 +522,31 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
     nparts = (size_t)L.nsplit * K;
   }
   size_t o = 0;
-  L.pair_feats = dt == SSCONV_F32 && rb->n_in > 0 && pair_path_wins(rb, dt, cout, cin, rb->n_in, false);
+  if (rb->n_in > 0 && rb->n_out > 0) {
+    if (dt == SSCONV_F32 && pair_path_wins(rb, dt, cout, cin, rb->n_in, false))
+      L.feats = BwdLayout::kPair;
+    else if (dt == SSCONV_F32 && use_split(nullptr, rb->n_out, cout, cin, rb->n_in, rb->K))
+      L.feats = BwdLayout::kSplit;
+    else if (use_bf16_kernel(nullptr, dt, rb->n_out, cout, cin, rb->n_in, rb->K))
+      L.feats = BwdLayout::kBf16;
+  }
   L.nbrT = o;  // inverse neighbour map: only generated output sets on the gather kernels need one
-  if (!rb->submanifold && !L.pair_feats) o += align256(K * (size_t)rb->n_in * 4);
+  if (!rb->submanifold && !L.pair_feats()) o += align256(K * (size_t)rb->n_in * 4);
   L.pair = o;
-  if (L.pair_feats) o += align256(pair_path_bytes(rb, cout, cin, rb->n_in));
+  if (L.pair_feats()) o += align256(pair_path_bytes(rb, cout, cin, rb->n_in));
+  // rows copied for the kernel gradient and behind them the scratch of the feature gradient, which then needs
+  // no copy of grad_out of its own
+  const bool copies = use_kgrad_tiles(rb, dt, cin, cout);
+  const size_t gb = copies ? kgrad_copy_bytes(dt, rb->n_out, cout) : 0;
+  const size_t fb = copies ? kgrad_copy_bytes(dt, rb->n_in, cin) : 0;
+  const size_t scratch = L.feats == BwdLayout::kSplit ? gather_split_bytes(rb->n_out, cout, cin, rb->n_in, rb->K)
+                         : L.feats == BwdLayout::kBf16 ? gather_bf16_bytes(rb->n_out, cout, cin, rb->n_in, rb->K)
+                                                       : 0;
+  L.rows = o;
+  L.gather = o + gb + fb;
+  o += std::max(gb, align256(scratch)) + fb;
   L.Wt = o;
-  o += align256(K * (size_t)cin * cout * sz);
+  if (L.feats == BwdLayout::kPair || L.feats == BwdLayout::kPlain) o += align256(K * (size_t)cin * cout * sz);
   L.part = o;
   o += align256(nparts * cin * cout * 4);
   L.dW = o;
@@ -546,7 +563,7 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
                         const void* W, void* grad_feats, char* ws, const BwdLayout& L, const BwdRows& rows,
                         hipStream_t st) {
   if (rb->n_in == 0) return SSCONV_OK;
-  if (L.pair_feats) {
+  if (L.pair_feats()) {
     // kappa^T in the same offset order: the pairs of R_s are walked with their roles swapped
     const int64_t nw = (int64_t)rb->K * cin * cout;
     transpose_kernel<float><<<cdiv(nw, 256), 256, 0, st>>>((const float*)W, rb->K, cout, cin, false,
@@ -570,10 +587,13 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
     nbrT = inv;
   }
   const int64_t nw = (int64_t)K * cin * cout;
-  if (dt == SSCONV_F32 && use_split(nullptr, rb->n_out, cout, cin, rb->n_in, K)) {
+  CallScratch sc;
+  sc.base = ws + (rows.parts ? L.gather : L.rows);
+  sc.cap = ws + L.Wt - sc.base;
+  if (L.feats == BwdLayout::kSplit) {
     KernelTimer timer(st);
     return gather_split((const float*)grad_out, rb->n_out, cout, {(const float*)W, 1, mirror ? 1 : 0}, cin, nbrT,
-                        rb->n_in, K, (float*)grad_feats, st, nullptr, rows.grad_out_copy);
+                        rb->n_in, K, (float*)grad_feats, st, &sc, rows.grad_out_copy);
   }
   if (dt == SSCONV_F32) {
     transpose_kernel<float><<<cdiv(nw, 256), 256, 0, st>>>((const float*)W, K, cout, cin, mirror, (float*)Wt);
@@ -581,9 +601,9 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
     KernelTimer timer(st);
     return dispatch_gg<float>(grad_out, rb->n_out, cout, Wt, cin, nbrT, rb->n_in, K, grad_feats, st);
   }
-  if (use_bf16_kernel(nullptr, dt, rb->n_out, cout, cin, rb->n_in, K)) {
+  if (L.feats == BwdLayout::kBf16) {
     KernelTimer timer(st);
-    return gather_bf16(grad_out, rb->n_out, cout, W, true, mirror, cin, nbrT, rb->n_in, K, grad_feats, st, nullptr,
+    return gather_bf16(grad_out, rb->n_out, cout, W, true, mirror, cin, nbrT, rb->n_in, K, grad_feats, st, &sc,
                        rows.grad_out_copy);
   }
   transpose_kernel<uint16_t><<<cdiv(nw, 256), 256, 0, st>>>((const uint16_t*)W, K, cout, cin, mirror, (uint16_t*)Wt);

@@ -9,9 +9,12 @@ namespace ssconv {
 struct NormSink;
 
 struct BwdLayout {
-  size_t nbrT = 0, Wt = 0, part = 0, dW = 0, pair = 0, total = 0;  // byte offsets in the workspace
+  size_t nbrT = 0, Wt = 0, part = 0, dW = 0, pair = 0, rows = 0, total = 0;  // byte offsets in the workspace
+  size_t gather = 0;  // scratch of the feature gradient's tile kernel, up to Wt, where the rows are copied for it
+                      // (without copies it starts at `rows`)
   int nsplit = 1;
-  bool pair_feats = false;  // feature gradient on the pair-list path
+  enum { kPair, kSplit, kBf16, kPlain } feats = kPlain;  // the kernel of the feature gradient
+  bool pair_feats() const { return feats == kPair; }
 };
 
 // The rows of a backward call as the tile kernels read them (split, or padded where the channels are not a
@@ -20,10 +23,9 @@ struct BwdRows {
   int parts = 0;
   KgradRows grad_out, feats;
   const uint16_t* grad_out_copy = nullptr;  // grad_out.p where it is a copy
-  void* ws = nullptr;                       // from the device memory cache; the caller gives it back
 };
 int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
-             BwdRows* r, hipStream_t st);
+             char* ws, const BwdLayout& L, BwdRows* r, hipStream_t st);
 
 // Pair-list GEMM for sparse fp32 layers (pair_gemm.hip).
 bool pair_path_supported(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb);

@@ -474,11 +474,12 @@ int gather_bf16(const void* src, int64_t n_src, int ca, const void* W, bool tran
   if (n_pos == 0) return SSCONV_OK;
   const Bf16Shape s = bf16_shape(n_src, ca, cb, n_pos, K);
   char* ws = nullptr;
-  SSC_TRY(scratch_take(sc, (void**)&ws, shape_bytes(s, n_src, ca, cb, K), st));
   const bool pad = ca % 8 != 0 && !padded;
+  const size_t ap = pad ? ap_bytes(n_src, ca) : 0;
+  SSC_TRY(scratch_take(sc, (void**)&ws, shape_bytes(s, n_src, ca, cb, K) - ap_bytes(n_src, ca) + ap, st));
   uint16_t* Ap = (uint16_t*)ws;
-  uint16_t* Bp = (uint16_t*)(ws + ap_bytes(n_src, ca));
-  float* part = (float*)(ws + ap_bytes(n_src, ca) + bp_bytes(ca, cb, K));
+  uint16_t* Bp = (uint16_t*)(ws + ap);
+  float* part = (float*)(ws + ap + bp_bytes(ca, cb, K));
   const unsigned row_blocks = pad ? cdiv(n_src * (pad32(ca) / 8), 256) : 0;
   const unsigned b_blocks = cdiv((int64_t)K * (pad_k(ca) / 8) * pad16(cb), 256);
   pack_operands<<<row_blocks + b_blocks, 256, 0, st>>>((const uint16_t*)src, n_src, ca, row_blocks, (const uint16_t*)W, K,
