@@ -4,6 +4,7 @@
 
 #include "conv.hpp"
 #include "norm.hpp"
+#include "split_guard.hpp"
 #include "synth.hpp"
 
 using namespace ssconv;
@@ -149,6 +150,8 @@ extern "C" int ssconv_backward(const void* feats, const void* grad_out, ssconv_d
   const bool fork_tail = both && !L.pair_feats() && rb->n_in > 0 && dtype == SSCONV_F32;
   bool need_join = fork;
   BwdRows rows;
+  if ((grad_coeffs && L.split_rows) || (grad_feats && L.feats == BwdLayout::kSplit))
+    SSC_TRY(clear_split_flags(SplitFlags{(int*)(ws + L.flags)}, stream));
   if (grad_coeffs) SSC_TRY(bwd_rows(feats, grad_out, dtype, cin, cout, rb, (char*)workspace, L, &rows, stream));
   if (fork) SSC_TRY(aux_fork(stream, &dw_stream));
   int rc = SSCONV_OK;

@@ -83,7 +83,8 @@ __device__ __forceinline__ void mma_chunk(f4& acc, const uint16_t* a, const uint
 template <typename T, int WNB>
 __global__ __launch_bounds__(kNT) void gather_gemm(const T* __restrict__ src, int ca, const T* __restrict__ Bt,
                                                    int cb, const int32_t* __restrict__ nbr, int64_t n_rows, int K,
-                                                   T* __restrict__ out) {
+                                                   T* __restrict__ out, OnlyIf only) {
+  if (idle(only)) return;
   using C = Cfg<T>;
   constexpr int BN = 16 * WNB;
   constexpr int AV = BM * C::VPR / kNT;                 // A vectors per thread (2 f32 / 1 bf16)
@@ -276,9 +277,9 @@ __global__ void invert_nbr(const int32_t* __restrict__ nbr, int64_t n_out, int K
 
 template <typename T, int WNB>
 void launch_gg(const void* src, int ca, const void* Bt, int cb, const int32_t* nbr, int64_t n_rows, int K, void* out,
-               hipStream_t st) {
+               hipStream_t st, const OnlyIf& only) {
   dim3 grid(cdiv(n_rows, BM), cdiv(cb, 16 * WNB));
-  gather_gemm<T, WNB><<<grid, kNT, 0, st>>>((const T*)src, ca, (const T*)Bt, cb, nbr, n_rows, K, (T*)out);
+  gather_gemm<T, WNB><<<grid, kNT, 0, st>>>((const T*)src, ca, (const T*)Bt, cb, nbr, n_rows, K, (T*)out, only);
 }
 
 // Picks the N-tile width (in 16-column blocks) for cb output channels.
@@ -292,19 +293,20 @@ int pick_wnb(int cb) {
 
 template <typename T>
 int dispatch_gg(const void* src, int64_t n_src, int ca, const void* Bt, int cb, const int32_t* nbr, int64_t n_rows, int K,
-                void* out, hipStream_t st, CallScratch* sc = nullptr, NormSink* sink = nullptr) {
+                void* out, hipStream_t st, CallScratch* sc = nullptr, NormSink* sink = nullptr,
+                const OnlyIf& only = OnlyIf()) {
   const ssconv_dtype dt = sizeof(T) == 4 ? SSCONV_F32 : SSCONV_BF16;
   if (gather_mfma_supported(dt, ca, cb, K))
-    return gather_mfma(src, n_src, dt, ca, Bt, cb, nbr, nullptr, n_rows, K, out, st, sc, sink);
+    return gather_mfma(src, n_src, dt, ca, Bt, cb, nbr, nullptr, n_rows, K, out, st, sc, sink, only);
   switch (pick_wnb(cb)) {
-    case 1: launch_gg<T, 1>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
-    case 2: launch_gg<T, 2>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
-    case 3: launch_gg<T, 3>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
-    case 4: launch_gg<T, 4>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
-    case 5: launch_gg<T, 5>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
-    case 6: launch_gg<T, 6>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
-    case 7: launch_gg<T, 7>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
-    default: launch_gg<T, 8>(src, ca, Bt, cb, nbr, n_rows, K, out, st); break;
+    case 1: launch_gg<T, 1>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
+    case 2: launch_gg<T, 2>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
+    case 3: launch_gg<T, 3>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
+    case 4: launch_gg<T, 4>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
+    case 5: launch_gg<T, 5>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
+    case 6: launch_gg<T, 6>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
+    case 7: launch_gg<T, 7>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
+    default: launch_gg<T, 8>(src, ca, Bt, cb, nbr, n_rows, K, out, st, only); break;
   }
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
@@ -351,7 +353,7 @@ static bool use_bf16_kernel(const CallScratch* sc, ssconv_dtype dt, int64_t n_sr
 static bool use_split(const CallScratch* sc, int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   const int64_t v = debug_gather_variant();
   if (v == 1 || v == 2 || v == 3 || v == 8 || !gather_split_supported(n_src, ca, cb, K)) return false;
-  return !(sc && sc->fixed()) || gather_split_bytes(n_src, ca, cb, n_pos, K) <= sc->left();
+  return !(sc && sc->fixed()) || SplitFlags::kBytes + gather_split_bytes(n_src, ca, cb, n_pos, K) <= sc->left();
 }
 
 // Forwards below 2^35 multiply-adds keep the fp32 MFMA kernel and its bits: what follows a convolution may
@@ -393,9 +395,19 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
     return rc;
   }
   if (dt == SSCONV_F32 && split_forward(rb, cin, cout) && use_split(sc, rb->n_in, cin, cout, rb->n_out, rb->K)) {
-    KernelTimer timer(st);
-    return gather_split((const float*)feats, rb->n_in, cin, {(const float*)W, 0, 0}, cout, rb->nbr, rb->n_out, rb->K,
-                        (float*)out, st, sc);
+    SplitFlags flags;
+    SSC_TRY(scratch_take(sc, (void**)&flags.w, SplitFlags::kBytes, st));
+    int rc = clear_split_flags(flags, st);
+    if (rc == SSCONV_OK) {
+      KernelTimer timer(st);
+      rc = gather_split((const float*)feats, rb->n_in, cin, {(const float*)W, 0, 0}, cout, rb->nbr, rb->n_out, rb->K,
+                        (float*)out, flags, flags.feats(), st, sc);
+      if (rc == SSCONV_OK)
+        rc = dispatch_gg<float>(feats, rb->n_in, cin, W, cout, rb->nbr, rb->n_out, rb->K, out, st, nullptr, nullptr,
+                                {flags.feats(), flags.kappa(), flags.gathered()});
+    }
+    scratch_give(sc, flags.w, st);
+    return rc;
   }
   if (dt == SSCONV_F32) {
     KernelTimer timer(st);
@@ -499,8 +511,10 @@ int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, 
   uint16_t* fc = fb ? (uint16_t*)(ws + L.rows + gb) : nullptr;
   const int64_t ng = gc ? rb->n_out : 0, nf = fc ? rb->n_in : 0;
   int rc;
+  const SplitFlags flags{(int*)(ws + L.flags)};
   if (dt == SSCONV_F32)
-    rc = split_rows((const float*)grad_out, ng, cout, gc, (const float*)feats, nf, cin, fc, st);
+    rc = split_rows((const float*)grad_out, ng, cout, gc, flags.grad_out(), (const float*)feats, nf, cin, fc,
+                    flags.feats(), st);
   else
     rc = pad_rows_bf16((const uint16_t*)grad_out, ng, cout, gc, (const uint16_t*)feats, nf, cin, fc, st);
   const int64_t gs = kgrad_row_bytes(dt, cout), fs = kgrad_row_bytes(dt, cin);
@@ -546,7 +560,10 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
   L.gather = o + gb + fb;
   o += std::max(gb, align256(scratch)) + fb;
   L.Wt = o;
-  if (L.feats == BwdLayout::kPair || L.feats == BwdLayout::kPlain) o += align256(K * (size_t)cin * cout * sz);
+  if (L.feats != BwdLayout::kBf16) o += align256(K * (size_t)cin * cout * sz);
+  L.split_rows = copies && dt == SSCONV_F32;
+  L.flags = o;
+  if (L.split_rows || L.feats == BwdLayout::kSplit) o += SplitFlags::kBytes;
   L.part = o;
   o += align256(nparts * cin * cout * 4);
   L.dW = o;
@@ -591,9 +608,14 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
   sc.base = ws + (rows.parts ? L.gather : L.rows);
   sc.cap = ws + L.Wt - sc.base;
   if (L.feats == BwdLayout::kSplit) {
+    const SplitFlags flags{(int*)(ws + L.flags)};
+    const OnlyIf only{flags.grad_out(), flags.kappa(), flags.gathered()};
     KernelTimer timer(st);
-    return gather_split((const float*)grad_out, rb->n_out, cout, {(const float*)W, 1, mirror ? 1 : 0}, cin, nbrT,
-                        rb->n_in, K, (float*)grad_feats, st, &sc, rows.grad_out_copy);
+    SSC_TRY(gather_split((const float*)grad_out, rb->n_out, cout, {(const float*)W, 1, mirror ? 1 : 0}, cin, nbrT,
+                         rb->n_in, K, (float*)grad_feats, flags, flags.grad_out(), st, &sc, rows.grad_out_copy,
+                         (float*)Wt));
+    return dispatch_gg<float>(grad_out, rb->n_out, cout, Wt, cin, nbrT, rb->n_in, K, grad_feats, st, nullptr, nullptr,
+                              only);
   }
   if (dt == SSCONV_F32) {
     transpose_kernel<float><<<cdiv(nw, 256), 256, 0, st>>>((const float*)W, K, cout, cin, mirror, (float*)Wt);

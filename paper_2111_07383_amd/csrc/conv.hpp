@@ -9,10 +9,11 @@ namespace ssconv {
 struct NormSink;
 
 struct BwdLayout {
-  size_t nbrT = 0, Wt = 0, part = 0, dW = 0, pair = 0, rows = 0, total = 0;  // byte offsets in the workspace
+  size_t nbrT = 0, Wt = 0, part = 0, dW = 0, pair = 0, rows = 0, flags = 0, total = 0;  // byte offsets in the workspace
   size_t gather = 0;  // scratch of the feature gradient's tile kernel, up to Wt, where the rows are copied for it
                       // (without copies it starts at `rows`)
   int nsplit = 1;
+  bool split_rows = false;  // the kernel gradient reads split rows
   enum { kPair, kSplit, kBf16, kPlain } feats = kPlain;  // the kernel of the feature gradient
   bool pair_feats() const { return feats == kPair; }
 };

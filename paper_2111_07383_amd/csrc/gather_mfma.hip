@@ -91,7 +91,8 @@ __global__ __launch_bounds__(64 * NW) void gather_mfma_kernel(const T* __restric
                                                           const int32_t* __restrict__ nbr,
                                                           const int32_t* __restrict__ order, int64_t n_pos, int K,
                                                           T* __restrict__ out, float* __restrict__ part,
-                                                          double* __restrict__ stats) {
+                                                          double* __restrict__ stats, OnlyIf only) {
+  if (idle(only)) return;
   using SH = Shape<T, WMB, WNB, S, NW>;
   constexpr int BM = SH::BM, RV = SH::RV, VE = SH::VE, BJ = SH::BJ, L = SH::L;
   // dynamic LDS only (base at LDS address 0): stages | junk | bmask | act | count | index table
@@ -421,11 +422,12 @@ int pick_nsplit(int64_t tiles, int K) {
 
 template <typename T, int WMB, int WNB, int S, int NW, typename IX>
 int launch(const void* src, int ca, const void* Bt, int cb, const int32_t* nbr, const int32_t* order, int64_t n_pos,
-           int K, void* out, hipStream_t st, CallScratch* sc, NormSink* sink) {
+           int K, void* out, hipStream_t st, CallScratch* sc, NormSink* sink, const OnlyIf& only) {
   using SH = Shape<T, WMB, WNB, S, NW>;
   const size_t smem = smem_bytes<T, WMB, WNB, S, NW, IX>(K);
   const int64_t mt = cdiv(n_pos, SH::BM), nt = cdiv(cb, SH::BN);
   int nsplit = debug_gather_variant() == 8 ? std::min(K, 3) : pick_nsplit(mt * nt, K);
+  if (only.a) nsplit = 1;
   if (sc && sc->fixed())
     while (nsplit > 1 && (size_t)nsplit * n_pos * cb * 4 > sc->left()) --nsplit;
   if (nsplit == 1 && sink) {  // the tiles also sum the Norm statistics of what they write
@@ -433,7 +435,7 @@ int launch(const void* src, int ca, const void* Bt, int cb, const int32_t* nbr, 
     SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
     SSC_TRY(norm_sink_take(sink, mt, st));
     kern<<<dim3(mt, nt, 1), SH::NT, smem, st>>>((const T*)src, ca, (const T*)Bt, cb, nbr, order, n_pos, K, (T*)out,
-                                                 nullptr, (double*)sink->ws);
+                                                 nullptr, (double*)sink->ws, only);
     SSC_HIP(hipGetLastError());
     return SSCONV_OK;
   }
@@ -441,14 +443,14 @@ int launch(const void* src, int ca, const void* Bt, int cb, const int32_t* nbr, 
   SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   if (nsplit == 1) {
     kern<<<dim3(mt, nt, 1), SH::NT, smem, st>>>((const T*)src, ca, (const T*)Bt, cb, nbr, order, n_pos, K, (T*)out,
-                                                 nullptr, nullptr);
+                                                 nullptr, nullptr, only);
     SSC_HIP(hipGetLastError());
     return SSCONV_OK;
   }
   float* part = nullptr;
   SSC_TRY(scratch_take(sc, (void**)&part, (size_t)nsplit * n_pos * cb * 4, st));
   kern<<<dim3(mt, nt, nsplit), SH::NT, smem, st>>>((const T*)src, ca, (const T*)Bt, cb, nbr, order, n_pos, K,
-                                                    (T*)out, part, nullptr);
+                                                    (T*)out, part, nullptr, only);
   hipError_t e = hipGetLastError();
   int rc = SSCONV_OK;
   StatsRows sr;
@@ -519,17 +521,17 @@ bool pick_cfg(ssconv_dtype dt, int cb, int K, int64_t n_src, Cfg* out) {
 
 template <typename T, int WMB, int S, int NW, typename IX>
 int launch_wnb(int wnb, const void* src, int ca, const void* Bt, int cb, const int32_t* nbr, const int32_t* order,
-               int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc, NormSink* sink) {
+               int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc, NormSink* sink, const OnlyIf& only) {
   switch (wnb) {
-    case 1: return launch<T, WMB, 1, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    case 2: return launch<T, WMB, 2, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    case 3: return launch<T, WMB, 3, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    case 4: return launch<T, WMB, 4, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    case 5: return launch<T, WMB, 5, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    case 6: return launch<T, WMB, 6, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    case 7: return launch<T, WMB, 7, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    case 8: return launch<T, WMB, 8, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
-    default: return launch<T, WMB, 13, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink);
+    case 1: return launch<T, WMB, 1, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    case 2: return launch<T, WMB, 2, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    case 3: return launch<T, WMB, 3, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    case 4: return launch<T, WMB, 4, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    case 5: return launch<T, WMB, 5, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    case 6: return launch<T, WMB, 6, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    case 7: return launch<T, WMB, 7, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    case 8: return launch<T, WMB, 8, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
+    default: return launch<T, WMB, 13, S, NW, IX>(src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only);
   }
 }
 
@@ -542,7 +544,7 @@ bool gather_mfma_supported(ssconv_dtype dt, int ca, int cb, int K) {
 
 int gather_mfma(const void* src, int64_t n_src, ssconv_dtype dt, int ca, const void* Bt, int cb, const int32_t* nbr,
                 const int32_t* order, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc,
-                NormSink* sink) {
+                NormSink* sink, const OnlyIf& only) {
   if (n_pos == 0) return SSCONV_OK;
   // tuning overrides (same results): 1 = four wavefronts of 32 rows, 2 = four of 16 rows,
   // 3 = no 16-bit index table, 8 = three offset splits (in launch)
@@ -553,7 +555,7 @@ int gather_mfma(const void* src, int64_t n_src, ssconv_dtype dt, int ca, const v
   if (variant == 1 && cfg_smem<float>({2, c.wnb, 3, 4, false}, K) <= (size_t)kLdsLimit) c = {2, c.wnb, 3, 4, false};
   if (variant == 2) c = {1, c.wnb, 3, 4, false};
 #define SSC_GO(T, WMB, S, NW, IX) \
-  return launch_wnb<T, WMB, S, NW, IX>(c.wnb, src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink)
+  return launch_wnb<T, WMB, S, NW, IX>(c.wnb, src, ca, Bt, cb, nbr, order, n_pos, K, out, st, sc, sink, only)
   if (dt == SSCONV_F32) {
     if (c.nw == 8 && c.idx16 && c.stages == 4) SSC_GO(float, 1, 4, 8, uint16_t);
     if (c.nw == 8 && c.idx16) SSC_GO(float, 1, 3, 8, uint16_t);

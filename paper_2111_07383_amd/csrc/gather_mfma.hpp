@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "split_guard.hpp"
 
 namespace ssconv {
 
@@ -15,9 +16,10 @@ bool gather_mfma_supported(ssconv_dtype dt, int ca, int cb, int K);
 // Offset splits (fp32 partials added in split order) take their partials from sc (nullptr: the
 // device memory cache); with a fixed scratch region the split count is lowered until they fit.
 // sink (optional): the kernel that writes out also leaves the Norm statistics of out there (norm.hpp).
+// only: condition of the launch (one launch then, no splits).
 int gather_mfma(const void* src, int64_t n_src, ssconv_dtype dt, int ca, const void* Bt, int cb, const int32_t* nbr,
                 const int32_t* order, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc = nullptr,
-                NormSink* sink = nullptr);
+                NormSink* sink = nullptr, const OnlyIf& only = OnlyIf());
 
 // bf16 pipeline kernel (gather_bf16.hip): any channel counts whose operands stay below 2 GB.
 bool gather_bf16_supported(int64_t n_src, int ca, int cb, int K);

@@ -8,8 +8,8 @@
 // one fp32 MFMA product's matrix-core time.  The five small terms of a chunk are summed by
 // themselves and join the large sum once, so that the latter is rounded twice a chunk instead of six
 // times: errors against fp64 came out 0.3 - 0.8 of those of v_mfma_f32_16x16x4f32 on every layer tried.
-// What three parts cannot carry (infinities, NaN, values past bf16's largest, results under 2^-100)
-// is recomputed by plain fp32 multiply-adds.
+// The scheme is that of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype
+// for higher-precision computations" (2019).  For what three parts cannot carry see split_guard.hpp.
 //
 // Bound: the matrix cores (55 - 60% busy) and the texture path that feeds the LDS (63 KB of DMA per
 // 256 x 112 x 32 chunk).  Two workgroup-wide stages of 69 KB fill the LDS; tall tiles because LDS
@@ -31,11 +31,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // Split rows: [row][ceil(ca / 32)][3 parts][32 channels] bf16, zero past ca; 192 bytes per 32 channels.
 __host__ __device__ __forceinline__ int chunks32(int ca) { return (ca + 31) / 32; }
-__device__ __forceinline__ void split3(float x, uint16_t* p) {
+// The parts of x; returns whether they are not all of it (an infinity or NaN leaves NaN behind).
+__device__ __forceinline__ bool split3(float x, uint16_t* p) {
   p[0] = f32_to_bf16_rne(x);
   const float r1 = x - bf16_to_f32(p[0]);
   p[1] = f32_to_bf16_rne(r1);
-  p[2] = f32_to_bf16_rne(r1 - bf16_to_f32(p[1]));
+  const float r2 = r1 - bf16_to_f32(p[1]);
+  p[2] = f32_to_bf16_rne(r2);
+  return !(r2 == bf16_to_f32(p[2]));
 }
 
 __device__ __forceinline__ void store_parts(const uint16_t (*e)[3], uint16_t* dst, int64_t step) {
@@ -52,7 +55,7 @@ __device__ __forceinline__ void store_parts(const uint16_t (*e)[3], uint16_t* ds
 
 // Thread i splits 8 channels of one row.
 __device__ __forceinline__ void split_row(const float* __restrict__ src, int64_t n, int ca, int64_t i,
-                                          uint16_t* __restrict__ A3) {
+                                          uint16_t* __restrict__ A3, int* __restrict__ flag) {
   const int cc = chunks32(ca), per = 4 * cc;
   if (i >= n * per) return;
   const int64_t r = i / per;
@@ -67,28 +70,34 @@ __device__ __forceinline__ void split_row(const float* __restrict__ src, int64_t
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = c0 + j < ca ? s[j] : 0.f;
   }
+  bool lost = false;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) split3(v[j], e[j]);
+  for (int j = 0; j < 8; ++j) lost |= split3(v[j], e[j]);
+  if (lost) *flag = 1;
   store_parts(e, A3 + (r * cc + (q >> 2)) * 96 + 8 * (q & 3), 32);
 }
 
 // Rows of two sources in one launch.
 __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ x, int64_t nx, int cx, unsigned x_blocks,
-                                                         uint16_t* __restrict__ x3, const float* __restrict__ y,
-                                                         int64_t ny, int cy, uint16_t* __restrict__ y3) {
+                                                         uint16_t* __restrict__ x3, int* __restrict__ x_flag,
+                                                         const float* __restrict__ y, int64_t ny, int cy,
+                                                         uint16_t* __restrict__ y3, int* __restrict__ y_flag) {
   if (blockIdx.x < x_blocks)
-    split_row(x, nx, cx, (int64_t)blockIdx.x * 256 + threadIdx.x, x3);
+    split_row(x, nx, cx, (int64_t)blockIdx.x * 256 + threadIdx.x, x3, x_flag);
   else
-    split_row(y, ny, cy, (int64_t)(blockIdx.x - x_blocks) * 256 + threadIdx.x, y3);
+    split_row(y, ny, cy, (int64_t)(blockIdx.x - x_blocks) * 256 + threadIdx.x, y3, y_flag);
 }
 
 // Both operands in one launch: blocks below row_blocks split the gathered rows, the others kappa into
-// B3[s][pad_k(ca) / 8][3 parts][cb16][8] (zeros past the end), a thread one 8-channel run of one column.
+// B3[s][pad_k(ca) / 8][3 parts][cb16][8] (zeros past the end), a thread one 8-channel run of one column, and
+// where Bt is given into Bt[s][n][k] in fp32.
 __global__ __launch_bounds__(256) void split_operands(const float* __restrict__ src, int64_t n_src, int ca,
                                                       unsigned row_blocks, SplitKernel B, int K, int cb,
-                                                      uint16_t* __restrict__ A3, uint16_t* __restrict__ B3) {
+                                                      uint16_t* __restrict__ A3, uint16_t* __restrict__ B3,
+                                                      int* __restrict__ rows_flag, int* __restrict__ kappa_flag,
+                                                      float* __restrict__ Bt) {
   if (blockIdx.x < row_blocks) {
-    split_row(src, n_src, ca, (int64_t)blockIdx.x * 256 + threadIdx.x, A3);
+    split_row(src, n_src, ca, (int64_t)blockIdx.x * 256 + threadIdx.x, A3, rows_flag);
     return;
   }
   uint16_t e[8][3];
@@ -99,29 +108,16 @@ __global__ __launch_bounds__(256) void split_operands(const float* __restrict__ 
   const int64_t sc = i / cbp;
   const int k0 = (int)(sc % cg) * 8;
   const int64_t s = sc / cg, sw = B.mirror ? K - 1 - s : s;
+  bool lost = false;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     float x = 0.f;
     if (n < cb && k0 + j < ca) x = B.transposed ? B.W[(sw * ca + k0 + j) * cb + n] : B.W[(sw * cb + n) * ca + k0 + j];
-    split3(x, e[j]);
+    lost |= split3(x, e[j]);
+    if (Bt && n < cb && k0 + j < ca) Bt[(s * cb + n) * ca + k0 + j] = x;
   }
+  if (lost) *kappa_flag = 1;
   store_parts(e, B3 + (sc * 3 * cbp + n) * 8, (int64_t)cbp * 8);
-}
-
-// One output by plain fp32 multiply-adds: what a value that the split cannot carry (infinite, NaN,
-// above bf16's largest, or so small that its third part would be lost) makes of an output is
-// computed again this way (doubtful).
-__device__ __forceinline__ float plain_dot(const float* __restrict__ src, int ca, const SplitKernel& B, int cb,
-                                           const int32_t* __restrict__ nbr, int64_t n_pos, int K, int64_t p, int n) {
-  float acc = 0.f;
-  for (int s = 0; s < K; ++s) {
-    const int r = nbr[(int64_t)s * n_pos + p];
-    if (r < 0) continue;
-    const int64_t sw = B.mirror ? K - 1 - s : s;
-    for (int k = 0; k < ca; ++k)
-      acc = fmaf(src[(int64_t)r * ca + k], B.transposed ? B.W[(sw * ca + k) * cb + n] : B.W[(sw * cb + n) * ca + k], acc);
-  }
-  return acc;
 }
 
 // Tile of BM = 64 MR output rows x 16 NB columns.  Row group wm = w % 4 (MR 16-row blocks), column
@@ -146,8 +142,9 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
                                                            const uint16_t* __restrict__ B3, int cb,
                                                            const int32_t* __restrict__ nbr, int64_t n_pos, int K,
                                                            TilePlan plan, float* __restrict__ part,
-                                                           const float* __restrict__ src, SplitKernel B,
+                                                           const int* __restrict__ rows_flag, SplitFlags flags,
                                                            float* __restrict__ out) {
+  if (*rows_flag | *flags.kappa()) return;  // set before this kernel: the plain one computes it all
   using G = GS<NB, MR>;
   constexpr int BM = G::BM, S = G::S, NRB = G::NRB;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -325,7 +322,6 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
     }
 
     // the tile, or this workgroup's share of it
-    const bool whole = sa == 0 && sb == K;
     // (the lane index again, opaque: its address arithmetic would otherwise be hoisted out of the tile
     // loop and hold some 60 registers through the chunk loop)
     int el = lane;
@@ -334,7 +330,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
     const int nbc = wn == 0 ? G::WN0 : G::WN1;
     const int c0 = 16 * G::WN0 * wn;
     if (sa == 0) {  // whole, or its first piece: straight to out
-      bool odd = false;
+      bool past = false;
 #pragma unroll
       for (int mb = 0; mb < MR; ++mb)
 #pragma unroll
@@ -346,18 +342,11 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
             const int col = n0 + c0 + 16 * nb + r16;
             if (nb < nbc && col < cb) {
               out[p * cb + col] = acc[mb][nb][i];
-              odd |= doubtful(acc[mb][nb][i]);
+              past |= past_range(acc[mb][nb][i]);
             }
           }
         }
-      if (odd && whole) {
-        for (int e = 0; e < MR * 4 * nbc; ++e) {
-          const int64_t p = p0 + 16 * (wm * MR + e / (4 * nbc)) + 4 * g + e / nbc % 4;
-          const int col = n0 + c0 + 16 * (e % nbc) + r16;
-          if (p < n_pos && col < cb && doubtful(out[p * cb + col]))
-            out[p * cb + col] = plain_dot(src, ca, B, cb, nbr, n_pos, K, p, col);
-        }
-      }
+      if (past) *flags.gathered() = 1;
     } else {
       float* dst = part + (int64_t)wg * BM * G::BN;
 #pragma unroll
@@ -377,8 +366,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_split_kernel(const uint16
 // Adds the pieces of the tiles that more than one workgroup held, in workgroup order.  A block takes
 // 1024 consecutive values of one tile.
 __global__ __launch_bounds__(256) void split_fixup(const float* __restrict__ part, TilePlan plan, int K, int BM,
-                                                   int BN, int cb, const int32_t* __restrict__ nbr, int64_t n_pos,
-                                                   const float* __restrict__ src, int ca, SplitKernel B,
+                                                   int BN, int cb, int64_t n_pos, SplitFlags flags,
                                                    float* __restrict__ out) {
   const int64_t t = blockIdx.x;
   const int64_t i0 = unit_owner(plan, t * K), i1 = unit_owner(plan, t * K + K - 1);
@@ -395,9 +383,7 @@ __global__ __launch_bounds__(256) void split_fixup(const float* __restrict__ par
     const float4 x = *reinterpret_cast<const float4*>(part + i * BM * BN + e);
     v[0] += x.x, v[1] += x.y, v[2] += x.z, v[3] += x.w;
   }
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (col + k < cb && doubtful(v[k])) v[k] = plain_dot(src, ca, B, cb, nbr, n_pos, K, p, col + k);
+  if (past_range(v[0]) || past_range(v[1]) || past_range(v[2]) || past_range(v[3])) *flags.gathered() = 1;
   if ((cb & 3) == 0) {
     *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
   } else {
@@ -461,15 +447,15 @@ SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
 
 template <int NB, int MR>
 int launch(const SplitShape& sh, const uint16_t* A3, int64_t a_bytes, int ca, const uint16_t* B3, int cb,
-           const int32_t* nbr, int64_t n_pos, int K, float* part, const float* src, const SplitKernel& B, float* out,
-           hipStream_t st) {
+           const int32_t* nbr, int64_t n_pos, int K, float* part, const int* rows_flag, const SplitFlags& flags,
+           float* out, hipStream_t st) {
   auto kern = gather_split_kernel<NB, MR>;
   using G = GS<NB, MR>;
   TilePlan plan = sh.plan;
   plan.panel = panel_offsets(G::ROOM, G::BM, pad_k(ca), K);
   const size_t smem = (size_t)(kTileLds - G::ROOM) + panel_bytes(plan.panel, G::BM, pad_k(ca));
   SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  kern<<<plan.G, kTileThreads, smem, st>>>(A3, a_bytes, ca, B3, cb, nbr, n_pos, K, plan, part, src, B, out);
+  kern<<<plan.G, kTileThreads, smem, st>>>(A3, a_bytes, ca, B3, cb, nbr, n_pos, K, plan, part, rows_flag, flags, out);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
 }
@@ -481,23 +467,32 @@ bool gather_split_supported(int64_t n_src, int ca, int cb, int K) {
          b3_bytes(ca, cb, K) < ((size_t)1 << 31);
 }
 
+__global__ void clear_words(int* __restrict__ w) { w[threadIdx.x] = 0; }
+
+int clear_split_flags(const SplitFlags& f, hipStream_t st) {
+  clear_words<<<1, SplitFlags::kBytes / 4, 0, st>>>(f.w);
+  SSC_HIP(hipGetLastError());
+  return SSCONV_OK;
+}
+
 size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   return shape_bytes(split_shape(n_src, ca, cb, n_pos, K), n_src, ca, cb, K);
 }
 
 int64_t split_row_bytes(int ca) { return (int64_t)chunks32(ca) * 192; }
 
-int split_rows(const float* x, int64_t nx, int cx, uint16_t* x3, const float* y, int64_t ny, int cy, uint16_t* y3,
-               hipStream_t st) {
+int split_rows(const float* x, int64_t nx, int cx, uint16_t* x3, int* x_flag, const float* y, int64_t ny, int cy,
+               uint16_t* y3, int* y_flag, hipStream_t st) {
   const unsigned xb = cdiv(nx * 4 * chunks32(cx), 256), yb = cdiv(ny * 4 * chunks32(cy), 256);
   if (xb + yb == 0) return SSCONV_OK;
-  split_rows_kernel<<<xb + yb, 256, 0, st>>>(x, nx, cx, xb, x3, y, ny, cy, y3);
+  split_rows_kernel<<<xb + yb, 256, 0, st>>>(x, nx, cx, xb, x3, x_flag, y, ny, cy, y3, y_flag);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
 }
 
 int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, int cb, const int32_t* nbr,
-                 int64_t n_pos, int K, float* out, hipStream_t st, CallScratch* sc, const uint16_t* rows3) {
+                 int64_t n_pos, int K, float* out, const SplitFlags& flags, int* rows_flag, hipStream_t st, CallScratch* sc,
+                 const uint16_t* rows3, float* Bt) {
   if (n_pos == 0) return SSCONV_OK;
   const SplitShape s = split_shape(n_src, ca, cb, n_pos, K);
   char* ws = nullptr;
@@ -509,10 +504,11 @@ int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, 
   float* part = (float*)(ws + a3 + b3_bytes(ca, cb, K));
   const unsigned row_blocks = rows3 ? 0 : cdiv(n_src * 4 * chunks32(ca), 256);
   const unsigned b_blocks = cdiv((int64_t)K * (pad_k(ca) / 8) * pad16(cb), 256);
-  split_operands<<<row_blocks + b_blocks, 256, 0, st>>>(src, n_src, ca, row_blocks, B, K, cb, split, B3);
+  split_operands<<<row_blocks + b_blocks, 256, 0, st>>>(src, n_src, ca, row_blocks, B, K, cb, split, B3,
+                                                        rows_flag, flags.kappa(), Bt);
   int rc = hipGetLastError() == hipSuccess ? SSCONV_OK : fail(SSCONV_E_HIP, "operand split launch failed");
   const int64_t ab = (int64_t)n_src * chunks32(ca) * 192;
-#define SSG_GO(NB_, MR_) rc = launch<NB_, MR_>(s, A3, ab, ca, B3, cb, nbr, n_pos, K, part, src, B, out, st)
+#define SSG_GO(NB_, MR_) rc = launch<NB_, MR_>(s, A3, ab, ca, B3, cb, nbr, n_pos, K, part, rows_flag, flags, out, st)
 #define SSG_NB(NB_)                                                   \
   case NB_:                                                           \
     if (s.mr == 4) SSG_GO(NB_, 4);                                    \
@@ -533,7 +529,7 @@ int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, 
   if (rc == SSCONV_OK && !whole_tiles(s.plan, K)) {
     const int BM = 64 * s.mr, BN = 16 * s.nb;
     dim3 grid((unsigned)(s.plan.mt * s.plan.nt), cdiv(BM * BN, 1024));
-    split_fixup<<<grid, 256, 0, st>>>(part, s.plan, K, BM, BN, cb, nbr, n_pos, src, ca, B, out);
+    split_fixup<<<grid, 256, 0, st>>>(part, s.plan, K, BM, BN, cb, n_pos, flags, out);
     if (hipGetLastError() != hipSuccess) rc = fail(SSCONV_E_HIP, "split fix-up launch failed");
   }
   scratch_give(sc, ws, st);

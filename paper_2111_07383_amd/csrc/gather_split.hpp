@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "split_guard.hpp"
 
 namespace ssconv {
 
@@ -17,13 +18,16 @@ bool gather_split_supported(int64_t n_src, int ca, int cb, int K);
 // Scratch of a call (the split operands and the partial tiles).
 size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K);
 // out[p][:] = sum_s B[s] (cb x ca) . src[nbr[s][p]] for p < n_pos; src [n_src, ca], out [n_pos, cb].
-// rows3 (optional): the rows of src already split.
+// rows3 (optional): the rows of src already split.  rows_flag (one of flags) is that of src's rows; where
+// one of the words is set afterwards, out is not valid.  Bt (optional): receives B[s][n][k] in fp32, which the
+// plain kernel then reads.
 int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, int cb, const int32_t* nbr,
-                 int64_t n_pos, int K, float* out, hipStream_t st, CallScratch* sc, const uint16_t* rows3 = nullptr);
+                 int64_t n_pos, int K, float* out, const SplitFlags& flags, int* rows_flag, hipStream_t st, CallScratch* sc,
+                 const uint16_t* rows3 = nullptr, float* Bt = nullptr);
 
 // Split rows [n][ceil(c / 32)][3 parts][32 channels] of two sources (either may have no rows).
 int64_t split_row_bytes(int c);
-int split_rows(const float* x, int64_t nx, int cx, uint16_t* x3, const float* y, int64_t ny, int cy, uint16_t* y3,
-               hipStream_t st);
+int split_rows(const float* x, int64_t nx, int cx, uint16_t* x3, int* x_flag, const float* y, int64_t ny, int cy,
+               uint16_t* y3, int* y_flag, hipStream_t st);
 
 }  // namespace ssconv

@@ -91,3 +91,67 @@ def test_values_the_parts_cannot_carry(n):
     fine &= torch.isfinite(f32)
     bound = 27 * 40 * 2.0 ** -24 * mag + 1e-43
     assert ((y.double() - want).abs()[fine] <= bound[fine]).all()
+
+
+@pytest.mark.parametrize("small", [-112, -120, -124, -140])
+@pytest.mark.parametrize("where", ["rows", "kernel"])
+def test_small_operands_keep_their_bits(where, small):
+    """An operand so small that bf16 has no room for its third part, times one that brings the result back to
+    ordinary size: the bound of the plain fp32 sums (a rounding per product), in both directions."""
+    rb = _rulebook(700, 3)
+    nbr = rb.neighbours()
+    g = torch.Generator("cuda").manual_seed(3)
+    x, W = torch.randn((700, 40), device="cuda", generator=g), torch.randn((27, 24, 40), device="cuda", generator=g)
+    dy = torch.randn((700, 24), device="cuda", generator=g)
+    big = min(-small - 8, 110)
+    if where == "rows":
+        x, dy, W = x * 2.0 ** small, dy * 2.0 ** small, W * 2.0 ** big
+    else:
+        x, dy, W = x * 2.0 ** big, dy * 2.0 ** big, W * 2.0 ** small
+    ss.debug_set(3, 13)
+    try:
+        y = ss.forward(x, rb, W)
+        dx = ss.backward(x, dy, rb, W, need_coeffs=False)[0]
+    finally:
+        ss.debug_set(3, 0)
+    Wt = W.transpose(1, 2).contiguous()
+    for got, (want, mag), c in ((y, _dense(x, W, nbr), 40), (dx, _dense(dy, Wt, _inverse(nbr, rb.n_in)), 24)):
+        assert ((got.double() - want).abs() <= 27 * c * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("n", [300, 4000])
+def test_whole_maps_of_them(n):
+    """Every value infinite, NaN or past fp32's range in the sums: what the fp32 matrix cores' kernel gives."""
+    rb = _rulebook(n, 3)
+    g = torch.Generator("cuda").manual_seed(4)
+    W, dy = torch.rand((27, 24, 40), device="cuda", generator=g) + 0.5, torch.rand((n, 24), device="cuda", generator=g) + 0.5
+    for x in (torch.full((n, 40), float("nan"), device="cuda"), torch.full((n, 40), -float("inf"), device="cuda"),
+              3e38 * torch.rand((n, 40), device="cuda", generator=g), 1e-37 * torch.rand((n, 40), device="cuda", generator=g)):
+        out = []
+        for variant in (13, 3):   # 3: the fp32 matrix cores
+            ss.debug_set(3, variant)
+            try:
+                out.append((ss.forward(x, rb, W), ss.backward(x, dy * x[:, :24], rb, W, need_coeffs=False)[0]))
+            finally:
+                ss.debug_set(3, 0)
+        for a, b in zip(*out):
+            a, b = a.double().cpu().numpy(), b.double().cpu().numpy()
+            np.testing.assert_allclose(a, b, rtol=27 * 40 * 2.0 ** -24, atol=0)   # (one sign of values)
+
+
+def test_parts_down_to_their_limit():
+    """Three parts carry every bit of a value from 2^-110 on (parts that are subnormal in bf16 count), and below
+    it the plain kernel does: single products with a power of two are exact."""
+    n = 4096
+    rb = _rulebook(n, 1)
+    g = torch.Generator("cuda").manual_seed(5)
+    for lo, hi in ((-110, -96), (-126, -110), (100, 127)):
+        e = torch.randint(lo, hi, (n, 8), device="cuda", generator=g)
+        x = torch.ldexp(1 + torch.rand((n, 8), device="cuda", generator=g), e)
+        W = 2.0 ** (-60 if lo > 0 else 60) * torch.eye(8, device="cuda")[None].contiguous()
+        ss.debug_set(3, 13)
+        try:
+            y = ss.forward(x, rb, W)
+        finally:
+            ss.debug_set(3, 0)
+        assert torch.equal(y, x * W[0, 0, 0])
