@@ -474,7 +474,7 @@ static bool use_kgrad_tiles(const ssconv_rulebook* rb, ssconv_dtype dt, int cin,
   // splitting costs a pass over the rows: not where each is gathered a few times only (60 -> 120 channels, 99k
   // pairs of 79k rows: 22 us and 15 for the split against 36 on the fp32 ring kernel; 17k of 1.9k: 9 and 4
   // against 20)
-  if (dt == SSCONV_F32 && rb->n_pairs < 6 * (rb->n_in + rb->n_out)) return false;
+  if (dt == SSCONV_F32 && v != 13 && rb->n_pairs < 6 * (rb->n_in + rb->n_out)) return false;
   if (dt == SSCONV_F32 ? v == 7 : v == 6 || (v == 12 && kgrad_supported(dt, cin, cout))) return false;
   return rb->K <= kKgradMaxK && rb->n_in > 0 && rb->n_out > 0 &&
          rb->n_in * kgrad_row_bytes(dt, cin) < ((int64_t)1 << 31) && rb->n_out * kgrad_row_bytes(dt, cout) < ((int64_t)1 << 31);
@@ -645,12 +645,13 @@ int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, i
   const int64_t n = (int64_t)K * cin * cout;
   if (use_kgrad_units(rb, dt, cin, cout)) {
     const KgradUnits units = plan_units(rb, dt, cin, cout);
-    PlainGrad plain;
     if (rows.parts) {
+      const SplitFlags flags{rows.parts == 3 ? (int*)(ws + L.flags) : nullptr};
       SSC_TRY(kgrad_tiles(rows.grad_out, rows.feats, rows.parts, cin, cout, rb, kgrad_tile(rb, rows.parts, cin, cout),
-                          units, part, st));
-      if (rows.parts == 3)
-        plain = {(const float*)grad_out, (const float*)feats, reinterpret_cast<const int2*>(rb->pairs), rb->pair_off_dev};
+                          units, flags, part, st));
+      if (rows.parts == 3)  // the same units on the fp32 matrix cores
+        SSC_TRY(kgrad_f32(grad_out, feats, cin, cout, rb, units, part, st,
+                          {flags.grad_out(), flags.feats(), flags.kgrad()}));
     } else if (dt == SSCONV_F32)
       SSC_TRY(kgrad_f32(grad_out, feats, cin, cout, rb, units, part, st));
     else
@@ -660,7 +661,7 @@ int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, i
       SSC_TRY(aux_fork(st, &rst));
       *tail = rst;
     }
-    return reduce_units(part, units, cin, cout, fout, fin, dW, rst, plain);
+    return reduce_units(part, units, cin, cout, fout, fin, dW, rst);
   }
   if (kgrad_supported(dt, cin, cout))
     SSC_TRY(kgrad_partials(grad_out, feats, dt, cin, cout, rb, kgrad_plan(rb, dt, cin, cout), part, st));

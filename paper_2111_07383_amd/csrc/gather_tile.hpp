@@ -23,13 +23,6 @@ __host__ __device__ __forceinline__ int pad32(int c) { return (c + 31) & ~31; }
 __host__ __device__ __forceinline__ int pad_k(int c) { return pad8(c) % 32 == 24 ? pad8(c) + 8 : pad8(c); }
 inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Results that three bf16 parts may have got wrong: what an infinity, a NaN or a value past bf16's largest
-// makes of a sum, and sums so small (under 2^-100) that third parts may have been lost.
-__device__ __forceinline__ bool doubtful(float v) {
-  const float a = fabsf(v);
-  return !(a <= 3.0e38f) || (a > 0.f && a < 7.9e-31f);
-}
-
 // Rows row0 .. in mt x nt tiles; workgroup i takes the units [i * units / G, (i + 1) * units / G) of the
 // (tile, offset) sequence (units = mt * nt * K), so that every workgroup has the same number of offsets
 // whatever the tile count.

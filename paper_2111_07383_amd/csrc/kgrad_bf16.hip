@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256) void kgrad_bf16_kernel(const uint16_t* __restr
 // per unit.
 template <int VEC>
 __global__ __launch_bounds__(256) void reduce_units_kernel(const float* __restrict__ part, KgradUnits units, int cin,
-                                                           int cout, FieldTab fout, FieldTab fin, PlainGrad plain,
+                                                           int cout, FieldTab fout, FieldTab fin,
                                                            float* __restrict__ dW) {
   const int e = (blockIdx.x * blockDim.x + threadIdx.x) * VEC;
   const int s = blockIdx.y;
@@ -328,16 +328,6 @@ __global__ __launch_bounds__(256) void reduce_units_kernel(const float* __restri
       for (int k = 0; k < VEC; ++k) acc[k] += u + j < u1 ? v[j][k] : 0.f;
   }
   const int o = e / cin;
-  if (plain.pairs) {
-#pragma unroll
-    for (int k = 0; k < VEC; ++k)
-      if (doubtful(acc[k])) {
-        float a = 0.f;
-        for (int64_t p = plain.pair_off[s]; p < plain.pair_off[s + 1]; ++p)
-          a = fmaf(plain.grad_out[(int64_t)plain.pairs[p].x * cout + o], plain.feats[(int64_t)plain.pairs[p].y * cin + e + k - o * cin], a);
-        acc[k] = a;
-      }
-  }
 #pragma unroll
   for (int k = 0; k < VEC; ++k) dW[dw_block_pos(fout, fin, units.K, cin, s, o, e + k - o * cin)] = acc[k];
 }
@@ -381,13 +371,13 @@ KgradUnits kgrad_units(const ssconv_rulebook* rb, int want) {
 }
 
 int reduce_units(const float* part, const KgradUnits& units, int cin, int cout, const FieldTab& fout,
-                 const FieldTab& fin, float* dW, hipStream_t st, const PlainGrad& plain) {
+                 const FieldTab& fin, float* dW, hipStream_t st) {
   const int64_t n = (int64_t)cin * cout;
   if (n == 0 || units.K == 0) return SSCONV_OK;
   if (cin % 4 == 0)
-    reduce_units_kernel<4><<<dim3(cdiv(n / 4, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, plain, dW);
+    reduce_units_kernel<4><<<dim3(cdiv(n / 4, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, dW);
   else
-    reduce_units_kernel<1><<<dim3(cdiv(n, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, plain, dW);
+    reduce_units_kernel<1><<<dim3(cdiv(n, 256), units.K), 256, 0, st>>>(part, units, cin, cout, fout, fin, dW);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
 }

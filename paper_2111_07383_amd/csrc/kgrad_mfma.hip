@@ -316,7 +316,9 @@ __global__ __launch_bounds__(256) void kgrad_f32_lds_kernel(const float* __restr
                                                             const float* __restrict__ F, int64_t f_rows, int cin,
                                                             const int2* __restrict__ pairs,
                                                             const int64_t* __restrict__ pair_off, KgradUnits units,
-                                                            int mtiles, int ntiles, float* __restrict__ part) {
+                                                            int mtiles, int ntiles, float* __restrict__ part,
+                                                            OnlyIf only) {
+  if (idle(only)) return;
   using C = KF<WMB, WNB>;
   static_assert(C::LG <= 2 && C::LF <= 2, "at most two DMA blocks per operand");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -432,22 +434,23 @@ __global__ __launch_bounds__(256) void kgrad_f32_lds_kernel(const float* __restr
 template <int WMB, int WNB>
 void launch_f32_lds(dim3 grid, const float* G, int64_t g_rows, int cout, const float* F, int64_t f_rows, int cin,
                     const int2* pairs, const int64_t* pair_off, const KgradUnits& units, int mt, int nt, float* part,
-                    hipStream_t st) {
+                    hipStream_t st, const OnlyIf& only) {
   auto kern = kgrad_f32_lds_kernel<WMB, WNB>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, KF<WMB, WNB>::SMEM);
-  kern<<<grid, 256, KF<WMB, WNB>::SMEM, st>>>(G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part);
+  kern<<<grid, 256, KF<WMB, WNB>::SMEM, st>>>(G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part,
+                                                only);
 }
 
 template <int WMB>
 void launch_f32_lds_n(int wnb, dim3 grid, const float* G, int64_t g_rows, int cout, const float* F, int64_t f_rows,
                       int cin, const int2* pairs, const int64_t* pair_off, const KgradUnits& units, int mt, int nt,
-                      float* part, hipStream_t st) {
+                      float* part, hipStream_t st, const OnlyIf& only) {
   switch (wnb) {
-    case 1: launch_f32_lds<WMB, 1>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st); break;
-    case 2: launch_f32_lds<WMB, 2>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st); break;
-    case 4: launch_f32_lds<WMB, 4>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st); break;
-    case 7: launch_f32_lds<WMB, 7>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st); break;
-    default: launch_f32_lds<WMB, 8>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st); break;
+    case 1: launch_f32_lds<WMB, 1>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st, only); break;
+    case 2: launch_f32_lds<WMB, 2>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st, only); break;
+    case 4: launch_f32_lds<WMB, 4>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st, only); break;
+    case 7: launch_f32_lds<WMB, 7>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st, only); break;
+    default: launch_f32_lds<WMB, 8>(grid, G, g_rows, cout, F, f_rows, cin, pairs, pair_off, units, mt, nt, part, st, only); break;
   }
 }
 
@@ -553,7 +556,7 @@ int kgrad_f32_units_want(const ssconv_rulebook* rb, int cin, int cout) {
 }
 
 int kgrad_f32(const void* grad_out, const void* feats, int cin, int cout, const ssconv_rulebook* rb,
-              const KgradUnits& units, float* part, hipStream_t st) {
+              const KgradUnits& units, float* part, hipStream_t st, const OnlyIf& only) {
   if (units.nunits == 0) return SSCONV_OK;
   const KgradPlan p = kgrad_plan(rb, SSCONV_F32, cin, cout);
   const int64_t ntask = (int64_t)units.nunits * p.mtiles * p.ntiles;
@@ -563,11 +566,11 @@ int kgrad_f32(const void* grad_out, const void* feats, int cin, int cout, const 
   const float* F = (const float*)feats;
   const int64_t g_rows = rb->n_out, f_rows = rb->n_in;
   switch (p.wmb) {
-    case 1: launch_f32_lds_n<1>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st); break;
-    case 2: launch_f32_lds_n<2>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st); break;
-    case 4: launch_f32_lds_n<4>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st); break;
-    case 7: launch_f32_lds_n<7>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st); break;
-    default: launch_f32_lds_n<8>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st); break;
+    case 1: launch_f32_lds_n<1>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st, only); break;
+    case 2: launch_f32_lds_n<2>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st, only); break;
+    case 4: launch_f32_lds_n<4>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st, only); break;
+    case 7: launch_f32_lds_n<7>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st, only); break;
+    default: launch_f32_lds_n<8>(p.wnb, grid, G, g_rows, cout, F, f_rows, cin, pairs, rb->pair_off_dev, units, p.mtiles, p.ntiles, part, st, only); break;
   }
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "split_guard.hpp"
 
 namespace ssconv {
 
@@ -39,7 +40,7 @@ KgradUnits kgrad_units(const ssconv_rulebook* rb, int want);
 bool kgrad_f32_units_ok(const ssconv_rulebook* rb, int cin, int cout);
 int kgrad_f32_units_want(const ssconv_rulebook* rb, int cin, int cout);
 int kgrad_f32(const void* grad_out, const void* feats, int cin, int cout, const ssconv_rulebook* rb,
-              const KgradUnits& units, float* part, hipStream_t st);
+              const KgradUnits& units, float* part, hipStream_t st, const OnlyIf& only = OnlyIf());
 
 // bf16 tile width (in 32-channel steps of the 2x2 wavefront grid) for cin x cout.
 int kgrad_bf16_tile(int cin, int cout);
@@ -51,15 +52,8 @@ int kgrad_bf16(const void* grad_out, int64_t n_out, const void* feats, int64_t n
 
 // dW[s][:] = sum over the units of offset s of part[u][:] (n = cout * cin per unit), fixed order.
 // dW (field-pair-blocked, dw_block_pos) from the unit partials, each offset's in unit order.
-// With plain.pairs given (partials from split fp32 rows), a sum that the parts cannot carry is computed
-// again from grad_out and feats by plain fp32 multiply-adds.
-struct PlainGrad {
-  const float *grad_out = nullptr, *feats = nullptr;
-  const int2* pairs = nullptr;
-  const int64_t* pair_off = nullptr;
-};
 int reduce_units(const float* part, const KgradUnits& units, int cin, int cout, const FieldTab& fout,
-                 const FieldTab& fin, float* dW, hipStream_t st, const PlainGrad& plain = PlainGrad());
+                 const FieldTab& fin, float* dW, hipStream_t st);
 
 // part[split][s][o][i] (fp32) = sum over the split's slice of R_s of grad_out[x][o] feats[y][i].
 int kgrad_partials(const void* grad_out, const void* feats, ssconv_dtype dt, int cin, int cout,

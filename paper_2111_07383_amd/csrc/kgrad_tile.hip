@@ -57,7 +57,9 @@ template <int P, int WM, int WN>
 __global__ __launch_bounds__(256) void kgrad_tile_kernel(KgradRows G, int cout, KgradRows F, int cin,
                                                          const int2* __restrict__ pairs,
                                                          const int64_t* __restrict__ pair_off, KgradUnits units,
-                                                         int mtiles, int ntiles, float* __restrict__ part) {
+                                                         int mtiles, int ntiles, SplitFlags flags,
+                                                         float* __restrict__ part) {
+  if (P == 3 && (*flags.grad_out() | *flags.feats())) return;  // set before this kernel
   using C = KT<P, WM, WN>;
   constexpr int S = C::S, L = C::L;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -231,6 +233,7 @@ __global__ __launch_bounds__(256) void kgrad_tile_kernel(KgradRows G, int cout, 
 #undef SSK_FRAG
 
   float* dst = part + (int64_t)u * cout * cin;
+  bool past = false;
 #pragma unroll
   for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -240,19 +243,24 @@ __global__ __launch_bounds__(256) void kgrad_tile_kernel(KgradRows G, int cout, 
 #pragma unroll
       for (int n = 0; n < WN; ++n) {
         const int col = n0 + (wn * WN + n) * 16 + r16;
-        if (col < cin) dst[(int64_t)m * cin + col] = P == 3 ? low[P == 3 ? i : 0][P == 3 ? n : 0][e] + acc[i][n][e] : acc[i][n][e];
+        if (col >= cin) continue;
+        const float v = P == 3 ? low[P == 3 ? i : 0][P == 3 ? n : 0][e] + acc[i][n][e] : acc[i][n][e];
+        dst[(int64_t)m * cin + col] = v;
+        past |= past_range(v);
       }
     }
+  if (P == 3 && past) *flags.kgrad() = 1;
 }
 
 template <int P, int WM, int WN>
 int launch(const KgradRows& G, const KgradRows& F, int cin, int cout, const ssconv_rulebook* rb, const KgradTile& t,
-           const KgradUnits& units, float* part, hipStream_t st) {
+           const KgradUnits& units, const SplitFlags& flags, float* part, hipStream_t st) {
   auto kern = kgrad_tile_kernel<P, WM, WN>;
   constexpr int smem = KT<P, WM, WN>::SMEM;
   SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
   kern<<<(unsigned)(units.nunits * t.mtiles * t.ntiles), 256, smem, st>>>(
-      G, cout, F, cin, reinterpret_cast<const int2*>(rb->pairs), rb->pair_off_dev, units, t.mtiles, t.ntiles, part);
+      G, cout, F, cin, reinterpret_cast<const int2*>(rb->pairs), rb->pair_off_dev, units, t.mtiles, t.ntiles, flags,
+      part);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
 }
@@ -284,9 +292,9 @@ KgradTile kgrad_tile(const ssconv_rulebook* rb, int parts, int cin, int cout) {
 }
 
 int kgrad_tiles(const KgradRows& G, const KgradRows& F, int parts, int cin, int cout, const ssconv_rulebook* rb,
-                const KgradTile& t, const KgradUnits& units, float* part, hipStream_t st) {
+                const KgradTile& t, const KgradUnits& units, const SplitFlags& flags, float* part, hipStream_t st) {
   if (units.nunits == 0) return SSCONV_OK;
-#define SSK_GO(P_, M_, N_) return launch<P_, M_, N_>(G, F, cin, cout, rb, t, units, part, st)
+#define SSK_GO(P_, M_, N_) return launch<P_, M_, N_>(G, F, cin, cout, rb, t, units, flags, part, st)
   if (parts == 1) {
     if (t.wm == 7) SSK_GO(1, 7, 7);
     if (t.wm == 4 && t.wn == 4) SSK_GO(1, 4, 4);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "kgrad_mfma.hpp"
+#include "split_guard.hpp"
 
 namespace ssconv {
 
@@ -20,8 +21,10 @@ struct KgradTile {
 };
 KgradTile kgrad_tile(const ssconv_rulebook* rb, int parts, int cin, int cout);
 
-// part[u][o][i] (fp32) = sum over unit u's slice of R_s of grad_out[x][o] feats[y][i].
+// part[u][o][i] (fp32) = sum over unit u's slice of R_s of grad_out[x][o] feats[y][i].  flags (split rows): where a
+// word of the rows or of the sums is set afterwards, part is not valid.
 int kgrad_tiles(const KgradRows& grad_out, const KgradRows& feats, int parts, int cin, int cout,
-                const ssconv_rulebook* rb, const KgradTile& t, const KgradUnits& units, float* part, hipStream_t st);
+                const ssconv_rulebook* rb, const KgradTile& t, const KgradUnits& units, const SplitFlags& flags, float* part,
+                hipStream_t st);
 
 }  // namespace ssconv

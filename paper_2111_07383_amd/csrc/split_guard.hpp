@@ -21,6 +21,7 @@ struct SplitFlags {
   __host__ __device__ int* grad_out() const { return w + 1; }  // rows of grad_out
   __host__ __device__ int* kappa() const { return w + 2; }
   __host__ __device__ int* gathered() const { return w + 3; }  // sums of the gather
+  __host__ __device__ int* kgrad() const { return w + 4; }     // sums of the kernel gradient
 };
 
 int clear_split_flags(const SplitFlags& f, hipStream_t st);

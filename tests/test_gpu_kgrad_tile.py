@@ -88,3 +88,53 @@ def test_values_the_parts_cannot_carry():
     assert torch.equal(torch.isfinite(gc), fine)
     assert torch.equal(torch.isnan(gc), torch.isnan(want))
     assert fine.any() and not fine.all()
+
+
+def _forced(f):
+    """f() on the kernels on three bf16 parts at every size."""
+    ss.debug_set(3, 13)
+    try:
+        return f()
+    finally:
+        ss.debug_set(3, 0)
+
+
+# pairs per offset at the edges of the 32-pair chunks and 512-pair blocks; 3x3x3: empty and one-pair lists too
+SPLIT = [(n, 1) for n in (1, 31, 32, 33, 511, 512, 513, 2000)] + [(2, 3), (40, 3), (1100, 3), (7900, 3)]
+
+
+@pytest.mark.parametrize("scale", [(0, 0), (-120, 112), (100, -126)])
+@pytest.mark.parametrize("ci,co", [(8, 5), (40, 33), (104, 120)])
+@pytest.mark.parametrize("n,ksize", SPLIT)
+def test_split_rows_keep_24_bits(n, ksize, ci, co, scale):
+    """fp32 rows as three parts: a third part that is lost or taken from another place leaves 2^-18 of a product.
+    Per entry |error| <= (roundings + K + 8) 2^-24 of the sum of magnitudes, with a rounding per 32 pairs (scaled
+    values, which the fp32 matrix cores take over: per pair), which catches that up to some 30 pairs.  Over all
+    entries the errors are random, and their root mean square stays under 2^-24 (0.3 + 1 / sqrt(pairs)) (0.6 with a
+    rounding per pair): a running sum of n random terms is about 1 / sqrt(n) of their magnitudes, each rounding a
+    third of a unit of it, and sqrt(roundings) of them add up."""
+    rb, desc, basis, x, dy, W = _layer(n, ksize, ci, co, torch.float32, seed=n)
+    x, dy = x * 2.0 ** scale[0], dy * 2.0 ** scale[1]
+    gc = _forced(lambda: ss.backward(x, dy, rb, W, desc, basis, need_feats=False)[1])
+    want, mag = _coeff_grad(rb, basis, ksize // 2 + 1, x, dy)
+    err = (gc.double() - want).abs() / mag
+    per, part = (32, 0.3) if scale == (0, 0) else (1, 0.6)
+    assert (err <= (rb.pair_counts.max() / per + rb.K + 8) * 2.0 ** -24).all()
+    assert err.square().mean().sqrt() <= 2.0 ** -24 * (part + max(rb.n_pairs, 1) ** -0.5)
+
+
+def test_whole_maps_the_parts_cannot_carry():
+    rb, desc, basis, x, dy, W = _layer(3000, 3, 24, 40, torch.float32)
+    dy = dy.abs() + 0.5
+    for v in (float("nan"), float("inf"), 3e36, 1e-37):
+        y = (x.abs() + 0.5) * v
+        run = lambda: ss.backward(y, dy, rb, W, desc, basis, need_feats=False)[1]  # noqa: E731
+        got = _forced(run).double()
+        ss.debug_set(3, 7)   # rows in registers, the fp32 matrix cores
+        try:
+            want = run().double()
+        finally:
+            ss.debug_set(3, 0)
+        assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+        fine = torch.isfinite(want)
+        assert ((got - want).abs()[fine] <= 2 * (3000 + 64) * 2.0 ** -24 * want.abs()[fine]).all()
