@@ -476,6 +476,14 @@ static bool use_kgrad_tiles(const ssconv_rulebook* rb, ssconv_dtype dt, int cin,
   // against 20)
   if (dt == SSCONV_F32 && v != 13 && rb->n_pairs < 6 * (rb->n_in + rb->n_out)) return false;
   if (dt == SSCONV_F32 ? v == 7 : v == 6 || (v == 12 && kgrad_supported(dt, cin, cout))) return false;
+  // padding bf16 rows is a launch: not where the generic kernel is done sooner, which takes about 18 ns per pair of
+  // the longest list and 32 channels (3x3x3: 979 pairs, 40 in the longest list, 71 -> 45: 17.5 us against 21.8;
+  // 360 and 300: 34 against 22; 2876 and 300, 4 -> 8: 19.6 against 22)
+  if (dt == SSCONV_BF16 && v != 13 && !(cin % 8 == 0 && cout % 8 == 0)) {
+    int64_t longest = 0;
+    for (int s = 0; s < rb->K; ++s) longest = std::max(longest, rb->pair_off[s + 1] - rb->pair_off[s]);
+    if (longest * (cin + cout) < 10000) return false;
+  }
   return rb->K <= kKgradMaxK && rb->n_in > 0 && rb->n_out > 0 &&
          rb->n_in * kgrad_row_bytes(dt, cin) < ((int64_t)1 << 31) && rb->n_out * kgrad_row_bytes(dt, cout) < ((int64_t)1 << 31);
 }
@@ -487,20 +495,13 @@ static bool use_kgrad_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin,
          (int64_t)rb->n_in * cin * 2 < ((int64_t)1 << 31) && (int64_t)rb->n_out * cout * 2 < ((int64_t)1 << 31);
 }
 
-// Work units of the kernel gradient: as many slices of every offset on the tile kernel (and the bf16 one in
-// columns, override 12), launched slice by slice; on the fp32 ring kernel slices of about equal length, enough
-// wavefront tasks for one round of the wavefront slots.
-static KgradUnits plan_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
+// Work units of the kernel gradient: slices of about equal length, on the tile kernel (and the bf16 one in
+// columns, override 12) with their launch order, on the fp32 ring kernel enough wavefront tasks for one round of
+// the wavefront slots.
+static KgradUnits plan_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout, KgradOrder* order) {
   if (dt == SSCONV_F32 && !use_kgrad_tiles(rb, dt, cin, cout))
     return kgrad_units(rb, kgrad_f32_units_want(rb, cin, cout));
-  KgradUnits u;
-  u.K = rb->K;
-  u.even = kgrad_tile(rb, dt == SSCONV_F32 ? 3 : 1, cin, cout).slices;
-  for (int s = 0; s <= rb->K; ++s) u.uoff[s] = s * u.even;
-  u.nunits = u.uoff[rb->K];
-  if (dt == SSCONV_BF16)
-    for (int i = 0; i < u.nunits && i < kKgradMaxUnits; ++i) u.order[i] = (uint16_t)(i % u.K * u.even + i / u.K);
-  return u;
+  return kgrad_units(rb, kgrad_tile(rb, dt == SSCONV_F32 ? 3 : 1, cin, cout).units, order);
 }
 
 int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
@@ -530,7 +531,8 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
   const size_t K = rb->K, sz = dtype_bytes(dt);
   size_t nparts;  // fp32 partial tiles of cout x cin
   if (use_kgrad_units(rb, dt, cin, cout)) {
-    nparts = (size_t)plan_units(rb, dt, cin, cout).nunits;
+    KgradOrder order;
+    nparts = (size_t)plan_units(rb, dt, cin, cout, &order).nunits;
   } else {
     L.nsplit = kgrad_supported(dt, cin, cout) ? kgrad_plan(rb, dt, cin, cout).nsplit : dw_nsplit(rb);
     nparts = (size_t)L.nsplit * K;
@@ -644,18 +646,19 @@ int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, i
   const int K = rb->K;
   const int64_t n = (int64_t)K * cin * cout;
   if (use_kgrad_units(rb, dt, cin, cout)) {
-    const KgradUnits units = plan_units(rb, dt, cin, cout);
+    KgradOrder order;
+    const KgradUnits units = plan_units(rb, dt, cin, cout, &order);
     if (rows.parts) {
       const SplitFlags flags{rows.parts == 3 ? (int*)(ws + L.flags) : nullptr};
       SSC_TRY(kgrad_tiles(rows.grad_out, rows.feats, rows.parts, cin, cout, rb, kgrad_tile(rb, rows.parts, cin, cout),
-                          units, flags, part, st));
+                          units, order, flags, part, st));
       if (rows.parts == 3)  // the same units on the fp32 matrix cores
         SSC_TRY(kgrad_f32(grad_out, feats, cin, cout, rb, units, part, st,
                           {flags.grad_out(), flags.feats(), flags.kgrad()}));
     } else if (dt == SSCONV_F32)
       SSC_TRY(kgrad_f32(grad_out, feats, cin, cout, rb, units, part, st));
     else
-      SSC_TRY(kgrad_bf16(grad_out, rb->n_out, feats, rb->n_in, cin, cout, rb, units, part, st));
+      SSC_TRY(kgrad_bf16(grad_out, rb->n_out, feats, rb->n_in, cin, cout, rb, units, order, part, st));
     hipStream_t rst = st;
     if (tail) {
       SSC_TRY(aux_fork(st, &rst));

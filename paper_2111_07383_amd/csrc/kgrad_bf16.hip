@@ -26,8 +26,6 @@
 // The unit's pair indices are staged in LDS in blocks of 1024, double-buffered and DMA'd one
 // block ahead.
 #include <algorithm>
-#include <utility>
-#include <vector>
 
 #include "gather_tile.hpp"
 #include "kgrad_mfma.hpp"
@@ -95,7 +93,7 @@ __global__ __launch_bounds__(256) void kgrad_bf16_kernel(const uint16_t* __restr
                                                          const uint16_t* __restrict__ F, int64_t f_rows, int cin,
                                                          const int2* __restrict__ pairs,
                                                          const int64_t* __restrict__ pair_off, KgradUnits units,
-                                                         int mtiles, int ntiles, float* __restrict__ part) {
+                                                         KgradOrder order, int mtiles, int ntiles, float* __restrict__ part) {
   using C = KB<W>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* stages = smem;
@@ -107,7 +105,7 @@ __global__ __launch_bounds__(256) void kgrad_bf16_kernel(const uint16_t* __restr
   // launch slot -> work unit (XCD-contiguous over the row-sorted order) -> (offset s, slice of
   // R_s), tile (mt, nt)
   const int tile = blockIdx.x % (mtiles * ntiles);
-  const int u = units.order[xcd_slot(blockIdx.x / (mtiles * ntiles), units.nunits)];
+  const int u = order.unit[xcd_slot(blockIdx.x / (mtiles * ntiles), units.nunits)];
   int s = 0;
   while (s + 1 < units.K && units.uoff[s + 1] <= u) ++s;
   const int j = u - units.uoff[s], ns = units.uoff[s + 1] - units.uoff[s];
@@ -334,11 +332,11 @@ __global__ __launch_bounds__(256) void reduce_units_kernel(const float* __restri
 
 }  // namespace
 
-KgradUnits kgrad_units(const ssconv_rulebook* rb, int want) {
+KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, KgradOrder* order) {
   KgradUnits u;
   u.K = rb->K;
   const int K = rb->K;
-  const int cap = kKgradMaxUnitsF32;
+  const int cap = order ? kKgradMaxUnits : kKgradMaxUnitsF32;
   int64_t total = 0;
   for (int s = 0; s < K; ++s) total += rb->pair_off[s + 1] - rb->pair_off[s];
   want = std::min(std::max(want, K), cap);
@@ -367,6 +365,17 @@ KgradUnits kgrad_units(const ssconv_rulebook* rb, int want) {
   u.uoff[0] = 0;
   for (int s = 0; s < K; ++s) u.uoff[s + 1] = u.uoff[s] + n[s];
   u.nunits = u.uoff[K];
+  if (!order) return u;
+  // launch order: by the centre of each unit's slice along R_s (pairs are sorted by output row) in 1024ths,
+  // ties by offset (counted, not compared: the host has microseconds)
+  constexpr int kPlaces = 1024;
+  int at[kPlaces + 1] = {};
+  auto place = [&](int s, int j) { return (int)((int64_t)(2 * j + 1) * (kPlaces / 2) / n[s]); };
+  for (int s = 0; s < K; ++s)
+    for (int j = 0; j < n[s]; ++j) ++at[place(s, j) + 1];
+  for (int p = 0; p < kPlaces; ++p) at[p + 1] += at[p];
+  for (int s = 0; s < K; ++s)
+    for (int j = 0; j < n[s]; ++j) order->unit[at[place(s, j)]++] = (uint16_t)(u.uoff[s] + j);
   return u;
 }
 
@@ -388,7 +397,7 @@ int kgrad_bf16_tile(int cin, int cout) {
 }
 
 int kgrad_bf16(const void* grad_out, int64_t n_out, const void* feats, int64_t n_in, int cin, int cout,
-               const ssconv_rulebook* rb, const KgradUnits& units, float* part, hipStream_t st) {
+               const ssconv_rulebook* rb, const KgradUnits& units, const KgradOrder& order, float* part, hipStream_t st) {
   if (units.nunits == 0) return SSCONV_OK;
   const int W = kgrad_bf16_tile(cin, cout);
   const int mtiles = (cout + 32 * W - 1) / (32 * W), ntiles = (cin + 32 * W - 1) / (32 * W);
@@ -400,7 +409,7 @@ int kgrad_bf16(const void* grad_out, int64_t n_out, const void* feats, int64_t n
     const int smem = KB<Wv>::SMEM;                                                                  \
     SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem)); \
     kern<<<grid, 256, smem, st>>>((const uint16_t*)grad_out, n_out, cout, (const uint16_t*)feats, n_in, cin, \
-                                  pairs, rb->pair_off_dev, units, mtiles, ntiles, part);            \
+                                  pairs, rb->pair_off_dev, units, order, mtiles, ntiles, part);            \
   } while (0)
   if (W == 2) SSK_LAUNCH(2);
   else if (W == 4) SSK_LAUNCH(4);

@@ -22,18 +22,20 @@ KgradPlan kgrad_plan(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
 // Work units of the kernel gradient: offset s owns units uoff[s] .. uoff[s+1]-1, which cut its pair list R_s
 // into near-equal slices (passed to the kernels by value).
 constexpr int kKgradMaxK = 125;  // ksize <= 5
-constexpr int kKgradMaxUnits = 512;      // bf16 (launch order recorded for the kernel in columns)
-constexpr int kKgradMaxUnitsF32 = 4096;  // fp32 (one wavefront per unit and tile)
+constexpr int kKgradMaxUnits = 1024;     // of kernels that are launched in the order of the rows
+constexpr int kKgradMaxUnitsF32 = 4096;  // fp32 ring kernel (one wavefront per unit and tile)
 struct KgradUnits {
   int K = 0, nunits = 0;
-  int even = 0;  // > 0: every offset has this many units, launched slice by slice
   int uoff[kKgradMaxK + 1] = {};
-  uint16_t order[kKgradMaxUnits] = {};
+};
+// Launch slot -> unit, along the output rows.
+struct KgradOrder {
+  uint16_t unit[kKgradMaxUnits] = {};
 };
 
-// Units of the fp32 ring kernel: about `want` in total (at least one per offset, at most kKgradMaxUnitsF32),
+// About `want` units in total (at least one per offset; at most kKgradMaxUnitsF32, with order kKgradMaxUnits),
 // distributed over the offsets in proportion to their pair counts (largest remainders).
-KgradUnits kgrad_units(const ssconv_rulebook* rb, int want);
+KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, KgradOrder* order = nullptr);
 
 // fp32 kernel gradient over work units (per-wavefront LDS ring): usable when every row offset
 // fits 31 bits; the unit count that fills one round of wavefront slots.
@@ -48,7 +50,7 @@ int kgrad_bf16_tile(int cin, int cout);
 // part[u][o][i] (fp32) = sum over unit u's slice of R_s of grad_out[x][o] feats[y][i]; grad_out
 // holds n_out rows, feats n_in rows.
 int kgrad_bf16(const void* grad_out, int64_t n_out, const void* feats, int64_t n_in, int cin, int cout,
-               const ssconv_rulebook* rb, const KgradUnits& units, float* part, hipStream_t st);
+               const ssconv_rulebook* rb, const KgradUnits& units, const KgradOrder& order, float* part, hipStream_t st);
 
 // dW[s][:] = sum over the units of offset s of part[u][:] (n = cout * cin per unit), fixed order.
 // dW (field-pair-blocked, dw_block_pos) from the unit partials, each offset's in unit order.

@@ -57,7 +57,7 @@ template <int P, int WM, int WN>
 __global__ __launch_bounds__(256) void kgrad_tile_kernel(KgradRows G, int cout, KgradRows F, int cin,
                                                          const int2* __restrict__ pairs,
                                                          const int64_t* __restrict__ pair_off, KgradUnits units,
-                                                         int mtiles, int ntiles, SplitFlags flags,
+                                                         KgradOrder order, int mtiles, int ntiles, SplitFlags flags,
                                                          float* __restrict__ part) {
   if (P == 3 && (*flags.grad_out() | *flags.feats())) return;  // set before this kernel
   using C = KT<P, WM, WN>;
@@ -68,11 +68,15 @@ __global__ __launch_bounds__(256) void kgrad_tile_kernel(KgradRows G, int cout, 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w >> 1, wn = w & 1;
 
-  // launch slot -> slice j of R_s, slice by slice (an XCD runs all offsets of a stretch of rows together, which
-  // its L2 then holds), and tile
+  // launch slot -> slice j of R_s, in the order of the rows (an XCD runs all offsets of a stretch of rows
+  // together, which its L2 then holds), and tile
   const int tile = blockIdx.x % (mtiles * ntiles);
   const int slot = xcd_slot(blockIdx.x / (mtiles * ntiles), units.nunits);
-  const int j = slot / units.K, s = slot - j * units.K, ns = units.even, u = s * ns + j;
+  const int u = order.unit[slot];
+  int s = 0;
+  for (int b = 64; b > 0; b >>= 1)
+    if (s + b < units.K && units.uoff[s + b] <= u) s += b;
+  const int j = u - units.uoff[s], ns = units.uoff[s + 1] - units.uoff[s];
   const int m0 = tile / ntiles * 32 * WM, n0 = tile % ntiles * 32 * WN;
   const int64_t off = pair_off[s], cnt = pair_off[s + 1] - off;
   const int64_t beg = off + cnt * j / ns, end = off + cnt * (j + 1) / ns;
@@ -254,12 +258,12 @@ __global__ __launch_bounds__(256) void kgrad_tile_kernel(KgradRows G, int cout, 
 
 template <int P, int WM, int WN>
 int launch(const KgradRows& G, const KgradRows& F, int cin, int cout, const ssconv_rulebook* rb, const KgradTile& t,
-           const KgradUnits& units, const SplitFlags& flags, float* part, hipStream_t st) {
+           const KgradUnits& units, const KgradOrder& order, const SplitFlags& flags, float* part, hipStream_t st) {
   auto kern = kgrad_tile_kernel<P, WM, WN>;
   constexpr int smem = KT<P, WM, WN>::SMEM;
   SSC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
   kern<<<(unsigned)(units.nunits * t.mtiles * t.ntiles), 256, smem, st>>>(
-      G, cout, F, cin, reinterpret_cast<const int2*>(rb->pairs), rb->pair_off_dev, units, t.mtiles, t.ntiles, flags,
+      G, cout, F, cin, reinterpret_cast<const int2*>(rb->pairs), rb->pair_off_dev, units, order, t.mtiles, t.ntiles, flags,
       part);
   SSC_HIP(hipGetLastError());
   return SSCONV_OK;
@@ -268,10 +272,16 @@ int launch(const KgradRows& G, const KgradRows& F, int cin, int cout, const ssco
 }  // namespace
 
 // The tile with the least matrix work on padded channels and transpose reads (about 0.35 of a block's MFMA
-// each).  Slices: two rounds of the compute units for bf16, four for split rows, whose gathers miss the L2
-// more (an XCD runs all offsets of a slice's rows together: 36k sites, 5x5x5, 104 -> 104: 2 slices 780 us,
-// 4 661, 8 596, 12 617; 200k sites, 3x3x3, 208 -> 208 in bf16: 9 slices 463 us and 18 to add the partials
-// up, 18 446 and 24, 28 439 and 33), and at least 256 pairs each, below which the partials outweigh the rows.
+// each).  Units have at least 256 pairs, below which the partials outweigh the rows.
+// bf16: about equal pieces of the lists, so that one long list (isolated sites: nearly all pairs are those of
+// the centre) is spread over the chip: 40k isolated sites, 3x3x3, 208 -> 208, as many slices of every list 150
+// us, equal pieces 80.  As many units as workgroups are on the chip at a time (their LDS), at most 512;
+// on 7x7 tiles, of which a compute unit holds one, two rounds where the rows take longer than
+// the further partials (200k sites, 5.4M pairs, 208 -> 208: 9 slices of every list 463 us and 18 to add the
+// partials up, 18 slices 446 and 24; 80k sites, 1.4M pairs: 218 us with 18 slices in all, 170 with 256 units).
+// Split rows: four rounds, since their gathers miss the L2 more (an XCD runs all offsets of a stretch of rows
+// together: 36k sites, 5x5x5, 104 -> 104, as many slices of every list: 2 slices 780 us, 4 661, 8 596, 12 617;
+// in equal pieces the training step of that layer 1634 -> 1594).
 KgradTile kgrad_tile(const ssconv_rulebook* rb, int parts, int cin, int cout) {
   static const int shapes[][2] = {{2, 2}, {2, 4}, {4, 2}, {4, 4}, {7, 7}};
   KgradTile best{};
@@ -286,15 +296,17 @@ KgradTile kgrad_tile(const ssconv_rulebook* rb, int parts, int cin, int cout) {
     if (i == 0 || cost < best_cost) best = t, best_cost = cost;
   }
   const int tiles = best.mtiles * best.ntiles;
-  const int64_t rounds = parts == 1 ? 512 : 1024;
-  best.slices = (int)std::max<int64_t>(1, std::min<int64_t>(rounds / (rb->K * tiles), rb->n_pairs / (256 * (int64_t)rb->K)));
+  const int64_t by_pairs = rb->n_pairs / 256;
+  const int64_t most = parts == 3 ? 1024 : best.wm < 7 || rb->n_pairs >= 4000000 ? 512 : 256;
+  best.units = (int)std::max<int64_t>(1, std::min<int64_t>(most / tiles, by_pairs));
   return best;
 }
 
 int kgrad_tiles(const KgradRows& G, const KgradRows& F, int parts, int cin, int cout, const ssconv_rulebook* rb,
-                const KgradTile& t, const KgradUnits& units, const SplitFlags& flags, float* part, hipStream_t st) {
+                const KgradTile& t, const KgradUnits& units, const KgradOrder& order, const SplitFlags& flags,
+                float* part, hipStream_t st) {
   if (units.nunits == 0) return SSCONV_OK;
-#define SSK_GO(P_, M_, N_) return launch<P_, M_, N_>(G, F, cin, cout, rb, t, units, flags, part, st)
+#define SSK_GO(P_, M_, N_) return launch<P_, M_, N_>(G, F, cin, cout, rb, t, units, order, flags, part, st)
   if (parts == 1) {
     if (t.wm == 7) SSK_GO(1, 7, 7);
     if (t.wm == 4 && t.wn == 4) SSK_GO(1, 4, 4);

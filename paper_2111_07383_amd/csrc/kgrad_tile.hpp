@@ -14,17 +14,16 @@ struct KgradRows {
   int stride = 0;
 };
 
-// Tile of a workgroup in 32-channel steps (out, in), tiles covering the channels, slices that every
-// pair list is cut into.
+// Tile of a workgroup in 32-channel steps (out, in), tiles covering the channels, work units wanted.
 struct KgradTile {
-  int wm, wn, mtiles, ntiles, slices;
+  int wm, wn, mtiles, ntiles, units;
 };
 KgradTile kgrad_tile(const ssconv_rulebook* rb, int parts, int cin, int cout);
 
 // part[u][o][i] (fp32) = sum over unit u's slice of R_s of grad_out[x][o] feats[y][i].  flags (split rows): where a
 // word of the rows or of the sums is set afterwards, part is not valid.
 int kgrad_tiles(const KgradRows& grad_out, const KgradRows& feats, int parts, int cin, int cout,
-                const ssconv_rulebook* rb, const KgradTile& t, const KgradUnits& units, const SplitFlags& flags, float* part,
-                hipStream_t st);
+                const ssconv_rulebook* rb, const KgradTile& t, const KgradUnits& units, const KgradOrder& order,
+                const SplitFlags& flags, float* part, hipStream_t st);
 
 }  // namespace ssconv

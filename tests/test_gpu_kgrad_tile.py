@@ -41,7 +41,7 @@ def _coeff_grad(rb, basis, nq, x, dy):
     return out.reshape(-1), mag.reshape(-1)
 
 
-# (fp32 layers take the tile kernel from six pairs per row on, the fp32 ring kernel below)
+# (fp32 layers of few pairs take the fp32 ring kernel)
 CASES = [(1, 3, 1, 1), (33, 3, 5, 8), (200, 3, 40, 33), (7900, 3, 64, 65), (8000, 3, 71, 45), (2000, 5, 60, 128),
          (3000, 3, 129, 100), (7950, 3, 208, 225), (8000, 3, 2, 4)]
 
@@ -138,3 +138,33 @@ def test_whole_maps_the_parts_cannot_carry():
         assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
         fine = torch.isfinite(want)
         assert ((got - want).abs()[fine] <= 2 * (3000 + 64) * 2.0 ** -24 * want.abs()[fine]).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("ci,co", [(16, 24), (71, 45), (208, 225)])
+def test_one_long_list(ci, co, dtype):
+    """Isolated sites: the centre holds every pair, the other offsets none, so that one list is cut into most of
+    the units.  The bound of the sums over 32 pairs."""
+    cells = np.stack(np.meshgrid(*[np.arange(0, 40, 2)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    n = len(cells)
+    coords = torch.from_numpy(np.concatenate([np.zeros((n, 1)), cells], 1).astype(np.int32)).cuda()
+    rb = ss.build_rulebook(coords, 40, 3)
+    assert rb.n_pairs == n
+    desc = ss.basis_desc(((0, ci),), ((0, co),), 3, (0.0, 1.0))
+    basis = torch.from_numpy(ss.basis_build(desc)).cuda()
+    g = torch.Generator("cuda").manual_seed(0)
+    x = torch.randn((n, ci), device="cuda", generator=g).to(dtype)
+    dy = torch.randn((n, co), device="cuda", generator=g).to(dtype)
+    W = torch.zeros((27, co, ci), device="cuda", dtype=dtype)
+    gc = _forced(lambda: ss.backward(x, dy, rb, W, desc, basis, need_feats=False)[1])
+    want, mag = _coeff_grad(rb, basis, 2, x, dy)
+    assert ((gc.double() - want).abs() <= (n / 32 + rb.K + 64) * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("n,ksize,ci,co", CASES)
+def test_bf16_tiles_at_every_count(n, ksize, ci, co):
+    """Ragged bf16 layers of short lists, which the generic kernel takes otherwise."""
+    rb, desc, basis, x, dy, W = _layer(n, ksize, ci, co, torch.bfloat16)
+    gc = _forced(lambda: ss.backward(x, dy, rb, W, desc, basis, need_feats=False)[1])
+    want, mag = _coeff_grad(rb, basis, ksize // 2 + 1, x, dy)
+    assert ((gc.double() - want).abs() <= (rb.pair_counts.max() / 32 + rb.K + 64) * 2.0 ** -24 * mag + 1e-30).all()
