@@ -20,6 +20,7 @@
 // v_mfma_f32_16x16x32_bf16 (one step per chunk).  Any assignment of channels
 // to K-steps is valid as long as both operands use the same one.
 #include <algorithm>
+#include <cmath>
 
 #include "conv.hpp"
 #include "norm.hpp"
@@ -467,46 +468,74 @@ static size_t kgrad_copy_bytes(ssconv_dtype dt, int64_t n, int c) {
   return dt == SSCONV_BF16 && c % 8 == 0 ? 0 : align256((size_t)n * kgrad_row_bytes(dt, c));
 }
 
+// fp32: the tile kernel on split rows against the ring kernel on the fp32 matrix cores, by their times in us
+// fitted to measured layers.  Both write and read back the partials.  The ring kernel runs its tasks one or two to
+// a SIMD (25 + 4.1 B ps a pair and tile of B blocks of 16 x 16, more where some SIMDs have two tasks and others
+// one; a task of few pairs takes 0.15 + 0.018 B us per four of them).  The tile kernel splits the rows first, with
+// three launches more, and takes 45 to 170 ps a pair and tile, half as much again where the offsets have fewer
+// than four units each and their rows no longer meet in an L2; its launches are 12 us, and 8 more of the host's,
+// which is what small calls wait for.  Coefficient gradients, ring and tile kernel, us:
+//   80k sites, 3x3x3 (1.4M pairs): 16 -> 16 62 and 98, 71 -> 45 189 and 204, 104 -> 104 324 and 298
+//   80k sites, 5x5x5 (4.2M): 24 -> 24 172 and 223, 60 -> 120 674 and 520, 104 -> 104 973 and 790, 208 -> 208 3960
+//   and 4420
+//   5k sites, 3x3x3 (79k): 16 -> 16 26 and 31, 71 -> 45 58 and 44, 208 -> 208 179 and 149
+// (the tenth in favour of the ring kernel is what the fit is good for).  Where each row is gathered a few times
+// only the split alone is too much (60 -> 120 channels, 99k pairs of 79k rows: 22 us and 15 for the split against 36
+// on the ring kernel; 17k of 1.9k: 9 and 4 against 20).
+static bool split_kgrad_wins(const ssconv_rulebook* rb, int cin, int cout) {
+  if (rb->n_pairs < 6 * (rb->n_in + rb->n_out)) return false;
+  const KgradPlan r = kgrad_plan(rb, SSCONV_F32, cin, cout);
+  const KgradTile t = kgrad_tile(rb, 3, cin, cout);
+  const double pairs = (double)rb->n_pairs, partial = 8.0 * cin * cout / 4.5e6;
+  const double r_units = std::max(rb->K, kgrad_f32_units_want(rb, cin, cout)), t_units = std::max(rb->K, t.units);
+  const double r_tiles = r.mtiles * r.ntiles, t_tiles = t.mtiles * t.ntiles, B = r.wmb * r.wnb;
+  const double tasks = r_units * r_tiles, uneven = tasks > 1024 ? std::ceil(tasks / 1024) * 1024 / tasks : 1.0;
+  const double ring = std::max(pairs / r_units / 4 * (0.15 + 0.018 * B), pairs * r_tiles * (25 + 4.1 * B) * 1e-6 * uneven) +
+                      r_units * partial;
+  const double rows = rb->n_in * (4.0 * cin + kgrad_row_bytes(SSCONV_F32, cin)) +
+                      rb->n_out * (4.0 * cout + kgrad_row_bytes(SSCONV_F32, cout));
+  const double ps = (t.wm * t.wn == 4 ? 45 : t.wm * t.wn == 8 ? 110 : 170) * (t_units < 4 * rb->K ? 1.5 : 1.0);
+  const double tile = 20 + rows / 4.5e6 + pairs * t_tiles * ps * 1e-6 + t_units * partial;
+  return tile < 0.9 * ring;
+}
+
 // The kernel gradient on the bf16 matrix cores: every row offset below 2^31.  Overrides 6 and 12 keep the
 // other bf16 kernels (12 where it has the channels in columns), 7 the fp32 one that loads rows into registers.
 static bool use_kgrad_tiles(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
   const int64_t v = debug_gather_variant();
-  // splitting costs a pass over the rows: not where each is gathered a few times only (60 -> 120 channels, 99k
-  // pairs of 79k rows: 22 us and 15 for the split against 36 on the fp32 ring kernel; 17k of 1.9k: 9 and 4
-  // against 20)
-  if (dt == SSCONV_F32 && v != 13 && rb->n_pairs < 6 * (rb->n_in + rb->n_out)) return false;
+  if (dt == SSCONV_F32 && v != 13 && !split_kgrad_wins(rb, cin, cout)) return false;
   if (dt == SSCONV_F32 ? v == 7 : v == 6 || (v == 12 && kgrad_supported(dt, cin, cout))) return false;
-  // padding bf16 rows is a launch: not where the generic kernel is done sooner, which takes about 18 ns per pair of
-  // the longest list and 32 channels (3x3x3: 979 pairs, 40 in the longest list, 71 -> 45: 17.5 us against 21.8;
-  // 360 and 300: 34 against 22; 2876 and 300, 4 -> 8: 19.6 against 22)
+  // padding bf16 rows is a launch: not where the generic kernel is done sooner, whose time grows with the longest
+  // list (3x3x3: 979 pairs, 48 in the longest list, 71 -> 45: 17.5 us against 21.8, 60 -> 120: 18.7 against 22.2;
+  // 360 pairs, all but 60 in one list: 34 against 22 and 28 against 23; 17k and 625, 4 -> 8: 29 against 22)
   if (dt == SSCONV_BF16 && v != 13 && !(cin % 8 == 0 && cout % 8 == 0)) {
     int64_t longest = 0;
     for (int s = 0; s < rb->K; ++s) longest = std::max(longest, rb->pair_off[s + 1] - rb->pair_off[s]);
-    if (longest * (cin + cout) < 10000) return false;
+    if (longest * (cin + cout + 46) < 18000) return false;
   }
   return rb->K <= kKgradMaxK && rb->n_in > 0 && rb->n_out > 0 &&
          rb->n_in * kgrad_row_bytes(dt, cin) < ((int64_t)1 << 31) && rb->n_out * kgrad_row_bytes(dt, cout) < ((int64_t)1 << 31);
 }
 
+// The other kernels over work units.
 static bool use_kgrad_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
-  if (use_kgrad_tiles(rb, dt, cin, cout)) return true;
   if (dt == SSCONV_F32) return kgrad_f32_units_ok(rb, cin, cout);
   return debug_gather_variant() != 6 && kgrad_supported(dt, cin, cout) && rb->K <= kKgradMaxK &&
          (int64_t)rb->n_in * cin * 2 < ((int64_t)1 << 31) && (int64_t)rb->n_out * cout * 2 < ((int64_t)1 << 31);
 }
 
 // Work units of the kernel gradient: slices of about equal length, on the tile kernel (and the bf16 one in
-// columns, override 12) with their launch order, on the fp32 ring kernel enough wavefront tasks for one round of
+// columns, override 12) launched in the order of the rows, on the fp32 ring kernel enough wavefront tasks for one round of
 // the wavefront slots.
-static KgradUnits plan_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout, KgradOrder* order) {
-  if (dt == SSCONV_F32 && !use_kgrad_tiles(rb, dt, cin, cout))
-    return kgrad_units(rb, kgrad_f32_units_want(rb, cin, cout));
-  return kgrad_units(rb, kgrad_tile(rb, dt == SSCONV_F32 ? 3 : 1, cin, cout).units, order);
+static KgradUnits plan_units(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout, bool tiles) {
+  if (dt == SSCONV_F32 && !tiles)
+    return kgrad_units(rb, kgrad_f32_units_want(rb, cin, cout), kKgradMaxUnitsF32);
+  return kgrad_units(rb, kgrad_tile(rb, dt == SSCONV_F32 ? 3 : 1, cin, cout).units, kKgradMaxUnits);
 }
 
 int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, int cout, const ssconv_rulebook* rb,
              char* ws, const BwdLayout& L, BwdRows* r, hipStream_t st) {
-  if (!use_kgrad_tiles(rb, dt, cin, cout)) return SSCONV_OK;
+  if (!L.tiles) return SSCONV_OK;
   const size_t gb = kgrad_copy_bytes(dt, rb->n_out, cout), fb = kgrad_copy_bytes(dt, rb->n_in, cin);
   uint16_t* gc = gb ? (uint16_t*)(ws + L.rows) : nullptr;
   uint16_t* fc = fb ? (uint16_t*)(ws + L.rows + gb) : nullptr;
@@ -530,9 +559,10 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
   BwdLayout L;
   const size_t K = rb->K, sz = dtype_bytes(dt);
   size_t nparts;  // fp32 partial tiles of cout x cin
-  if (use_kgrad_units(rb, dt, cin, cout)) {
-    KgradOrder order;
-    nparts = (size_t)plan_units(rb, dt, cin, cout, &order).nunits;
+  L.tiles = use_kgrad_tiles(rb, dt, cin, cout);
+  if (L.tiles || use_kgrad_units(rb, dt, cin, cout)) {
+    L.units = plan_units(rb, dt, cin, cout, L.tiles);
+    nparts = (size_t)L.units.nunits;
   } else {
     L.nsplit = kgrad_supported(dt, cin, cout) ? kgrad_plan(rb, dt, cin, cout).nsplit : dw_nsplit(rb);
     nparts = (size_t)L.nsplit * K;
@@ -552,9 +582,8 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
   if (L.pair_feats()) o += align256(pair_path_bytes(rb, cout, cin, rb->n_in));
   // rows copied for the kernel gradient and behind them the scratch of the feature gradient, which then needs
   // no copy of grad_out of its own
-  const bool copies = use_kgrad_tiles(rb, dt, cin, cout);
-  const size_t gb = copies ? kgrad_copy_bytes(dt, rb->n_out, cout) : 0;
-  const size_t fb = copies ? kgrad_copy_bytes(dt, rb->n_in, cin) : 0;
+  const size_t gb = L.tiles ? kgrad_copy_bytes(dt, rb->n_out, cout) : 0;
+  const size_t fb = L.tiles ? kgrad_copy_bytes(dt, rb->n_in, cin) : 0;
   const size_t scratch = L.feats == BwdLayout::kSplit ? gather_split_bytes(rb->n_out, cout, cin, rb->n_in, rb->K)
                          : L.feats == BwdLayout::kBf16 ? gather_bf16_bytes(rb->n_out, cout, cin, rb->n_in, rb->K)
                                                        : 0;
@@ -563,7 +592,7 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
   o += std::max(gb, align256(scratch)) + fb;
   L.Wt = o;
   if (L.feats != BwdLayout::kBf16) o += align256(K * (size_t)cin * cout * sz);
-  L.split_rows = copies && dt == SSCONV_F32;
+  L.split_rows = L.tiles && dt == SSCONV_F32;
   L.flags = o;
   if (L.split_rows || L.feats == BwdLayout::kSplit) o += SplitFlags::kBytes;
   L.part = o;
@@ -645,20 +674,19 @@ int conv_backward_dw(const void* feats, const void* grad_out, ssconv_dtype dt, i
   if (tail) *tail = st;
   const int K = rb->K;
   const int64_t n = (int64_t)K * cin * cout;
-  if (use_kgrad_units(rb, dt, cin, cout)) {
-    KgradOrder order;
-    const KgradUnits units = plan_units(rb, dt, cin, cout, &order);
+  if (L.units.nunits > 0) {
+    const KgradUnits& units = L.units;
     if (rows.parts) {
       const SplitFlags flags{rows.parts == 3 ? (int*)(ws + L.flags) : nullptr};
       SSC_TRY(kgrad_tiles(rows.grad_out, rows.feats, rows.parts, cin, cout, rb, kgrad_tile(rb, rows.parts, cin, cout),
-                          units, order, flags, part, st));
+                          units, kgrad_order(units), flags, part, st));
       if (rows.parts == 3)  // the same units on the fp32 matrix cores
         SSC_TRY(kgrad_f32(grad_out, feats, cin, cout, rb, units, part, st,
                           {flags.grad_out(), flags.feats(), flags.kgrad()}));
     } else if (dt == SSCONV_F32)
       SSC_TRY(kgrad_f32(grad_out, feats, cin, cout, rb, units, part, st));
     else
-      SSC_TRY(kgrad_bf16(grad_out, rb->n_out, feats, rb->n_in, cin, cout, rb, units, order, part, st));
+      SSC_TRY(kgrad_bf16(grad_out, rb->n_out, feats, rb->n_in, cin, cout, rb, units, kgrad_order(units), part, st));
     hipStream_t rst = st;
     if (tail) {
       SSC_TRY(aux_fork(st, &rst));

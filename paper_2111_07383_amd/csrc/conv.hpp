@@ -13,7 +13,9 @@ struct BwdLayout {
   size_t gather = 0;  // scratch of the feature gradient's tile kernel, up to Wt, where the rows are copied for it
                       // (without copies it starts at `rows`)
   int nsplit = 1;
-  bool split_rows = false;  // the kernel gradient reads split rows
+  bool tiles = false;       // the kernel gradient on the tile kernel
+  bool split_rows = false;  // it reads split rows
+  KgradUnits units;         // its work units (none: per-offset splits)
   enum { kPair, kSplit, kBf16, kPlain } feats = kPlain;  // the kernel of the feature gradient
   bool pair_feats() const { return feats == kPair; }
 };

@@ -332,11 +332,10 @@ __global__ __launch_bounds__(256) void reduce_units_kernel(const float* __restri
 
 }  // namespace
 
-KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, KgradOrder* order) {
+KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, int cap) {
   KgradUnits u;
   u.K = rb->K;
   const int K = rb->K;
-  const int cap = order ? kKgradMaxUnits : kKgradMaxUnitsF32;
   int64_t total = 0;
   for (int s = 0; s < K; ++s) total += rb->pair_off[s + 1] - rb->pair_off[s];
   want = std::min(std::max(want, K), cap);
@@ -349,12 +348,14 @@ KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, KgradOrder* order) {
     rem[s] = quota - n[s];
     sum += n[s];
   }
-  // largest remainders first (the floors leave fewer than K units to hand out, one per offset at
-  // most); ties by offset, so the split is deterministic
-  int by_rem[kKgradMaxK];
-  for (int s = 0; s < K; ++s) by_rem[s] = s;
-  std::stable_sort(by_rem, by_rem + K, [&](int a, int b) { return rem[a] > rem[b]; });
-  for (int i = 0; i < K && sum < want && rem[by_rem[i]] > 0.0; ++i) ++n[by_rem[i]], ++sum;
+  if (sum < want) {
+    // largest remainders first (the floors leave fewer than K units to hand out, one per offset at
+    // most); ties by offset, so the split is deterministic
+    int by_rem[kKgradMaxK];
+    for (int s = 0; s < K; ++s) by_rem[s] = s;
+    std::stable_sort(by_rem, by_rem + K, [&](int a, int b) { return rem[a] > rem[b]; });
+    for (int i = 0; i < K && sum < want && rem[by_rem[i]] > 0.0; ++i) ++n[by_rem[i]], ++sum;
+  }
   while (sum > cap) {  // the one-unit minimum can overshoot: trim the largest offsets
     int big = 0;
     for (int s = 1; s < K; ++s)
@@ -365,18 +366,27 @@ KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, KgradOrder* order) {
   u.uoff[0] = 0;
   for (int s = 0; s < K; ++s) u.uoff[s + 1] = u.uoff[s] + n[s];
   u.nunits = u.uoff[K];
-  if (!order) return u;
-  // launch order: by the centre of each unit's slice along R_s (pairs are sorted by output row) in 1024ths,
-  // ties by offset (counted, not compared: the host has microseconds)
-  constexpr int kPlaces = 1024;
-  int at[kPlaces + 1] = {};
-  auto place = [&](int s, int j) { return (int)((int64_t)(2 * j + 1) * (kPlaces / 2) / n[s]); };
-  for (int s = 0; s < K; ++s)
-    for (int j = 0; j < n[s]; ++j) ++at[place(s, j) + 1];
-  for (int p = 0; p < kPlaces; ++p) at[p + 1] += at[p];
-  for (int s = 0; s < K; ++s)
-    for (int j = 0; j < n[s]; ++j) order->unit[at[place(s, j)]++] = (uint16_t)(u.uoff[s] + j);
   return u;
+}
+
+// By the centre of each unit's slice along R_s (pairs are sorted by output row) in 256ths, ties by offset (counted,
+// not compared: the host has microseconds).
+KgradOrder kgrad_order(const KgradUnits& u) {
+  KgradOrder o;
+  constexpr int kPlaces = 256;
+  int at[kPlaces + 1] = {};
+  for (int s = 0; s < u.K; ++s) {
+    const int n = u.uoff[s + 1] - u.uoff[s];
+    const double step = kPlaces / 2.0 / n;
+    for (int j = 0; j < n; ++j) ++at[(int)((2 * j + 1) * step) + 1];
+  }
+  for (int p = 0; p < kPlaces; ++p) at[p + 1] += at[p];
+  for (int s = 0; s < u.K; ++s) {
+    const int n = u.uoff[s + 1] - u.uoff[s];
+    const double step = kPlaces / 2.0 / n;
+    for (int j = 0; j < n; ++j) o.unit[at[(int)((2 * j + 1) * step)]++] = (uint16_t)(u.uoff[s] + j);
+  }
+  return o;
 }
 
 int reduce_units(const float* part, const KgradUnits& units, int cin, int cout, const FieldTab& fout,

@@ -22,7 +22,7 @@ KgradPlan kgrad_plan(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
 // Work units of the kernel gradient: offset s owns units uoff[s] .. uoff[s+1]-1, which cut its pair list R_s
 // into near-equal slices (passed to the kernels by value).
 constexpr int kKgradMaxK = 125;  // ksize <= 5
-constexpr int kKgradMaxUnits = 1024;     // of kernels that are launched in the order of the rows
+constexpr int kKgradMaxUnits = 1024;     // of kernels that are launched in the order of the rows (KgradOrder)
 constexpr int kKgradMaxUnitsF32 = 4096;  // fp32 ring kernel (one wavefront per unit and tile)
 struct KgradUnits {
   int K = 0, nunits = 0;
@@ -33,9 +33,10 @@ struct KgradOrder {
   uint16_t unit[kKgradMaxUnits] = {};
 };
 
-// About `want` units in total (at least one per offset; at most kKgradMaxUnitsF32, with order kKgradMaxUnits),
-// distributed over the offsets in proportion to their pair counts (largest remainders).
-KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, KgradOrder* order = nullptr);
+// About `want` units in total (at least one per offset, at most cap), distributed over the offsets in proportion to
+// their pair counts (largest remainders).
+KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, int cap);
+KgradOrder kgrad_order(const KgradUnits& u);
 
 // fp32 kernel gradient over work units (per-wavefront LDS ring): usable when every row offset
 // fits 31 bits; the unit count that fills one round of wavefront slots.
