@@ -379,17 +379,17 @@ double chunk_us(int mr, int nb) { return 0.15 + 0.012 * mr * nb; }
 TilePlan best_plan(int64_t row0, int64_t n_pos, int nt, int nb, int K, double chunks, size_t room, int* mr, double* cost) {
   TilePlan best{}, p;
   bool best_fits = false;
-  for (int i = 0; i < 6; ++i) {
-    const int m = 4 >> (i >> 1);
+  for (int i = 0; i < 3 * (1 + kCutChoices); ++i) {
+    const int m = 4 >> (i / (1 + kCutChoices)), cut = i % (1 + kCutChoices);
     p.row0 = row0;
     p.mt = (int)cdiv(n_pos - row0, 64 * m);
     p.nt = nt;
     const int64_t tiles = (int64_t)p.mt * nt;
     p.units = tiles * K;
     double c = chunks * chunk_us(m, nb);
-    if (i & 1) {
-      p.G = (int)std::min<int64_t>(kTileWG, p.units);
-      c = c * tiles / p.G + 8.0 + (double)part_bytes(p, m, nb, K) / 4e6;
+    if (cut) {
+      p.G = (int)std::min<int64_t>(kTileWG >> (cut - 1), p.units);
+      c = c * tiles / p.G + cut_us(p.G, tiles) + (double)part_bytes(p, m, nb, K) / 4e6;
     } else {
       p.G = (int)tiles;
       c *= cdiv(tiles, kTileWG);

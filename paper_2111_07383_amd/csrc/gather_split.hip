@@ -396,6 +396,7 @@ __global__ __launch_bounds__(256) void split_fixup(const float* __restrict__ par
 struct SplitShape {
   int nb, mr;
   TilePlan plan;
+  double us;  // of the gather and the pieces
 };
 
 size_t a3_bytes(int64_t n_src, int ca) { return align256((size_t)n_src * chunks32(ca) * 192); }
@@ -412,35 +413,33 @@ size_t shape_bytes(const SplitShape& s, int64_t n_src, int ca, int cb, int K) {
 // 0.3 + 0.0625 MR NB us (measured: 2.07 us at 4 x 7; the constant part is the barrier and the first
 // fragment reads, which is why tall tiles win where there are rows enough).  Either every workgroup
 // holds whole tiles, in rounds of one per compute unit, or the (tile, offset) sequence is cut evenly
-// over the compute units, which costs the pieces' traffic and one more launch (8 us and up).  Shapes
-// whose scratch fits the fixed region of the allocation-free forward come first, so that it gives
-// the same bits.
+// over the compute units, or over fewer workgroups, which costs the pieces' traffic and one more launch
+// (cut_us).  Shapes whose scratch fits the fixed region of the allocation-free forward come first, so that
+// it gives the same bits.
 SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   const int blocks = (cb + 15) / 16, tiles = (blocks + 7) / 8, per = (blocks + tiles - 1) / tiles;
-  SplitShape best, s;
+  SplitShape best{}, s{};
   s.nb = per <= 2 ? 2 : per <= 4 ? 4 : per;
   s.plan.nt = (int)cdiv(cb, 16 * s.nb);
   s.plan.row0 = 0;
   const double chunks = pad_k(ca) / 32.0 * K;
-  double best_cost = 0.0;
   bool best_fits = false;
-  for (int i = 0; i < 6; ++i) {
-    s.mr = 4 >> (i >> 1);
+  for (int i = 0; i < 3 * (1 + kCutChoices); ++i) {
+    s.mr = 4 >> (i / (1 + kCutChoices));
     s.plan.mt = (int)cdiv(n_pos, 64 * s.mr);
     const int64_t nt = (int64_t)s.plan.mt * s.plan.nt;
     s.plan.units = nt * K;
-    const bool cut = i & 1;
-    double cost = chunks * (0.3 + 0.0625 * s.mr * s.nb);
+    const int cut = i % (1 + kCutChoices);
+    s.us = chunks * (0.3 + 0.0625 * s.mr * s.nb);
     if (cut) {
-      s.plan.G = (int)std::min<int64_t>(kTileWG, s.plan.units);
-      cost = cost * nt / s.plan.G + 8.0 + (double)part_bytes(s, K) / 4e6;
+      s.plan.G = (int)std::min<int64_t>(kTileWG >> (cut - 1), s.plan.units);
+      s.us = s.us * nt / s.plan.G + cut_us(s.plan.G, nt) + (double)part_bytes(s, K) / 4e6;
     } else {
       s.plan.G = (int)std::min<int64_t>(nt, INT32_MAX);
-      cost *= cdiv(nt, kTileWG);
+      s.us *= cdiv(nt, kTileWG);
     }
     const bool fits = shape_bytes(s, n_src, ca, cb, K) <= SSCONV_NOALLOC_SCRATCH_BYTES;
-    if (i == 0 || (fits && !best_fits) || (fits == best_fits && cost < best_cost))
-      best = s, best_cost = cost, best_fits = fits;
+    if (i == 0 || (fits && !best_fits) || (fits == best_fits && s.us < best.us)) best = s, best_fits = fits;
   }
   return best;
 }

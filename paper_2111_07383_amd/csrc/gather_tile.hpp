@@ -32,6 +32,12 @@ struct TilePlan {
 };
 inline bool whole_tiles(const TilePlan& p, int K) { return p.units % ((int64_t)p.G * K) == 0; }
 
+// Time that cutting nt tiles over G workgroups costs beyond the pieces' traffic, in us: a launch, and a piece after
+// the other in the fix-up (300 rows, 5x5x5, 16 -> 16: five tiles of 51 pieces made the bf16 layer 36 us, with 64
+// workgroups 20; the generic kernel 24).  G is tried in halves from one per compute unit down.
+constexpr int kCutChoices = 4;
+inline double cut_us(int G, int64_t nt) { return 8.0 + 0.22 * G / (double)nt; }
+
 // Workgroup i -> slot such that each XCD (i % 8) runs a contiguous range of slots.
 __device__ __forceinline__ int xcd_slot(int i, int n) {
   const int x = i & 7, j = i >> 3, q = n >> 3, r = n & 7;

@@ -39,7 +39,7 @@ def _inverse(nbr, n_in):
     return inv
 
 
-SHAPES = [(1, 1, 1, 1, 1), (63, 3, 1, 8, 16), (65, 3, 1, 7, 3), (300, 3, 1, 24, 40), (257, 5, 1, 40, 113), (129, 1, 1, 33, 17),
+SHAPES = [(1, 1, 1, 1, 1), (63, 3, 1, 8, 16), (65, 3, 1, 7, 3), (300, 3, 1, 24, 40), (257, 5, 1, 40, 113), (300, 5, 1, 16, 24), (129, 1, 1, 33, 17),
           (3000, 3, 1, 56, 128), (3000, 3, 2, 104, 129), (5000, 5, 1, 16, 96), (9000, 3, 1, 120, 60), (13000, 5, 1, 48, 256)]
 
 

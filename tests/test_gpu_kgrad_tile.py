@@ -43,7 +43,7 @@ def _coeff_grad(rb, basis, nq, x, dy):
 
 # (fp32 layers of few pairs take the fp32 ring kernel)
 CASES = [(1, 3, 1, 1), (33, 3, 5, 8), (200, 3, 40, 33), (7900, 3, 64, 65), (8000, 3, 71, 45), (2000, 5, 60, 128),
-         (3000, 3, 129, 100), (7950, 3, 208, 225), (8000, 3, 2, 4)]
+         (300, 5, 16, 24), (3000, 3, 129, 100), (7950, 3, 208, 225), (8000, 3, 2, 4)]
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
