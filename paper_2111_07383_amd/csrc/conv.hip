@@ -313,6 +313,25 @@ int dispatch_gg(const void* src, int64_t n_src, int ca, const void* Bt, int cb, 
   return SSCONV_OK;
 }
 
+// Offsets that a tile of `rows` destination rows holds, were the pairs spread evenly (every site is its own
+// neighbour in a submanifold layer).
+double active_offsets(const ssconv_rulebook* rb, int64_t n_dst, int rows) {
+  const int own = rb->submanifold ? 1 : 0;
+  if (rb->K <= own || n_dst <= 0) return own;
+  const double share = ((double)rb->n_pairs - own * n_dst) / ((double)n_dst * (rb->K - own));
+  return own + (rb->K - own) * (1.0 - std::pow(1.0 - std::min(1.0, std::max(0.0, share)), rows));
+}
+
+// Time of the feature gradient by dispatch_gg in fp32, us.  gather_gemm walks the offsets in steps of 32 channels:
+// bound by a step's latency, or by the work of the workgroups that share a compute unit.
+double plain_us(const ssconv_rulebook* rb, int ca, int cb, int64_t n_dst) {
+  if (gather_mfma_supported(SSCONV_F32, ca, cb, rb->K))
+    return gather_mfma_us(ca, cb, n_dst, rb->K, active_offsets(rb, n_dst, kMfmaRows));
+  const int wnb = pick_wnb(cb);
+  const double tiles = (double)cdiv(n_dst, BM) * cdiv(cb, 16 * wnb);
+  return 5.0 + active_offsets(rb, n_dst, BM) * cdiv(ca, BK) * std::max(0.9 + 0.14 * wnb, tiles / 256 * (0.5 + 0.13 * wnb));
+}
+
 template <typename T, int WNB>
 void launch_dw(const void* G, int cout, const void* F, int cin, const int32_t* pairs, const int64_t* pair_off, int K,
                int nsplit, float* part, hipStream_t st) {
@@ -384,7 +403,7 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
   // the pair-list path needs its Y buffer; with a fixed scratch region too small for it the
   // output-stationary kernel runs instead (same sums, another order of the fp32 additions)
   const bool pair_fits = !(sc && sc->fixed()) || pair_path_bytes(rb, cin, cout, rb->n_out) <= sc->left();
-  if (dt == SSCONV_F32 && pair_fits && pair_path_wins(rb, dt, cin, cout, rb->n_out, true)) {
+  if (dt == SSCONV_F32 && pair_fits && pair_path_wins(rb, dt, cin, cout, rb->n_out)) {
     void* ws = nullptr;
     SSC_TRY(scratch_take(sc, &ws, pair_path_bytes(rb, cin, cout, rb->n_out), st));
     int rc;
@@ -555,6 +574,28 @@ int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, 
   return rc;
 }
 
+// The kernel of the fp32 feature gradient, by the times that the three are measured to take (the split one from a
+// tenth on; 5 us against it and 8 against the pair path for two and four launches more, which take the host's time
+// where it is what small calls wait for).  Feature gradients on the fp32 matrix cores, as pairs and split, us:
+//   300 sites, 3x3x3: 4 -> 8 channels 11, 18, 15; 32 -> 64 19, 21, 25; 120 -> 60 115, 23, 29; 208 -> 208 85, 39, 43
+//   5k sites, 3x3x3, stride 2: 60 -> 120 46, 28, 41; 71 -> 45 92, -, 37
+//   20k sites, 3x3x3: 32 -> 64 52, 51, 50; 104 -> 104 161, 158, 89
+//   80k sites, 3x3x3: 16 -> 16 44, 67, 55; 5x5x5: 104 -> 104 2210, 1735, 885; 208 -> 208, 20k sites 2121, 1286, 1354
+// (-: no pair path).  Generated output sets build the inverse map for all but the pair path.
+static auto feats_path(const ssconv_rulebook* rb, int cin, int cout) {
+  const int64_t v = debug_gather_variant();
+  const bool split = use_split(nullptr, rb->n_out, cout, cin, rb->n_in, rb->K);
+  const bool pair = (v == 0 || v == 9 || v == 11 || v == 12) && pair_path_supported(rb, SSCONV_F32, cout, cin);
+  if (v == 13) return split ? BwdLayout::kSplit : BwdLayout::kPlain;
+  if (v == 9 && pair) return BwdLayout::kPair;
+  const double inverse = rb->submanifold ? 0.0 : 4.0 + 0.4e-6 * rb->K * (8.0 * rb->n_in + 4.0 * rb->n_out);
+  const double t_plain = plain_us(rb, cout, cin, rb->n_in) + inverse;
+  const double t_split = 5.0 + 1.1 * gather_split_us(rb->n_out, cout, cin, rb->n_in, rb->K) + inverse;
+  const double t_pair = 8.0 + pair_path_us(rb, cout, cin, rb->n_in);
+  if (pair && t_pair < t_plain && (!split || t_pair < t_split)) return BwdLayout::kPair;
+  return split && t_split < t_plain ? BwdLayout::kSplit : BwdLayout::kPlain;
+}
+
 BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int cout) {
   BwdLayout L;
   const size_t K = rb->K, sz = dtype_bytes(dt);
@@ -569,10 +610,8 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
   }
   size_t o = 0;
   if (rb->n_in > 0 && rb->n_out > 0) {
-    if (dt == SSCONV_F32 && pair_path_wins(rb, dt, cout, cin, rb->n_in, false))
-      L.feats = BwdLayout::kPair;
-    else if (dt == SSCONV_F32 && use_split(nullptr, rb->n_out, cout, cin, rb->n_in, rb->K))
-      L.feats = BwdLayout::kSplit;
+    if (dt == SSCONV_F32)
+      L.feats = feats_path(rb, cin, cout);
     else if (use_bf16_kernel(nullptr, dt, rb->n_out, cout, cin, rb->n_in, rb->K))
       L.feats = BwdLayout::kBf16;
   }

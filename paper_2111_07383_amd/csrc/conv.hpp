@@ -32,7 +32,8 @@ int bwd_rows(const void* feats, const void* grad_out, ssconv_dtype dt, int cin, 
 
 // Pair-list GEMM for sparse fp32 layers (pair_gemm.hip).
 bool pair_path_supported(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb);
-bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst, bool forward);
+bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst);
+double pair_path_us(const ssconv_rulebook* rb, int ca, int cb, int64_t n_dst);
 size_t pair_path_bytes(const ssconv_rulebook* rb, int ca, int cb, int64_t n_dst);
 // sink (optional): the reduce pass also leaves the Norm statistics of dst there (norm.hpp).
 int pair_gemm(const void* src, int ca, const void* Bt, int cb, const ssconv_rulebook* rb, int sel_in, void* dst,

@@ -542,6 +542,16 @@ bool gather_mfma_supported(ssconv_dtype dt, int ca, int cb, int K) {
   return ca % 8 == 0 && ca >= 8 && K <= kMaxK && pick_cfg(dt, cb, K, INT64_MAX, &c);
 }
 
+// Fitted to 270 measured layers within a tenth: one workgroup to a compute unit.
+double gather_mfma_us(int ca, int cb, int64_t n_pos, int K, double active) {
+  const int wnb = column_blocks(SSCONV_F32, cb);
+  const int64_t tiles = (int64_t)cdiv(n_pos, kMfmaRows) * cdiv(cb, 16 * wnb);
+  const int ns = pick_nsplit(tiles, K);
+  const double rounds = cdiv(tiles * ns, 256), chunks = active * ca / kBK / ns;
+  return 6.6 + rounds * (chunks * (0.49 + 0.25 * wnb) + 0.077 * K) +
+         (ns > 1 ? 1.1 + 1.9e-6 * (ns + 1) * n_pos * cb : 0.0);
+}
+
 int gather_mfma(const void* src, int64_t n_src, ssconv_dtype dt, int ca, const void* Bt, int cb, const int32_t* nbr,
                 const int32_t* order, int64_t n_pos, int K, void* out, hipStream_t st, CallScratch* sc,
                 NormSink* sink, const OnlyIf& only) {

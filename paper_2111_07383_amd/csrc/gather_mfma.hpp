@@ -11,6 +11,10 @@ struct NormSink;
 // True when gather_mfma handles the shape (ca a multiple of 8, at most 128 offsets).
 bool gather_mfma_supported(ssconv_dtype dt, int ca, int cb, int K);
 
+// Its time in us (fp32); active: the offsets that occur in a tile of kMfmaRows rows.
+constexpr int kMfmaRows = 128;
+double gather_mfma_us(int ca, int cb, int64_t n_pos, int K, double active);
+
 // out[order ? order[p] : p][:] = sum_s Bt[s] (cb x ca) . src[nbr[s][p]] for p < n_pos.
 // src [*, ca], Bt [K][cb][ca] and out [*, cb] in dt; nbr [K][n_pos] (-1 = absent).
 // Offset splits (fp32 partials added in split order) take their partials from sc (nullptr: the

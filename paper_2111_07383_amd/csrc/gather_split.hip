@@ -478,6 +478,15 @@ size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   return shape_bytes(split_shape(n_src, ca, cb, n_pos, K), n_src, ca, cb, K);
 }
 
+// Fitted to 350 measured layers within a tenth: launches (the guard's among them), the rows read and written as
+// parts, kappa, the gather, the row tables of the tiles past one round.
+double gather_split_us(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+  const double rounds = (double)cdiv(n_pos, 256) * cdiv(cb, 128) / kTileWG;
+  return 13.5 + 0.5e-6 * n_src * (4.0 * ca + split_row_bytes(ca)) +
+         1e-6 * K * (4.0 * ca * cb + 6.0 * pad_k(ca) * pad16(cb)) + split_shape(n_src, ca, cb, n_pos, K).us +
+         0.1 * K * std::max(0.0, rounds - 1.0);
+}
+
 int64_t split_row_bytes(int ca) { return (int64_t)chunks32(ca) * 192; }
 
 int split_rows(const float* x, int64_t nx, int cx, uint16_t* x3, int* x_flag, const float* y, int64_t ny, int cy,

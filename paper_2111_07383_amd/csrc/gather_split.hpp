@@ -17,6 +17,8 @@ struct SplitKernel {
 bool gather_split_supported(int64_t n_src, int ca, int cb, int K);
 // Scratch of a call (the split operands and the partial tiles).
 size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K);
+// Its time in us.
+double gather_split_us(int64_t n_src, int ca, int cb, int64_t n_pos, int K);
 // out[p][:] = sum_s B[s] (cb x ca) . src[nbr[s][p]] for p < n_pos; src [n_src, ca], out [n_pos, cb].
 // rows3 (optional): the rows of src already split.  rows_flag (one of flags) is that of src's rows; where
 // one of the words is set afterwards, out is not valid.  Bt (optional): receives B[s][n][k] in fp32, which the

@@ -252,33 +252,30 @@ bool pair_path_supported(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int
          rb->n_pairs < ((int64_t)1 << 31) && (int64_t)rb->n_pairs * cb < ((int64_t)1 << 40);
 }
 
-// Cost models.  Forward, against the fp32 MFMA kernel (measured rates on MI355X): the output-stationary
-// kernel executes about pairs / density rows of MFMA work at ~100 TFLOP/s, density = pairs / (destination
-// rows x offsets) (a tile of 128 rows holds nearly every offset, so its zero rows follow the density);
+// Cost model of the forward (measured rates on MI355X): the output-stationary kernels execute about
+// pairs / density rows of MFMA work at ~100 TFLOP/s, density = pairs / (destination rows x
+// offsets) (a tile of 128 rows holds nearly every offset, so its zero rows follow the density);
 // this path does the useful products at ~80 TFLOP/s and moves Y (written, read) plus the gathered
-// rows at ~4 TB/s, plus ~8 us of launches.
-// Gradient, against the kernel on three bf16 parts, fitted to measured layers: that one does the products of
-// every destination row at every offset at ~185 TFLOP/s, plus ~20 us; this path mostly moves Y and the
-// gathered rows, 2.6 ps per pair and column and 1.05 ps per pair and channel, plus ~30 us of launches (120 ->
-// 60 channels, 3x3x3: 90k pairs on 29k rows 52 us against 87, 612k on 87k 180 against 212, 1.87M on 160k 538
-// against 399; 5x5x5: 1.68M on 87k 533 against 786, 1.96M on 50k 578 against 481).
-// Kernel-selection override 9 forces it, 10 forbids it.
-bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst, bool forward) {
+// rows at ~4 TB/s, plus ~8 us of launches.  Kernel-selection override 9 forces it, 10 forbids it.
+bool pair_path_wins(const ssconv_rulebook* rb, ssconv_dtype dt, int ca, int cb, int64_t n_dst) {
   if (!pair_path_supported(rb, dt, ca, cb) || n_dst <= 0) return false;
   const int64_t v = debug_gather_variant();
   if (v == 9) return true;
   if (v != 0 && v != 11 && v != 12) return false;  // 10 and the others forbid it (11, 12 concern other kernels)
-  const double P = (double)rb->n_pairs, prod = 2.0 * ca * cb;
-  if (forward) {
-    const double density = std::min(1.0, P / ((double)n_dst * rb->K));
-    const double flops = P * prod;
-    const double t_os = flops / density / 100e12;
-    const double t_pair = flops / 80e12 + P * (8.0 * cb + 4.0 * ca) / 4e12 + 8e-6;
-    return t_pair < 0.85 * t_os;
-  }
-  const double t_os = (double)n_dst * rb->K * prod / 185e12 + 20e-6;
-  const double t_pair = P * std::max(prod / 80e12, 2.6e-12 * cb + 1.05e-12 * ca) + 30e-6;
-  return t_pair < t_os;
+  const double P = (double)rb->n_pairs;
+  const double density = std::min(1.0, P / ((double)n_dst * rb->K));
+  const double flops = 2.0 * P * ca * cb;
+  const double t_os = flops / density / 100e12;
+  const double t_pair = flops / 80e12 + P * (8.0 * cb + 4.0 * ca) / 4e12 + 8e-6;
+  return t_pair < 0.85 * t_os;
+}
+
+// Time of a gradient on this path in us (fitted to 350 measured layers within a tenth): the launches, then what
+// is larger of the products and of the gathered rows and Y, the map filled and scattered, dst, the packed kappa.
+double pair_path_us(const ssconv_rulebook* rb, int ca, int cb, int64_t n_dst) {
+  const double P = (double)rb->n_pairs, n = (double)n_dst, prod = (double)ca * cb;
+  return 14.4 + 0.123 * rb->K + P * std::max(2 * prod / 75e6, (2.17 * cb + 0.8 * ca) * 1e-6) + 3.1e-6 * rb->K * n +
+         2.5e-6 * n * cb + 13e-6 * rb->K * prod;
 }
 
 static size_t y_bytes(const ssconv_rulebook* rb, int cb) { return ((size_t)rb->n_pairs * cb * 4 + 255) & ~(size_t)255; }
