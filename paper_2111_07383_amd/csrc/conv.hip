@@ -376,10 +376,12 @@ static bool use_split(const CallScratch* sc, int64_t n_src, int ca, int cb, int6
   return !(sc && sc->fixed()) || SplitFlags::kBytes + gather_split_bytes(n_src, ca, cb, n_pos, K) <= sc->left();
 }
 
-// Forwards below 2^35 multiply-adds keep the fp32 MFMA kernel and its bits: what follows a convolution may
-// decide by sign (ReLU, gates), so that any change of rounding can turn single decisions over, and a small
-// call gains little (2.5k sites, 3x3x3, 104 -> 128: 52 -> 35 us; 36k sites, 5x5x5, 104 -> 104, 49 G: 1100 ->
-// 490).  Gradients are linear in what they sum and take the faster kernel at every size.
+// Forwards below 2^35 multiply-adds (of n_out x K, not of pairs) keep the kernels that they have always had and
+// with them their bits, which a ReLU or a gate behind them may turn on.  That is a choice and no matter of
+// precision: above the line the same holds, the split kernel's errors are the smaller ones, and small calls would
+// gain as well (2.5k sites, 3x3x3, 104 -> 128: 52 -> 35 us).  Above it calls take half a millisecond and more and
+// the gain counts (36k sites, 5x5x5, 104 -> 104, 49 G: 1100 -> 445 us; 5.2M sites, 3x3x3, 16 -> 16: 3590 -> 2110;
+// 700k, 32 -> 64: 1850 -> 570).  The pair path is compared with the fp32 matrix cores on both sides of the line.
 static bool split_forward(const ssconv_rulebook* rb, int cin, int cout) {
   return debug_gather_variant() == 13 || (double)rb->n_out * rb->K * cin * cout >= 34359738368.0;
 }

@@ -11,12 +11,13 @@
 // The scheme is that of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype
 // for higher-precision computations" (2019).  For what three parts cannot carry see split_guard.hpp.
 //
-// Bound: the matrix cores (55 - 60% busy) and the texture path that feeds the LDS (63 KB of DMA per
-// 256 x 112 x 32 chunk).  Two workgroup-wide stages of 69 KB fill the LDS; tall tiles because LDS
-// reads per product fall with the tile (256 rows: 93 bytes a clock of 128).  Measured on a 36 555-site
-// 5x5x5 layer, 104 -> 104: 1100 us (fp32 MFMA, 286 tiles on 256 compute units) -> 490 us.  On the way:
-// chunks that straddle two 64-byte parts 544 us against 496 aligned; DMAs issued in one burst 568
-// against 534 spread out; kappa and rows always from L2 (a probe) 510 against 544, so memory is not it.
+// Bound: the matrix cores (63% busy) and the texture path that feeds the LDS (63 KB of DMA per
+// 256 x 112 x 32 chunk, 2.0 GB of a launch from past the L2 at 5 TB/s).  Two workgroup-wide stages of 69 KB fill
+// the LDS; tall tiles because LDS reads per product fall with the tile (256 rows: 93 bytes a clock of 128).
+// Measured on a 36 555-site 5x5x5 layer, 104 -> 104: 1100 us (fp32 MFMA, 286 tiles on 256 compute units) -> 445,
+// 411 of them this kernel.  On the way: chunks that straddle two 64-byte parts 544 us against 496 aligned; DMAs
+// issued in one burst 568 against 534 spread out; kappa and rows always from L2 (a probe) 510 against 544, so
+// memory is not what bounds it.
 #include <algorithm>
 
 #include "conv.hpp"
