@@ -407,7 +407,8 @@ int ssconv_interpolate_backward(ssconv_rulebook_t rb, const float* grad, int cha
  * next to the fp32 gather kernel); 12 = the bf16 kernel gradient stages its
  * operands as 16-byte granule columns instead of 64-byte quads (the same
  * results, bit for bit); 13 = the tile kernels at every size: fp32 on three bf16
- * parts in the forward and both gradients, bf16 in the kernel gradient; results
+ * parts in the forward and both gradients, bf16 in the kernel gradient, gates
+ * with rows staged through LDS; results
  * agree within the dtype's tolerance for every value); option 4 = kernel
  * timing: a nonzero value switches it on and clears this thread's log, 0
  * switches it off; while on, every gather-GEMM kernel launch (the one of

@@ -84,9 +84,18 @@ constexpr int kGateRows = 8;        // rows of a workgroup are a multiple of thi
 inline int64_t gate_tab_bytes(const GateTab& t) { return (t.n_fields * 8 + 15) / 16 * 16; }
 inline int64_t gate_row_bytes(const GateTab& t, int64_t es) { return (2 * t.C + t.G) * es; }
 
-// Rows of a workgroup, 0 when even the smallest number needs more LDS than kGateLds.  Few rows are
-// spread over at least two workgroups per compute unit where there are enough.
+// Rows of a workgroup, 0 when even the smallest number needs more LDS than kGateLds or the rows are too few: staging
+// is two more round trips and barriers, and a workgroup of 8 wide rows has many fields for its 256 threads.  Few rows
+// are spread over at least two workgroups per compute unit where there are enough.  By field and staged, forward, us:
+//   fp32: 28 fields, 40k rows 10.6 and 9.0, 3k rows 4.1 and 3.8; 80 fields, 40k rows 28 and 19, 100 rows 4.0 and 4.8
+//   bf16: 28 fields, 40k rows 10.1 and 12.1, 300k rows 61 and 44; 280 fields, 3k rows 7.5 and 10.5, 100 rows 4.1 and
+//   9.5, 40k rows 73 and 46
+//   scalars alone, which are addressed in order anyway: 5, 300k rows 5.6 and 6.3; 64, 40k rows 7.8 and 7.7, 300k 46
+//   and 32
+// Override 13 stages any number.
 inline int gate_rows(const GateTab& t, int64_t es, int64_t n) {
+  const int64_t line = t.G == 0 ? 4000000 : es == 4 ? 1000000 : 2000000;
+  if (n * t.n_fields < line && debug_gather_variant() != 13) return 0;
   const int64_t fit = (kGateLds - gate_tab_bytes(t)) / (gate_row_bytes(t, es) * kGateRows);
   if (kGateLds < gate_tab_bytes(t) || fit < 1) return 0;
   const int64_t want = (n + 512 * kGateRows - 1) / (512 * kGateRows);

@@ -1,5 +1,5 @@
 """The gate's kernels that stage rows through LDS against the ones that address memory by field
-(taken for arrays that start off a 16-byte boundary): the same bits, at the edges of a workgroup's
+(taken for few rows and for arrays that start off a 16-byte boundary): the same bits, at the edges of a workgroup's
 rows and at widths that just fit or exceed LDS; both against the oracle."""
 import numpy as np
 import pytest
@@ -34,7 +34,11 @@ def test_staged_rows(fields, n, dtype):
     dy = torch.from_numpy(rng.standard_normal((n, C)).astype(np.float32)).to("cuda", dtype)
     x[0, 0] = float("nan")
     x[-1, -1] = float("inf")
-    y, dx = P.gate_forward(fields, x), P.gate_backward(fields, x, dy)
+    P.debug_set(3, 13)   # staged at any number of rows
+    try:
+        y, dx = P.gate_forward(fields, x), P.gate_backward(fields, x, dy)
+    finally:
+        P.debug_set(3, 0)
     assert torch.equal(y.view(torch.uint8), P.gate_forward(fields, shifted(x)).view(torch.uint8))
     assert torch.equal(dx.view(torch.uint8), P.gate_backward(fields, shifted(x), shifted(dy)).view(torch.uint8))
     # a few roundings of fp32 (the sigmoid's exponential), one rounding of the result's type
