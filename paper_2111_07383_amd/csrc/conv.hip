@@ -497,8 +497,7 @@ static size_t kgrad_copy_bytes(ssconv_dtype dt, int64_t n, int c) {
 // than four units each and their rows no longer meet in an L2; its launches are 12 us, and 8 more of the host's,
 // which is what small calls wait for.  Coefficient gradients, ring and tile kernel, us:
 //   80k sites, 3x3x3 (1.4M pairs): 16 -> 16 62 and 98, 71 -> 45 189 and 204, 104 -> 104 324 and 298
-//   80k sites, 5x5x5 (4.2M): 24 -> 24 172 and 223, 60 -> 120 674 and 520, 104 -> 104 973 and 790, 208 -> 208 3960
-//   and 4420
+//   80k sites, 5x5x5 (4.2M): 24 -> 24 172 and 223, 60 -> 120 674 and 520, 104 -> 104 973 and 790
 //   5k sites, 3x3x3 (79k): 16 -> 16 26 and 31, 71 -> 45 58 and 44, 208 -> 208 179 and 149
 // (the tenth in favour of the ring kernel is what the fit is good for).  Where each row is gathered a few times
 // only the split alone is too much (60 -> 120 channels, 99k pairs of 79k rows: 22 us and 15 for the split against 36
@@ -510,6 +509,9 @@ static bool split_kgrad_wins(const ssconv_rulebook* rb, int cin, int cout) {
   const double pairs = (double)rb->n_pairs, partial = 8.0 * cin * cout / 4.5e6;
   const double r_units = std::max(rb->K, kgrad_f32_units_want(rb, cin, cout)), t_units = std::max(rb->K, t.units);
   const double r_tiles = r.mtiles * r.ntiles, t_tiles = t.mtiles * t.ntiles, B = r.wmb * r.wnb;
+  // sums of more pairs than these in one accumulator lose to the tile kernel's, which are rounded once per 32 pairs
+  // (60k sites, 5x5x5, 208 -> 208, 8400 pairs a unit: error 1.7e-6 of the result against 0.9e-6, 4138 and 4150 us)
+  if (B > kKgradFoldBlocks && pairs > kKgradRingPairs * r_units) return true;
   const double tasks = r_units * r_tiles, uneven = tasks > 1024 ? std::ceil(tasks / 1024) * 1024 / tasks : 1.0;
   const double ring = std::max(pairs / r_units / 4 * (0.15 + 0.018 * B), pairs * r_tiles * (25 + 4.1 * B) * 1e-6 * uneven) +
                       r_units * partial;

@@ -38,6 +38,10 @@ struct KgradOrder {
 KgradUnits kgrad_units(const ssconv_rulebook* rb, int want, int cap);
 KgradOrder kgrad_order(const KgradUnits& u);
 
+// Blocks of 16 x 16 per tile up to which the ring kernel keeps its sums short, and pairs per unit up to which they
+// are short enough in larger tiles.
+constexpr int kKgradFoldBlocks = 16, kKgradRingPairs = 2048;
+
 // fp32 kernel gradient over work units (per-wavefront LDS ring): usable when every row offset
 // fits 31 bits; the unit count that fills one round of wavefront slots.
 bool kgrad_f32_units_ok(const ssconv_rulebook* rb, int cin, int cout);

@@ -168,3 +168,22 @@ def test_bf16_tiles_at_every_count(n, ksize, ci, co):
     gc = _forced(lambda: ss.backward(x, dy, rb, W, desc, basis, need_feats=False)[1])
     want, mag = _coeff_grad(rb, basis, ksize // 2 + 1, x, dy)
     assert ((gc.double() - want).abs() <= (rb.pair_counts.max() / 32 + rb.K + 64) * 2.0 ** -24 * mag + 1e-30).all()
+
+
+@pytest.mark.parametrize("c", [8, 104])
+def test_long_fp32_units_keep_their_precision(c):
+    """13M pairs.  A rounding is of random sign and of about 0.4 2^-24 of a sum that grows along its run: 8 channels
+    (ring kernel, 256 roundings between two folds) and 104 (tile kernel, one per 32 of 26k pairs) stay under 16 of
+    2^-24 of the result, runs over a whole unit of 6500 pairs would be at 24 and more."""
+    n, ksize = 48, 5
+    ax = torch.arange(n, device="cuda", dtype=torch.int32)
+    xyz = torch.cartesian_prod(ax, ax, ax)
+    rb = ss.build_rulebook(torch.cat([torch.zeros_like(xyz[:, :1]), xyz], 1).contiguous(), n, ksize)
+    assert rb.n_pairs > 12_000_000
+    desc = ss.basis_desc(((0, c),), ((0, c),), ksize, (0.0, 1.0, 2.0))
+    basis = torch.from_numpy(ss.basis_build(desc)).cuda()
+    g = torch.Generator("cuda").manual_seed(7)
+    x, dy = (torch.randn((n ** 3, c), device="cuda", generator=g) for _ in range(2))
+    gc = ss.backward(x, dy, rb, torch.zeros((ksize ** 3, c, c), device="cuda"), desc, basis, need_feats=False)[1]
+    want = _coeff_grad(rb, basis, 3, x, dy)[0]
+    assert (gc.double() - want).norm() <= 16 * 2.0 ** -24 * want.norm()
