@@ -373,7 +373,8 @@ static bool use_bf16_kernel(const CallScratch* sc, ssconv_dtype dt, int64_t n_sr
 static bool use_split(const CallScratch* sc, int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   const int64_t v = debug_gather_variant();
   if (v == 1 || v == 2 || v == 3 || v == 8 || !gather_split_supported(n_src, ca, cb, K)) return false;
-  return !(sc && sc->fixed()) || SplitFlags::kBytes + gather_split_bytes(n_src, ca, cb, n_pos, K) <= sc->left();
+  return !(sc && sc->fixed()) ||
+         SplitFlags::kBytes + gather_split_bytes(n_src, ca, cb, n_pos, K, SplitPlans::kForward) <= sc->left();
 }
 
 // Forwards below 2^35 multiply-adds (of n_out x K, not of pairs) keep the kernels that they have always had and
@@ -423,7 +424,7 @@ int conv_forward(const void* feats, ssconv_dtype dt, int cin, const ssconv_ruleb
     if (rc == SSCONV_OK) {
       KernelTimer timer(st);
       rc = gather_split((const float*)feats, rb->n_in, cin, {(const float*)W, 0, 0}, cout, rb->nbr, rb->n_out, rb->K,
-                        (float*)out, flags, flags.feats(), st, sc);
+                        (float*)out, flags, flags.feats(), st, sc, SplitPlans::kForward);
       if (rc == SSCONV_OK)
         rc = dispatch_gg<float>(feats, rb->n_in, cin, W, cout, rb->nbr, rb->n_out, rb->K, out, st, nullptr, nullptr,
                                 {flags.feats(), flags.kappa(), flags.gathered()});
@@ -627,7 +628,8 @@ BwdLayout bwd_layout(const ssconv_rulebook* rb, ssconv_dtype dt, int cin, int co
   // no copy of grad_out of its own
   const size_t gb = L.tiles ? kgrad_copy_bytes(dt, rb->n_out, cout) : 0;
   const size_t fb = L.tiles ? kgrad_copy_bytes(dt, rb->n_in, cin) : 0;
-  const size_t scratch = L.feats == BwdLayout::kSplit ? gather_split_bytes(rb->n_out, cout, cin, rb->n_in, rb->K)
+  const size_t scratch = L.feats == BwdLayout::kSplit  ? gather_split_bytes(rb->n_out, cout, cin, rb->n_in, rb->K,
+                                                                            SplitPlans::kGradient)
                          : L.feats == BwdLayout::kBf16 ? gather_bf16_bytes(rb->n_out, cout, cin, rb->n_in, rb->K)
                                                        : 0;
   L.rows = o;
@@ -686,8 +688,8 @@ int conv_backward_feats(const void* grad_out, ssconv_dtype dt, int cin, int cout
     const OnlyIf only{flags.grad_out(), flags.kappa(), flags.gathered()};
     KernelTimer timer(st);
     SSC_TRY(gather_split((const float*)grad_out, rb->n_out, cout, {(const float*)W, 1, mirror ? 1 : 0}, cin, nbrT,
-                         rb->n_in, K, (float*)grad_feats, flags, flags.grad_out(), st, &sc, rows.grad_out_copy,
-                         (float*)Wt));
+                         rb->n_in, K, (float*)grad_feats, flags, flags.grad_out(), st, &sc, SplitPlans::kGradient,
+                         rows.grad_out_copy, (float*)Wt));
     return dispatch_gg<float>(grad_out, rb->n_out, cout, Wt, cin, nbrT, rb->n_in, K, grad_feats, st, nullptr, nullptr,
                               only);
   }

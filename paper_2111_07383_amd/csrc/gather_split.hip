@@ -415,9 +415,9 @@ size_t shape_bytes(const SplitShape& s, int64_t n_src, int ca, int cb, int K) {
 // fragment reads, which is why tall tiles win where there are rows enough).  Either every workgroup
 // holds whole tiles, in rounds of one per compute unit, or the (tile, offset) sequence is cut evenly
 // over the compute units, or over fewer workgroups, which costs the pieces' traffic and one more launch
-// (cut_us).  Shapes whose scratch fits the fixed region of the allocation-free forward come first, so that
-// it gives the same bits.
-SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
+// (cut_us).  A gradient's plan that is larger than the fixed region has to be a twentieth cheaper: closer than
+// that whole tiles are sooner done (60k sites, 3x3x3, 128 -> 128: modelled 248 and 245, measured 265 and 292).
+SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K, SplitPlans plans) {
   const int blocks = (cb + 15) / 16, tiles = (blocks + 7) / 8, per = (blocks + tiles - 1) / tiles;
   SplitShape best{}, s{};
   s.nb = per <= 2 ? 2 : per <= 4 ? 4 : per;
@@ -425,6 +425,7 @@ SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   s.plan.row0 = 0;
   const double chunks = pad_k(ca) / 32.0 * K;
   bool best_fits = false;
+  double best_us = 0;
   for (int i = 0; i < 3 * (1 + kCutChoices); ++i) {
     s.mr = 4 >> (i / (1 + kCutChoices));
     s.plan.mt = (int)cdiv(n_pos, 64 * s.mr);
@@ -439,8 +440,10 @@ SplitShape split_shape(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
       s.plan.G = (int)std::min<int64_t>(nt, INT32_MAX);
       s.us *= cdiv(nt, kTileWG);
     }
-    const bool fits = shape_bytes(s, n_src, ca, cb, K) <= SSCONV_NOALLOC_SCRATCH_BYTES;
-    if (i == 0 || (fits && !best_fits) || (fits == best_fits && s.us < best.us)) best = s, best_fits = fits;
+    const bool fits = shape_bytes(s, n_src, ca, cb, K) + SplitFlags::kBytes <= SSCONV_NOALLOC_SCRATCH_BYTES;
+    const double us = s.us * (fits ? 1.0 : 1.05);
+    if (i == 0 || (plans == SplitPlans::kForward && fits != best_fits ? fits : us < best_us))
+      best = s, best_fits = fits, best_us = us;
   }
   return best;
 }
@@ -475,16 +478,17 @@ int clear_split_flags(const SplitFlags& f, hipStream_t st) {
   return SSCONV_OK;
 }
 
-size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
-  return shape_bytes(split_shape(n_src, ca, cb, n_pos, K), n_src, ca, cb, K);
+size_t gather_split_bytes(int64_t n_src, int ca, int cb, int64_t n_pos, int K, SplitPlans plans) {
+  return shape_bytes(split_shape(n_src, ca, cb, n_pos, K, plans), n_src, ca, cb, K);
 }
 
 // Fitted to 350 measured layers within a tenth: launches (the guard's among them), the rows read and written as
 // parts, kappa, the gather, the row tables of the tiles past one round.
 double gather_split_us(int64_t n_src, int ca, int cb, int64_t n_pos, int K) {
   const double rounds = (double)cdiv(n_pos, 256) * cdiv(cb, 128) / kTileWG;
+  const double gather = split_shape(n_src, ca, cb, n_pos, K, SplitPlans::kGradient).us;
   return 13.5 + 0.5e-6 * n_src * (4.0 * ca + split_row_bytes(ca)) +
-         1e-6 * K * (4.0 * ca * cb + 6.0 * pad_k(ca) * pad16(cb)) + split_shape(n_src, ca, cb, n_pos, K).us +
+         1e-6 * K * (4.0 * ca * cb + 6.0 * pad_k(ca) * pad16(cb)) + gather +
          0.1 * K * std::max(0.0, rounds - 1.0);
 }
 
@@ -501,9 +505,9 @@ int split_rows(const float* x, int64_t nx, int cx, uint16_t* x3, int* x_flag, co
 
 int gather_split(const float* src, int64_t n_src, int ca, const SplitKernel& B, int cb, const int32_t* nbr,
                  int64_t n_pos, int K, float* out, const SplitFlags& flags, int* rows_flag, hipStream_t st, CallScratch* sc,
-                 const uint16_t* rows3, float* Bt) {
+                 SplitPlans plans, const uint16_t* rows3, float* Bt) {
   if (n_pos == 0) return SSCONV_OK;
-  const SplitShape s = split_shape(n_src, ca, cb, n_pos, K);
+  const SplitShape s = split_shape(n_src, ca, cb, n_pos, K, plans);
   char* ws = nullptr;
   const size_t a3 = rows3 ? 0 : a3_bytes(n_src, ca);
   SSC_TRY(scratch_take(sc, (void**)&ws, a3 + b3_bytes(ca, cb, K) + part_bytes(s, K), st));

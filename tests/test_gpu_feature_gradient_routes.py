@@ -1,6 +1,6 @@
 """The fp32 feature gradient by every kernel that its cost model may pick (the fp32 matrix cores, the pair lists,
 three bf16 parts) and by its own choice, against fp64: few and many rows, sparse and dense sites, channels in
-multiples of 8, of 4 and of neither, generated output sites, one offset."""
+multiples of 8, of 4 and of neither, generated output sites, one offset, cut tiles past 64 MiB of scratch."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 AUTO, PLAIN, PAIRS, NO_PAIRS, PARTS = 0, 3, 9, 10, 13
 LAYERS = [(1, 8, 3, 1, 4, 8), (300, 32, 3, 1, 104, 104), (300, 32, 5, 1, 24, 24), (700, 20, 3, 2, 60, 120),
           (700, 20, 3, 2, 71, 45), (2000, 16, 3, 1, 8, 4), (2000, 16, 5, 1, 16, 36), (5000, 24, 1, 1, 40, 33),
-          (7000, 20, 3, 1, 32, 64), (7000, 20, 3, 1, 13, 130)]
+          (7000, 20, 3, 1, 32, 64), (7000, 20, 3, 1, 13, 130), (25000, 36, 3, 1, 208, 208)]
 
 
 @pytest.mark.parametrize("n,grid,ksize,stride,ci,co", LAYERS)
